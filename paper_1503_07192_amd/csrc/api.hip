@@ -155,24 +155,12 @@ hipError_t dalloc(T** p, int64_t count) {
 
 int64_t round_up(int64_t x, int64_t t) { return (x + t - 1) / t * t; }
 
-// Rows of v valid ones that the composition kernels relax: whole 128-tiles,
-// but in the last, partial tile a wave skips its 16 rows of a half when they
-// all lie past the valid ones (a wave holds rows 16w .. 16w+15 and
-// 64+16w .. 64+16w+15 of the tile).
-double mp_rows(int32_t v) {
-  const int32_t rem = v % 128;
-  double rows = (double)(v - rem);
-  if (rem)
-    for (int w = 0; w < 4; w++) rows += (16 * w < rem ? 16 : 0) + (64 + 16 * w < rem ? 16 : 0);
-  return rows;
-}
+// Rows (or columns) of v valid ones in whole tiles of the composition's products.
+double mp_tiles(int32_t v) { return (double)round_up(v, 64); }
 
-// Columns of v valid ones that the composition kernels relax: whole
-// 128-tiles, and of the last, partial tile its first half alone when that
-// holds them all.
-double mp_cols(int32_t v) {
-  const int32_t rem = v % 128;
-  return (double)(v - rem) + (rem == 0 ? 0 : rem <= 64 ? 64 : 128);
+// Words of one pair's slot of the composition: XT, statistics and masks.
+int64_t mp_slot_words(int32_t Kp, int32_t Vp) {
+  return (int64_t)Kp * Vp + spq::mp_stats_words(Kp, Vp) + 2 * spq::mp_mask_words(Kp, Vp);
 }
 
 }  // namespace
@@ -230,23 +218,20 @@ struct spq_index {
   uint8_t* flag2 = nullptr;
   u32 *Mg = nullptr, *R = nullptr, *XT = nullptr, *BG2 = nullptr, *H = nullptr;
   int64_t* pairbase = nullptr;
-  // the composition's positions: per group its width (B2 vertices padded to
-  // a multiple of 4, then the others), their bound Vrp and the table
-  int32_t Vrp = 0;
-  std::vector<int32_t> h_W;
-  int32_t* pos = nullptr;
+  int4* meta = nullptr;  // per BG vertex: row offset, |B|, local index (composition stores)
   // level 3 (closure of BG2 by super-groups of gpt groups)
   int32_t nT = 0, gpt = 0, V3gp = 0, V3 = 0, m3pmax = 0;
   int64_t V3p = 0;
   std::vector<int32_t> h_tbase, h_tsize, h_m3, h_b3off;
   int32_t *tbase = nullptr, *tsize = nullptr, *b3list = nullptr, *b3rank = nullptr, *m3 = nullptr;
-  int32_t* pos3 = nullptr;  // the super-groups' positions
   int32_t* b3off = nullptr;
   uint8_t* flag3 = nullptr;
   // composition pair lists (level 2 or share, level 3)
   int2 *plist = nullptr, *plist3 = nullptr;
   int32_t npairs = 0, chunk = 0;
   u32 *M3 = nullptr, *R3 = nullptr, *XT3 = nullptr, *BG3 = nullptr;
+  spq::MpWork mp, mp3;                  // composition scratch, level 2 and 3
+  unsigned long long* mp_exec = nullptr;  // executed relaxations of the products
   // share mode
   int32_t share_comps = 0, share_groups = 0, S2 = 0, bf_rounds = 0;
   int64_t S2p = 0;
@@ -317,12 +302,13 @@ struct spq_index {
     void* ptrs[] = {comp, local, nb,   off,  bgoff, P,     order, bgcomp,  bglocal,
                     cnt,  fill,  moff, flag, sumc,  total, err,   members, M,      BG,
                     vrec, gT,    grp,   gbg0, gV,   bgrow, bgnb,  bggrp, b2list,  b2rank, m2,
-                    b2off, flag2, Mg,  R,    XT,    BG2,   H,     pairbase, pos,
+                    b2off, flag2, Mg,  R,    XT,    BG2,   H,     pairbase,
                     bgvert, label, bglabel, cert, A,    DT,    bfflag,  bfstamp, bfcnt, bflist,
                     sb_flag, sb_flagn, sb_list, sb_nlist, sb_rank, sb_nrank, sb_m, sb_n, sb_A3, sb_Aout,
                     xe, xcount, boff, bsize, bfirst, gblk,
                     eu_own, ev_own, w_own, tbase, tsize, b3list, b3rank, m3, b3off, flag3,
-                    M3, R3, XT3, BG3, plist, plist3, rowptr, adj, adeg, w_copy, pos3};
+                    M3, R3, XT3, BG3, plist, plist3, rowptr, adj, adeg, w_copy, meta,
+                    mp.stats, mp.mask, mp3.stats, mp3.mask, mp_exec};
     for (void* p : ptrs) pool_release(p);
   }
 };
@@ -375,33 +361,27 @@ static hipError_t make_pairs(int32_t rows, int32_t G, bool upper, int64_t slot_e
   const int64_t budget = std::min<int64_t>((int64_t)1 << 30,
                                            std::max<int64_t>((int64_t)1 << 26, out_elems / 32));
   const int64_t fit = budget / std::max<int64_t>(slot_elems, 1);
-  *chunk = (int32_t)std::max<int64_t>(1, std::min<int64_t>({(int64_t)*npairs, fit, 65535}));
+  *chunk = (int32_t)std::max<int64_t>(1, std::min<int64_t>({(int64_t)*npairs, fit, 65528}));
   hipError_t e = dalloc(dev, std::max<int64_t>(*npairs, 1));
   if (e != hipSuccess || h.empty()) return e;
   return hipMemcpyAsync(*dev, h.data(), sizeof(int2) * h.size(), hipMemcpyHostToDevice, s);
 }
 
-// The composition's positions from the level-2 boundary counts: widths and
-// their bound Vrp (a multiple of 128).
-static void set_positions(spq_index* X) {
-  X->h_W.resize(X->ngroups);
-  int64_t wmax = 0;
-  for (int32_t g = 0; g < X->ngroups; g++) {
-    X->h_W[g] = (int32_t)round_up(X->h_m2[g], 4) + X->h_gV[g] - X->h_m2[g];
-    wmax = std::max<int64_t>(wmax, X->h_W[g]);
-  }
-  X->Vrp = (int32_t)std::max<int64_t>(128, round_up(wmax, 128));
+// Relaxations of a pair's two products before pruning: the first over B2(a1)
+// (rows B2(a2), columns a1's vertices), the second over B2(a2) (rows: a1's,
+// columns: a2's vertices).
+static double pair_relax(const spq_index* X, int32_t a1, int32_t a2) {
+  return mp_tiles(X->h_m2[a2]) * mp_tiles(X->h_gV[a1]) * (double)X->h_m2[a1] +
+         mp_tiles(X->h_gV[a1]) * mp_tiles(X->h_gV[a2]) * (double)X->h_m2[a2];
 }
 
-// Executed relaxations of a pair's two products, the first over B2(a1)
-// (rows B2(a2), columns: a1's vertices outside B2(a1); its B2 columns are
-// copied from D2), the second over B2(a2) (rows: a1's positions, columns:
-// a2's vertices outside B2(a2)).
-static double xt_relax(const spq_index* X, int32_t a1, int32_t a2) {
-  return mp_rows(X->h_m2[a2]) * mp_cols(X->h_gV[a1] - X->h_m2[a1]) * (double)round_up(X->h_m2[a1], 16);
-}
-static double y_relax(const spq_index* X, int32_t a1, int32_t a2) {
-  return mp_rows(X->h_W[a1]) * mp_cols(X->h_gV[a2] - X->h_m2[a2]) * (double)round_up(X->h_m2[a2], 16);
+// Scratch of the composition for `chunk` pairs per launch.
+static hipError_t mp_work_alloc(spq_index* X, spq::MpWork* w, int32_t Kp, int32_t Vp, int32_t chunk) {
+  hipError_t e = dalloc(&w->stats, chunk * spq::mp_stats_words(Kp, Vp));
+  if (e == hipSuccess) e = dalloc(&w->mask, chunk * spq::mp_mask_words(Kp, Vp));
+  if (e == hipSuccess && !X->mp_exec) e = dalloc(&X->mp_exec, spq::MP_EXEC);
+  w->exec = X->mp_exec;
+  return e;
 }
 
 // The query kernel locates a pair block from the two vertex records alone:
@@ -485,23 +465,19 @@ static spq_status build_share(spq_index* X, spq::HierArgs& ha, int64_t m, bool p
   HIP_TRY(hipMemcpyAsync(X->bfirst, X->h_bfirst.data(), sizeof(int32_t) * (NB + 1), hipMemcpyHostToDevice,
                          s));
   HIP_TRY(hipMemcpyAsync(X->gblk, X->h_gblk.data(), sizeof(int32_t) * G, hipMemcpyHostToDevice, s));
-  set_positions(X);
-  const int32_t Vrp = X->Vrp;
-  // R's last row is read up to 127 words past its end (the second product's
-  // column tiles start past the B2 positions)
-  HIP_TRY(dalloc(&X->R, (int64_t)G * X->m2pmax * Vrp + 128));
-  HIP_TRY(dalloc(&X->pos, (int64_t)G * Vrp));
+  HIP_TRY(dalloc(&X->R, (int64_t)G * X->m2pmax * Vgp));
   // each output block (S1, S2) through the cheaper boundary: through B2(S2)
   // or, S1 and S2 exchanged, through B2(S1) (its first product then reads D2
   // transposed, which is the Bellman-Ford table)
-  auto cost = [&](int32_t a, int32_t b) { return xt_relax(X, a, b) + y_relax(X, a, b); };
+  auto cost = [&](int32_t a, int32_t b) { return pair_relax(X, a, b); };
   std::vector<uint8_t> swap((size_t)X->share_groups * G, 0);
   for (int32_t a1 = 0; a1 < X->share_groups; a1++)
     for (int32_t a2 = 0; a2 < G; a2++)
       swap[(size_t)a1 * G + a2] = a1 != a2 && cost(a2, a1) < cost(a1, a2);
-  HIP_TRY(make_pairs(X->share_groups, G, false, (int64_t)X->m2pmax * Vrp, X->h_elems, &X->plist,
+  HIP_TRY(make_pairs(X->share_groups, G, false, mp_slot_words(X->m2pmax, Vgp), X->h_elems, &X->plist,
                      &X->npairs, &X->chunk, s, &swap));
-  HIP_TRY(dalloc(&X->XT, (int64_t)X->chunk * X->m2pmax * Vrp));
+  HIP_TRY(dalloc(&X->XT, (int64_t)X->chunk * X->m2pmax * Vgp));
+  HIP_TRY(mp_work_alloc(X, &X->mp, X->m2pmax, Vgp, X->chunk));
   HIP_TRY(dalloc(&X->A, (int64_t)NB * BP * BP));
   // the Bellman-Ford matrix carries 128 spare rows: a row tile may start at
   // the last block's last level-2 id
@@ -535,8 +511,8 @@ static spq_status build_share(spq_index* X, spq::HierArgs& ha, int64_t m, bool p
                          hipMemcpyHostToDevice, s));
   ha.m2pmax = X->m2pmax; ha.V2 = X->V2; ha.V2p = V2p; ha.b2off = X->b2off; ha.R = X->R;
   ha.XT = X->XT; ha.BG2 = X->BG2; ha.H = X->H; ha.pairbase = X->pairbase;
-  ha.pos = X->pos; ha.Vrp = Vrp;
   ha.plist = X->plist; ha.npairs = X->npairs; ha.chunk = X->chunk;
+  ha.work = X->mp;
   ha.share_groups = X->share_groups; ha.S2 = X->S2; ha.S2p = X->S2p; ha.DT = X->DT;
   ha.D2t = X->DT; ha.d2tld = X->S2p;
   ha.xe = X->xe; ha.xcount = X->xcount;
@@ -645,21 +621,13 @@ static spq_status build_share(spq_index* X, spq::HierArgs& ha, int64_t m, bool p
     if (X->h_sbm[t] > 0)
       X->relax_bg_exec += (double)((X->h_sbn[t] + 127) / 128) * ntc * 128.0 * 128.0 *
                           (double)round_up(X->h_sbm[t], 16);
-  for (int32_t p1 = 0; p1 < X->share_groups; p1++)
-    for (int32_t p2 = 0; p2 < G; p2++) {
-      const bool sw = swap[(size_t)p1 * G + p2];
-      const int32_t a1 = sw ? p2 : p1, a2 = sw ? p1 : p2;  // the products' roles
-      X->relax_bg_exec += xt_relax(X, a1, a2);
-      const double y = y_relax(X, a1, a2);
-      X->relax_bg_exec += y;
-      X->relax_inner += y;
-    }
   X->inner_launches = (X->npairs + X->chunk - 1) / X->chunk;
   if (profile) {
     X->prof.resize(2 * X->inner_launches);
     for (auto& e : X->prof) HIP_TRY(hipEventCreate(&e));
     ha.evt = X->prof.data();
   }
+  HIP_TRY(spq::launch_mp_zero(X->mp, s));
   HIP_TRY(spq::launch_share_compose(ha, X->DT, s));
   return SPQ_OK;
 }
@@ -1139,6 +1107,8 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
     TRY(dalloc(&X->bgrow, V));
     TRY(dalloc(&X->bgnb, V));
     TRY(dalloc(&X->bggrp, V));
+    TRY(dalloc(&X->meta, V));
+    ha.meta = X->meta;
     // level-2 boundary flags depend on the edges only and are only ever set
     if (V > 0) TRY(hipMemsetAsync(X->flag2, 0, V, s));
     ha.V = V; ha.ngroups = G; ha.Vgp = Vgp; ha.m = m; ha.kc = inner_kc; ha.pivot = X->cpivot;
@@ -1217,16 +1187,7 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
     // executed relaxations of level 2 (its BG2 closure is counted with level 3)
     if (X->V2p > 0 && X->nT == 0)
       X->relax_bg_exec += spq::dense_fw_exec_relax(X->V2p / 128, 128, X->cpivot);
-    set_positions(X);
-    const int32_t Vrp = X->Vrp;
-    for (int32_t a1 = 0; a1 < G; a1++)
-      for (int32_t a2 = a1; a2 < G; a2++) {
-        if (X->V2p > 0) X->relax_bg_exec += xt_relax(X, a1, a2);
-        const double y = y_relax(X, a1, a2);
-        X->relax_bg_exec += y;
-        X->relax_inner += y;
-      }
-    TRY(make_pairs(G, G, true, (int64_t)X->m2pmax * Vrp, X->h_elems, &X->plist, &X->npairs,
+    TRY(make_pairs(G, G, true, mp_slot_words(X->m2pmax, Vgp), X->h_elems, &X->plist, &X->npairs,
                    &X->chunk, s));
     X->inner_launches = (X->npairs + X->chunk - 1) / X->chunk;
     if (profile) {
@@ -1235,11 +1196,10 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
       ha.evt = X->prof.data();
     }
     TRY(hipMemcpyAsync(X->b2off, X->h_b2off.data(), sizeof(int32_t) * (G + 1), hipMemcpyHostToDevice, s));
-    // R's last row is read up to 127 words past its end (the second
-    // product's column tiles start past the B2 positions)
-    TRY(dalloc(&X->R, (int64_t)G * X->m2pmax * Vrp + 128));
-    TRY(dalloc(&X->pos, (int64_t)G * Vrp));
-    TRY(dalloc(&X->XT, (int64_t)X->chunk * X->m2pmax * Vrp));
+    TRY(dalloc(&X->R, (int64_t)G * X->m2pmax * Vgp));
+    TRY(dalloc(&X->XT, (int64_t)X->chunk * X->m2pmax * Vgp));
+    TRY(mp_work_alloc(X, &X->mp, X->m2pmax, Vgp, X->chunk));
+    ha.work = X->mp;
     if (X->V2p > 0) TRY(dalloc(&X->BG2, X->V2p * X->V2p));
     TRY(dalloc(&X->H, X->h_elems));
     TRY(dalloc(&X->pairbase, (int64_t)G * G));
@@ -1247,8 +1207,7 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
                        hipMemcpyHostToDevice, s));
     ha.m2pmax = X->m2pmax; ha.V2 = X->V2; ha.V2p = X->V2p; ha.b2off = X->b2off; ha.R = X->R;
     ha.XT = X->XT; ha.BG2 = X->BG2; ha.H = X->H; ha.pairbase = X->pairbase;
-    ha.pos = X->pos; ha.Vrp = Vrp;
-    ha.plist = X->plist; ha.npairs = X->npairs; ha.chunk = X->chunk;
+      ha.plist = X->plist; ha.npairs = X->npairs; ha.chunk = X->chunk;
     if (X->certify) {
       ha.bglabel = X->bglabel;
       ha.cert_bad = X->cert + 1;
@@ -1257,7 +1216,8 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
     }
     if (X->nT == 0) {
       TRY(graph_segment(X, s, [&](hipStream_t st) -> hipError_t {
-        hipError_t e = spq::launch_hier_level2_prep(ha, st);
+        hipError_t e = spq::launch_mp_zero(X->mp, st);
+        if (e == hipSuccess) e = spq::launch_hier_level2_prep(ha, st);
         if (e == hipSuccess) e = spq::launch_hier_level2_close(ha, st);
         if (e == hipSuccess) e = spq::launch_hier_level2_compose(ha, st);
         return e;
@@ -1300,44 +1260,25 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
       X->V3 = X->h_b3off[nT];
       X->V3p = round_up(X->V3, 128);
       X->m3pmax = (int32_t)std::max<int64_t>(128, round_up(m3max, 128));
-      // the super-groups' positions (B3 vertices first, as the groups' at
-      // level 2): widths and their bound V3rp
-      std::vector<int32_t> w3(nT);
-      int64_t w3max = 0;
-      for (int32_t t = 0; t < nT; t++) {
-        w3[t] = (int32_t)round_up(X->h_m3[t], 4) + X->h_tsize[t] - X->h_m3[t];
-        w3max = std::max<int64_t>(w3max, w3[t]);
-      }
-      const int32_t V3rp = (int32_t)std::max<int64_t>(128, round_up(w3max, 128));
-      // executed relaxations of level 3 (the first product over T1's
-      // vertices outside B3, its B3 positions being copied; the second over
-      // T2's vertices outside B3)
+      // executed relaxations of level 3's closures
       X->relax_bg_exec += nT * spq::dense_fw_exec_relax(V3gp / 128, 128, X->cpivot);
       if (X->V3p > 0) X->relax_bg_exec += spq::dense_fw_exec_relax(X->V3p / 128, 128, X->cpivot);
-      for (int32_t t1 = 0; t1 < nT; t1++)
-        for (int32_t t2 = t1; t2 < nT; t2++) {
-          if (X->V3p > 0)
-            X->relax_bg_exec += mp_rows(X->h_m3[t2]) * mp_cols(X->h_tsize[t1] - X->h_m3[t1]) *
-                                (double)round_up(X->h_m3[t1], 16);
-          X->relax_bg_exec += mp_rows(w3[t1]) * mp_cols(X->h_tsize[t2] - X->h_m3[t2]) *
-                              (double)round_up(X->h_m3[t2], 16);
-        }
       TRY(hipMemcpyAsync(X->b3off, X->h_b3off.data(), sizeof(int32_t) * (nT + 1),
                          hipMemcpyHostToDevice, s));
-      // R3's last row is read up to 127 words past its end (as R's)
-      TRY(dalloc(&X->R3, (int64_t)nT * X->m3pmax * V3rp + 128));
-      TRY(dalloc(&X->pos3, (int64_t)nT * V3rp));
+      TRY(dalloc(&X->R3, (int64_t)nT * X->m3pmax * V3gp));
       int32_t np3 = 0, ch3 = 0;
-      TRY(make_pairs(nT, nT, true, (int64_t)X->m3pmax * V3rp, X->V2p * X->V2p / 2, &X->plist3,
+      TRY(make_pairs(nT, nT, true, mp_slot_words(X->m3pmax, V3gp), X->V2p * X->V2p / 2, &X->plist3,
                      &np3, &ch3, s));
-      TRY(dalloc(&X->XT3, (int64_t)ch3 * X->m3pmax * V3rp));
+      TRY(dalloc(&X->XT3, (int64_t)ch3 * X->m3pmax * V3gp));
+      TRY(mp_work_alloc(X, &X->mp3, X->m3pmax, V3gp, ch3));
+      la.work = X->mp3;
       la.plist = X->plist3; la.npairs = np3; la.chunk = ch3;
-      la.pos3 = X->pos3; la.V3rp = V3rp;
       if (X->V3p > 0) TRY(dalloc(&X->BG3, X->V3p * X->V3p));
       la.V3 = X->V3; la.V3p = X->V3p; la.m3pmax = X->m3pmax; la.b3off = X->b3off; la.R3 = X->R3;
       la.XT3 = X->XT3; la.BG3 = X->BG3; la.side = ha.side; la.sync = ha.sync;
       TRY(graph_segment(X, s, [&](hipStream_t st) -> hipError_t {
-        hipError_t e = spq::launch_level3_b(la, st);
+        hipError_t e = spq::launch_mp_zero(X->mp, st);
+        if (e == hipSuccess) e = spq::launch_level3_b(la, st);
         if (e == hipSuccess) e = spq::launch_hier_level2_compose(ha, st);
         return e;
       }));
@@ -1642,6 +1583,14 @@ spq_status spq_index_stats(const spq_index* X, spq_stats* st) {
   st->v_bg3 = X->V3;
   if (X->method == 2) st->v_bg_padded = X->Vgp;
   HIP_TRY(hipEventSynchronize(X->ev[4]));
+  if (X->mp_exec) {  // the products' relaxations, counted on the device
+    unsigned long long h[spq::MP_EXEC];
+    HIP_TRY(hipMemcpy(h, X->mp_exec, sizeof(h), hipMemcpyDeviceToHost));
+    for (int i = 0; i < spq::MP_EXEC; i++) {
+      st->relax_bg_exec += (double)h[i];
+      if (i >= spq::MP_EXEC / 2) st->relax_dominant += (double)h[i];
+    }
+  }
   for (size_t i = 0; i + 1 < X->prof.size(); i += 2) {
     float ms = 0;
     HIP_TRY(hipEventElapsedTime(&ms, X->prof[i], X->prof[i + 1]));
@@ -1796,8 +1745,8 @@ spq_status spq_minplus_batched(int32_t layout, int32_t groups, const int32_t* nv
     obase += (int64_t)nv[s1] * nv[s2];
     // through B2(S1) instead of B2(S2): the products' roles exchanged
     auto cost = [&](int32_t a, int32_t b) {
-      return mp_rows(nk[b]) * mp_cols(nv[a]) * (double)round_up(nk[a], 16) +
-             mp_rows(nv[a]) * mp_cols(nv[b]) * (double)round_up(nk[b], 16);
+      return mp_tiles(nk[b]) * mp_tiles(nv[a]) * (double)nk[a] +
+             mp_tiles(nv[a]) * mp_tiles(nv[b]) * (double)nk[b];
     };
     const bool sw = s1 != s2 && (assoc == 2 || (assoc == 1 && cost(s2, s1) < cost(s1, s2)));
     plist[p] = sw ? make_int2(s2, s1 | spq::PAIR_SWAP) : make_int2(s1, s2);
@@ -1807,7 +1756,7 @@ spq_status spq_minplus_batched(int32_t layout, int32_t groups, const int32_t* nv
   // pairs per launch: XT slots of kp x vp words within 256 MiB
   const int64_t slot = (int64_t)kp * vp;
   const int32_t chunk =
-      (int32_t)std::max<int64_t>(1, std::min<int64_t>({(int64_t)npairs, 65535, ((int64_t)1 << 26) / slot}));
+      (int32_t)std::max<int64_t>(1, std::min<int64_t>({(int64_t)npairs, 65528, ((int64_t)1 << 26) / slot}));
   Scratch sc(s);
   int2* d_plist = nullptr;
   int32_t *d_nk = nullptr, *d_nv = nullptr, *d_koff = nullptr, *d_voff = nullptr;
@@ -1818,6 +1767,10 @@ spq_status spq_minplus_batched(int32_t layout, int32_t groups, const int32_t* nv
   HIP_TRY(sc.get(&d_koff, groups + 1));
   HIP_TRY(sc.get(&d_voff, groups + 1));
   HIP_TRY(sc.get(&d_xt, (int64_t)chunk * slot));
+  spq::MpWork work;
+  HIP_TRY(sc.get(&work.stats, chunk * spq::mp_stats_words(kp, vp)));
+  HIP_TRY(sc.get(&work.mask, chunk * spq::mp_mask_words(kp, vp)));
+  HIP_TRY(sc.get(&work.exec, spq::MP_EXEC));
   HIP_TRY(hipMemcpyAsync(d_plist, plist.data(), sizeof(int2) * npairs, hipMemcpyHostToDevice, s));
   HIP_TRY(hipMemcpyAsync(d_nk, nk, sizeof(int32_t) * groups, hipMemcpyHostToDevice, s));
   HIP_TRY(hipMemcpyAsync(d_nv, nv, sizeof(int32_t) * groups, hipMemcpyHostToDevice, s));
@@ -1833,29 +1786,23 @@ spq_status spq_minplus_batched(int32_t layout, int32_t groups, const int32_t* nv
     a.R3 = const_cast<u32*>(reinterpret_cast<const u32*>(R));
     a.M3 = const_cast<u32*>(reinterpret_cast<const u32*>(M));
     a.XT3 = d_xt; a.BG2 = reinterpret_cast<u32*>(out); a.V2p = ldo;
-    a.plist = d_plist; a.npairs = npairs; a.chunk = chunk;
+    a.plist = d_plist; a.npairs = npairs; a.chunk = chunk; a.work = work;
     HIP_TRY(spq::launch_level3_compose(a, s));
   } else {
     // every group cut into consecutive components of cb vertices: per vertex
     // its component's first index, size and its own index inside it
     const int32_t V = voff[groups];
-    std::vector<int32_t> row(V), cnb(V), loc(V);
+    std::vector<int4> meta(V);
     for (int32_t g = 0; g < groups; g++)
       for (int32_t x = 0; x < nv[g]; x++) {
         const int32_t r0 = x - x % cb;
-        row[voff[g] + x] = r0;
-        cnb[voff[g] + x] = std::min(cb, nv[g] - r0);
-        loc[voff[g] + x] = x % cb;
+        meta[voff[g] + x] = make_int4(r0, std::min(cb, nv[g] - r0), x % cb, 0);
       }
-    int32_t *d_row = nullptr, *d_cnb = nullptr, *d_loc = nullptr;
+    int4* d_meta = nullptr;
     int64_t* d_pb = nullptr;
-    HIP_TRY(sc.get(&d_row, V));
-    HIP_TRY(sc.get(&d_cnb, V));
-    HIP_TRY(sc.get(&d_loc, V));
+    HIP_TRY(sc.get(&d_meta, V));
     HIP_TRY(sc.get(&d_pb, (int64_t)groups * groups));
-    HIP_TRY(hipMemcpyAsync(d_row, row.data(), sizeof(int32_t) * V, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(d_cnb, cnb.data(), sizeof(int32_t) * V, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(d_loc, loc.data(), sizeof(int32_t) * V, hipMemcpyHostToDevice, s));
+    HIP_TRY(hipMemcpyAsync(d_meta, meta.data(), sizeof(int4) * V, hipMemcpyHostToDevice, s));
     HIP_TRY(hipMemcpyAsync(d_pb, pairbase.data(), sizeof(int64_t) * groups * groups,
                            hipMemcpyHostToDevice, s));
     spq::HierArgs a{};
@@ -1864,9 +1811,9 @@ spq_status spq_minplus_batched(int32_t layout, int32_t groups, const int32_t* nv
     a.R = const_cast<u32*>(reinterpret_cast<const u32*>(R));
     a.Mg = const_cast<u32*>(reinterpret_cast<const u32*>(M));
     a.XT = d_xt; a.H = reinterpret_cast<u32*>(out); a.pairbase = d_pb;
-    a.bgrow = d_row; a.bgnb = d_cnb; a.bglocal = d_loc;
+    a.meta = d_meta;
     a.D2t = koff[groups] > 0 && Dt ? reinterpret_cast<const u32*>(Dt) : dD; a.d2tld = ld;
-    a.plist = d_plist; a.npairs = npairs; a.chunk = chunk;
+    a.plist = d_plist; a.npairs = npairs; a.chunk = chunk; a.work = work;
     HIP_TRY(spq::launch_hier_level2_compose(a, s));
   }
   HIP_TRY(hipStreamSynchronize(s));

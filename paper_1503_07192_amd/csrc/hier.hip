@@ -144,60 +144,6 @@ __global__ void k_r_gather(int32_t Vgp, int32_t m2pmax, const int32_t* __restric
   }
 }
 
-// Positions of every group (one workgroup each; the layout is described with
-// the composition below): B2 vertices, padding to a multiple of 4, the other
-// vertices ascending (found by b2rank < 0), padding up to Vrp.
-__global__ __launch_bounds__(256) void k_pos_build(const int32_t* __restrict__ gbg0,
-                                                   const int32_t* __restrict__ gV,
-                                                   const int32_t* __restrict__ b2rank,
-                                                   const int32_t* __restrict__ b2list,
-                                                   const int32_t* __restrict__ m2, int32_t Vgp,
-                                                   int32_t Vrp, int32_t* __restrict__ pos) {
-  __shared__ int32_t wsum[4];
-  const int s = blockIdx.x;
-  const int32_t g0 = gbg0[s], V = gV[s], k = m2[s], P2 = (k + 3) & ~3, W = P2 + V - k;
-  int32_t* out = pos + (int64_t)s * Vrp;
-  for (int32_t p = threadIdx.x; p < Vrp; p += 256) {
-    if (p < k) out[p] = b2list[(int64_t)s * Vgp + p];
-    else if (p < P2 || p >= W) out[p] = -1;
-  }
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  int32_t base = 0;
-  for (int32_t c0 = 0; c0 < V; c0 += 256) {
-    const int32_t p = c0 + (int32_t)threadIdx.x;
-    const bool f = p < V && b2rank[g0 + p] < 0;
-    const unsigned long long bal = __ballot(f);
-    const int32_t before = __popcll(bal & ((1ull << lane) - 1ull));
-    if (lane == 0) wsum[wid] = __popcll(bal);
-    __syncthreads();
-    int32_t woff = 0, tot = 0;
-    for (int i = 0; i < 4; i++) {
-      if (i < wid) woff += wsum[i];
-      tot += wsum[i];
-    }
-    if (f) out[P2 + base + woff + before] = p;
-    base += tot;
-    __syncthreads();
-  }
-}
-
-// R_S by position: R[S][r][p] = d_S(r-th B2 vertex, vertex at position p) for
-// r < m2[S]; INF on the other rows and at padding positions.
-__global__ void k_rpos_gather(int32_t Vgp, int32_t Vrp, int32_t m2pmax, const int32_t* __restrict__ m2,
-                              const int32_t* __restrict__ b2list, const int32_t* __restrict__ pos,
-                              const u32* __restrict__ Mg, u32* __restrict__ R) {
-  const int s = blockIdx.y;
-  const int32_t i = blockIdx.x;
-  u32* dst = R + ((int64_t)s * m2pmax + i) * Vrp;
-  const bool live = i < m2[s];
-  const u32* src = Mg + ((int64_t)s * Vgp + (live ? b2list[(int64_t)s * Vgp + i] : 0)) * Vgp;
-  const int32_t* ps = pos + (int64_t)s * Vrp;
-  for (int32_t p = threadIdx.x; p < Vrp; p += blockDim.x) {
-    const int32_t x = live ? ps[p] : -1;
-    dst[p] = x >= 0 ? src[x] : INF;
-  }
-}
-
 // BG2 matrix init: d_S between B2 vertices of one group, 0 on the diagonal,
 // INF elsewhere and on the padding.
 __global__ void k_bg2_init(int32_t V2, int64_t V2p, int32_t ngroups, const int32_t* __restrict__ b2off,
@@ -253,14 +199,16 @@ __global__ void k_bg2_edges(int64_t m, const int32_t* __restrict__ eu, const int
 // component's boundary count (the layout terms of D(S1,S2)).
 __global__ void k_hier_vmeta(int32_t V, const int32_t* __restrict__ bgcomp, const int32_t* __restrict__ bgoff,
                              const int32_t* __restrict__ nb, const int32_t* __restrict__ grp,
-                             const int32_t* __restrict__ gbg0, int32_t* __restrict__ bgrow,
-                             int32_t* __restrict__ bgnb, int32_t* __restrict__ bggrp) {
+                             const int32_t* __restrict__ gbg0, const int32_t* __restrict__ bglocal,
+                             int32_t* __restrict__ bgrow, int32_t* __restrict__ bgnb,
+                             int32_t* __restrict__ bggrp, int4* __restrict__ meta) {
   const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (x >= V) return;
   const int32_t c = bgcomp[x], s = grp[c];
   bgrow[x] = bgoff[c] - gbg0[s];
   bgnb[x] = nb[c];
   bggrp[x] = s;
+  if (meta) meta[x] = make_int4(bgoff[c] - gbg0[s], nb[c], bglocal[x], 0);
 }
 
 // Flat method: row x of the closed BG matrix into the blocked store of one
@@ -276,118 +224,15 @@ __global__ void k_flat_store(int32_t V, int64_t Vp, const u32* __restrict__ BG,
 }
 
 // ------------------------------------------------------- min-plus products --
-// c (128 x 128 in registers) = min(c, min over k < K of At[k][i] + B[k][j]).
-// Rows k of At and B are ldA / ldB apart; K is a multiple of 16 and is
-// streamed through LDS 16 rows at a time (double buffered, next chunk
-// prefetched into registers).  With MASKED, rows k >= kvalid and columns
-// i >= avalid of At read as INF without touching memory, and rows k >= kvalid
-// of B likewise.  Rows of c at or past rv are left unfinished (never
-// stored by the caller).
-template <bool MASKED>
-__device__ __forceinline__ uint4 mp_load_a(const u32* At, int64_t ldA, int k, int col, int kvalid,
-                                           int avalid) {
-  if (!MASKED) return *reinterpret_cast<const uint4*>(At + (int64_t)k * ldA + col);
-  if (k >= kvalid) return make_uint4(INF, INF, INF, INF);
-  const u32* p = At + (int64_t)k * ldA + col;
-  if (col + 3 < avalid) return *reinterpret_cast<const uint4*>(p);
-  return make_uint4(col < avalid ? p[0] : INF, col + 1 < avalid ? p[1] : INF,
-                    col + 2 < avalid ? p[2] : INF, INF);
-}
-
-template <bool MASKED>
-__device__ __forceinline__ uint4 mp_load_b(const u32* B, int64_t ldB, int k, int col, int kvalid) {
-  if (MASKED && k >= kvalid) return make_uint4(INF, INF, INF, INF);
-  return *reinterpret_cast<const uint4*>(B + (int64_t)k * ldB + col);
-}
-
-// The relaxations of one LDS chunk for a thread's first NR rows (8 all, 4
-// the first half of the tile, 0 none: the wave only stages chunks) and its
-// first NC columns (8 all, 4 the first half).
-template <int NR, int NC = 8>
-__device__ __forceinline__ void mp_chunk(u32 (&c)[8][8], const u32* sA, const u32* sB, int K) {
-  if (NR > 0) minplus_lds<128, NR, NC>(c, sA, sB, K);
-}
-
-// The rows a wave relaxes when only rows below rv of the tile are ever
-// stored: a thread's rows are h*64 + ty*4 + a and a wave holds four
-// consecutive ty (16 rows of each half), so a wave whose rows of the second
-// half (or of both halves) all lie at or past rv skips them, and its VALU
-// slots go to the other waves of its SIMD.  Every wave still stages its
-// share of each chunk and meets every barrier.
-__device__ __forceinline__ int wave_rows(int rv) {
-  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  return (rv >= 128 || 64 + 16 * w < rv) ? 8 : (16 * w < rv) ? 4 : 0;
-}
-
-template <bool MASKED, int NR, int NC>
-__device__ __forceinline__ void mp_stream128_n(u32 (&c)[8][8], const u32* At, int64_t ldA, const u32* B,
-                                               int64_t ldB, int K, int kvalid, int avalid, u32* sA,
-                                               u32* sB) {
-  constexpr int T = 128, KC = 16;
-  const int nch = K / KC;
-  if (nch <= 0) return;
-  // two uint4 of each operand per thread per chunk: rows e/32, columns 4*(e%32)
-  const int e0 = threadIdx.x, e1 = threadIdx.x + 256;
-  const int r0 = e0 >> 5, c0 = (e0 & 31) * 4, r1 = e1 >> 5, c1 = (e1 & 31) * 4;
-  uint4 pa0 = mp_load_a<MASKED>(At, ldA, r0, c0, kvalid, avalid);
-  uint4 pa1 = mp_load_a<MASKED>(At, ldA, r1, c1, kvalid, avalid);
-  uint4 pb0 = mp_load_b<MASKED>(B, ldB, r0, c0, kvalid);
-  uint4 pb1 = mp_load_b<MASKED>(B, ldB, r1, c1, kvalid);
-  reinterpret_cast<uint4*>(sA)[e0] = pa0;
-  reinterpret_cast<uint4*>(sA)[e1] = pa1;
-  reinterpret_cast<uint4*>(sB)[e0] = pb0;
-  reinterpret_cast<uint4*>(sB)[e1] = pb1;
-  __syncthreads();
-  for (int ch = 0; ch < nch; ch++) {
-    // the last iteration reloads its own chunk into the idle buffer (unused)
-    const int kn = (ch + 1 < nch ? ch + 1 : ch) * KC;
-    pa0 = mp_load_a<MASKED>(At, ldA, kn + r0, c0, kvalid, avalid);
-    pa1 = mp_load_a<MASKED>(At, ldA, kn + r1, c1, kvalid, avalid);
-    pb0 = mp_load_b<MASKED>(B, ldB, kn + r0, c0, kvalid);
-    pb1 = mp_load_b<MASKED>(B, ldB, kn + r1, c1, kvalid);
-    const int cur = (ch & 1) * KC * T, nxt = ((ch + 1) & 1) * KC * T;
-    mp_chunk<NR, NC>(c, sA + cur, sB + cur, KC);
-    reinterpret_cast<uint4*>(sA + nxt)[e0] = pa0;
-    reinterpret_cast<uint4*>(sA + nxt)[e1] = pa1;
-    reinterpret_cast<uint4*>(sB + nxt)[e0] = pb0;
-    reinterpret_cast<uint4*>(sB + nxt)[e1] = pb1;
-    __syncthreads();
-  }
-}
-
-// Columns of c at or past cv are likewise left unfinished: when cv <= 64
-// every thread relaxes only its columns of the tile's first half (a branch
-// uniform over the workgroup).
-template <bool MASKED>
-__device__ __forceinline__ void mp_stream128(u32 (&c)[8][8], const u32* At, int64_t ldA, const u32* B,
-                                             int64_t ldB, int K, int kvalid, int avalid, u32* sA,
-                                             u32* sB, int rv = 128, int cv = 128) {
-  const int nr = wave_rows(rv);
-  if (nr == 0)
-    mp_stream128_n<MASKED, 0, 8>(c, At, ldA, B, ldB, K, kvalid, avalid, sA, sB);
-  else if (cv > 64) {
-    if (nr == 8)
-      mp_stream128_n<MASKED, 8, 8>(c, At, ldA, B, ldB, K, kvalid, avalid, sA, sB);
-    else
-      mp_stream128_n<MASKED, 4, 8>(c, At, ldA, B, ldB, K, kvalid, avalid, sA, sB);
-  } else {
-    if (nr == 8)
-      mp_stream128_n<MASKED, 8, 4>(c, At, ldA, B, ldB, K, kvalid, avalid, sA, sB);
-    else
-      mp_stream128_n<MASKED, 4, 4>(c, At, ldA, B, ldB, K, kvalid, avalid, sA, sB);
-  }
-}
-
 // c = min(c, min over k < cnt of At[rows[k]][i] + B[bmap[rows[k]]][j]): the K
 // rows are gathered through the list `rows` (rows k themselves when it is
 // null; cnt of them, streamed 16 at a time, rows past cnt read as INF without
 // touching memory), and B's rows once more through bmap when it is not null.
-template <int NR>
-__device__ __forceinline__ void mp_stream128_rows_n(u32 (&c)[8][8], const u32* At, int64_t ldA,
-                                                    const u32* B, int64_t ldB,
-                                                    const int32_t* __restrict__ rows, int cnt,
-                                                    u32* sA, u32* sB,
-                                                    const int32_t* __restrict__ bmap) {
+__device__ __forceinline__ void mp_stream128_rows(u32 (&c)[8][8], const u32* At, int64_t ldA,
+                                                  const u32* B, int64_t ldB,
+                                                  const int32_t* __restrict__ rows, int cnt,
+                                                  u32* sA, u32* sB,
+                                                  const int32_t* __restrict__ bmap = nullptr) {
   constexpr int T = 128, KC = 16;
   const int nch = (cnt + KC - 1) / KC;
   if (nch <= 0) return;
@@ -417,7 +262,7 @@ __device__ __forceinline__ void mp_stream128_rows_n(u32 (&c)[8][8], const u32* A
     pb0 = ldb(kn + r0, c0);
     pb1 = ldb(kn + r1, c1);
     const int cur = (ch & 1) * KC * T, nxt = ((ch + 1) & 1) * KC * T;
-    mp_chunk<NR>(c, sA + cur, sB + cur, KC);
+    minplus_lds<128>(c, sA + cur, sB + cur, KC);
     reinterpret_cast<uint4*>(sA + nxt)[e0] = pa0;
     reinterpret_cast<uint4*>(sA + nxt)[e1] = pa1;
     reinterpret_cast<uint4*>(sB + nxt)[e0] = pb0;
@@ -426,78 +271,15 @@ __device__ __forceinline__ void mp_stream128_rows_n(u32 (&c)[8][8], const u32* A
   }
 }
 
-__device__ __forceinline__ void mp_stream128_rows(u32 (&c)[8][8], const u32* At, int64_t ldA,
-                                                  const u32* B, int64_t ldB,
-                                                  const int32_t* __restrict__ rows, int cnt,
-                                                  u32* sA, u32* sB,
-                                                  const int32_t* __restrict__ bmap = nullptr) {
-  // every row: the gathered operands leave no registers for a second copy
-  // of the loop (the kernels' last row tiles are a small share of them)
-  mp_stream128_rows_n<8>(c, At, ldA, B, ldB, rows, cnt, sA, sB, bmap);
-}
-
 // The composition kernels fit in 128 VGPRs without spilling: four waves per
 // SIMD (four workgroups per CU) instead of two or three.
 #define SPQ_MP_ATTR __attribute__((amdgpu_waves_per_eu(4, 4)))
-
-// c = min(c, the 128 x 128 tile at g), in the register layout of tile_load.
-__device__ __forceinline__ void tile_min128(u32 (&c)[8][8], const u32* __restrict__ g, int64_t ld) {
-  const int tx = tid_x(), ty = tid_y();
-#pragma unroll
-  for (int h = 0; h < 2; h++)
-#pragma unroll
-    for (int a = 0; a < 4; a++) {
-      const u32* row = g + (int64_t)(h * 64 + ty * 4 + a) * ld + tx * 4;
-#pragma unroll
-      for (int h2 = 0; h2 < 2; h2++) {
-        const uint4 v = *reinterpret_cast<const uint4*>(row + h2 * 64);
-        u32* r = c[h * 4 + a] + h2 * 4;
-        r[0] = min(r[0], v.x);
-        r[1] = min(r[1], v.y);
-        r[2] = min(r[2], v.z);
-        r[3] = min(r[3], v.w);
-      }
-    }
-}
 
 __device__ __forceinline__ void fill_inf(u32 (&c)[8][8]) {
 #pragma unroll
   for (int i = 0; i < 8; i++)
 #pragma unroll
     for (int j = 0; j < 8; j++) c[i][j] = INF;
-}
-
-// The composition runs over a list of group pairs (S1, S2), a chunk of it per
-// launch: blockIdx.y = pair plist[pbase + blockIdx.y], whose XT takes slot
-// blockIdx.y of the XT buffer (one slot per pair of the chunk).
-//
-// Workgroups are dealt round-robin to the eight XCDs in order of their linear
-// id, so with gridDim.x a multiple of 8 an XCD would get the same tile column
-// of every pair; the tiles past a group's last vertex (the padded last
-// column, empty for most groups) would then leave one XCD idle.  The tile of
-// a workgroup is therefore rotated by its pair.
-__device__ __forceinline__ int comp_tile() {
-  return (int)((blockIdx.x + blockIdx.y) % gridDim.x);
-}
-
-// Positions.  The two-level builds lay each group's vertices out in R, XT
-// and the composition's tiles by position: its B2 vertices first (b2list
-// order), padding up to a multiple of 4, then its other vertices ascending
-// (pos[group * Vrp + p] = local index, -1 for padding).  For y in B2(S2),
-// D(S1,S2)[x][y] = XT[y][x]: the first product already holds it (the
-// minimum of the second one is reached at b = y, d_S2(y, y) = 0, and no other
-// b goes lower, d_S2 being closed), so the first product stores those
-// entries and the second one runs only over S2's other vertices.  pos NULL:
-// positions are local indices and every column takes the second product.
-__device__ __forceinline__ int32_t pos_first(int32_t m2, bool skip) { return skip ? (m2 + 3) & ~3 : 0; }
-__device__ __forceinline__ int32_t pos_width(int32_t V, int32_t m2, bool skip) {
-  return skip ? ((m2 + 3) & ~3) + V - m2 : V;
-}
-// local index at position p of a group (base = group * Vrp), -1 for none
-__device__ __forceinline__ int32_t pos_local(const int32_t* __restrict__ pos, int64_t base, int32_t p,
-                                             int32_t W, int32_t V) {
-  if (p >= W) return -1;
-  return pos ? pos[base + p] : (p < V ? p : -1);
 }
 
 // The certificate's per-wave reduction: largest finite value, and whether
@@ -513,351 +295,701 @@ __device__ __forceinline__ void cert_reduce(u32 best, u32 wrong, u32* cert_bad, 
   }
 }
 
-// Stores tile c into its block of the query layout, whose element (x, y)
-// sits at rowoff(x) |Y| + nb(x) rowoff(y) + loc(x) nb(y) + loc(y) (below
-// |X| |Y| < 2^30: 32-bit offsets from the block's base).  Row i of the
-// thread is vertex lr[i] of the group whose first BG id is gr (-1: none),
-// column j vertex lc[j] of the group at gc.  ROWS_X: c's rows are the
-// block's rows x, else its columns y.  CERT: the certificate is folded in.
-template <bool CERT, bool ROWS_X>
-__device__ __forceinline__ void store_block(const u32 (&c)[8][8], u32* base, int32_t gr, int32_t gc,
-                                            const int32_t (&lr)[8], const int32_t (&lc)[8], u32 nY,
-                                            const int32_t* __restrict__ bgrow,
-                                            const int32_t* __restrict__ bgnb,
-                                            const int32_t* __restrict__ bglocal,
-                                            const int32_t* __restrict__ bglabel, u32* cert_bad,
-                                            u32* cert_mbg) {
-  u32 best = 0, wrong = 0;
-  // one half of the columns at a time (fewer live registers beside the tile)
-#pragma unroll
-  for (int h2 = 0; h2 < 2; h2++) {
-    // column terms: the block's y terms (rowoff, nb, loc), or with ROWS_X
-    // false its x terms (rowoff x |Y|, nb, loc); nb = 0 marks no column
-    u32 t0[4], t1[4], t2[4];
-    int32_t collab[4];
-#pragma unroll
-    for (int jj = 0; jj < 4; jj++) {
-      const int32_t l = lc[h2 * 4 + jj];
-      const int32_t qg = gc + (l >= 0 ? l : 0);
-      t0[jj] = ROWS_X ? (u32)bgrow[qg] : (u32)bgrow[qg] * nY;
-      t1[jj] = l >= 0 ? (u32)bgnb[qg] : 0u;
-      t2[jj] = (u32)bglocal[qg];
-      if (CERT) collab[jj] = bglabel[qg];
+// Where the composition's results go: the query layout (with or without the
+// certificate), or (level 3) the dense BG2 matrix.
+struct CompStore {
+  const int32_t* g0;       // first BG (level 3: BG2) id of every group
+  const int32_t* rank;     // per such id its index among the group's boundary vertices, -1 if
+                           // none (NULL, test hooks: every column is multiplied)
+  const int4* meta;        // per id: row offset, |B|, index inside its component
+  const u32* Mg;           // the groups' closures (leading dimension Vp)
+  int32_t ngroups;
+  const int64_t* pairbase;
+  u32* H;
+  const int32_t* bglabel;  // certificate
+  u32 *cert_bad, *cert_mbg;
+  // dense store (level 3): element (x, y) of the pair block (S1, S2) at
+  // dense[(g0[S1] + x) * ldo + g0[S2] + y]; NULL: the query layout
+  u32* dense;
+  int64_t ldo;
+};
+
+// The composition's products, pruned.
+//
+// Both products have the form out[x][y] = min over k < K of A[k][x] + B[k][y]
+// with K boundary vertices of one group, A the distances to them from far
+// away (the other group's vertices) and B rows of the group's own closure.
+// Most k never give a minimum: shortest paths from a whole region enter a
+// group through few of its boundary vertices.  For a row tile X (MP_SR rows)
+// let r(x) be any value per row and mn[k] <= A[k][x] - r(x) <= mx[k] for x in
+// X.  If mx[k'] + B[k'][y] <= mn[k] + B[k][y], then A[k'][x] + B[k'][y] <=
+// A[k][x] + B[k][y] for every x of X: column y needs k no more once it has
+// k'.  So with U[y] = min over k' of mx[k'] + B[k'][y], reached first at
+// arg[y], the rows X x columns Y of the product need only the k that some y
+// of Y has as arg[y] or with mn[k] + B[k][y] < U[y]: exactly the same minima
+// from (measured) a quarter to a half of the K.  r is near a row's minimum,
+// so that mx - mn stays small.
+//
+// A column y that is itself one of the K (y in B2 of its group) takes part in
+// neither: out[x][y] = A[y][x], its minimum (B[y][y] = 0, and no other k goes
+// lower, A being distances in a closed graph and B at least those distances), and the
+// product starts from it.
+//
+// Measured (MI355X): 400,000 Delaunay vertices in 128 groups, both levels'
+// products 79 -> 52 ms with all tests, the second one executing 0.48e12
+// relaxations instead of 1.45e12; build 117 -> 87 ms.  A 30,700-row share of a
+// 1024 x 1024 grid: 45 -> 22 ms, 0.13e12 of 0.93e12 relaxations; build 79.5 ->
+// 56.5 ms.  The test stays exact and costs little on operands it cannot prune.
+//
+// Three kernels per product and chunk of pairs: k_mp_stats (mn, mx per row
+// tile and k), k_mp_keep (per row tile and 64 columns a bit mask of the k to
+// keep), k_mp_prod (the product over the kept k).  The test costs 6 VALU
+// instructions per (k, 64 columns, row tile), 1/16 of the full product at 64
+// rows.
+// rows per tile of the statistics, row tiles per wave of k_mp_keep: the first
+// product has few rows (a group's boundary, 200 or so), the second a whole
+// group's.  There 128 rows per tile test half as often as 64 and keep 10 - 17%
+// more: second product and test 21.6 + 5.4 ms against 20.6 + 8.2 on 400,000
+// Delaunay vertices in 128 groups, 12.4 + 3.5 against 11.8 + 6.6 ms on a share
+// of 32 of a 1024 x 1024 grid's 256 groups
+template <int SIDE>
+constexpr int MP_SR = SIDE ? 128 : 64;
+template <int SIDE>
+constexpr int MP_RG = SIDE ? 8 : 4;
+constexpr int MP_T = 64;           // rows and columns of a product tile (one wave)
+constexpr int MP_KC = 4;           // k per LDS step of a product
+constexpr int MP_RING = 4;         // steps in LDS
+// Statistics are kept above MP_SHIFT (only their differences matter), the
+// upper ones clamped to [0, MP_BIG], the lower ones to [-MP_BIG - 1, MP_BIG],
+// B to MP_BIG: no sum overflows.  A bound with a term at MP_BIG is none; a lower
+// one at -MP_BIG - 1 is below every bound.
+constexpr int32_t MP_BIG = (1 << 29) - 1, MP_SHIFT = 1 << 27;
+constexpr int32_t MP_ALL = 1 << 30, MP_NONE = -(1 << 30);  // bounds above and below every sum
+
+typedef const __attribute__((address_space(4))) int32_t* cptr32;  // scalar loads
+
+// One chunk of the composition's pairs, as its kernels take it.
+struct MpArgs {
+  const int2* plist;     // pair of slot i: plist[pbase + i]
+  int32_t pbase, np;     // pairs of the launch
+  int32_t Vp, Kp;        // row length and rows per slot of XT, R
+  int32_t NT, NC, NW;    // row tiles (whole MP_RG), column tiles, mask words
+  const int32_t *m2, *gV, *b2off;
+  const u32* D2;         // D2: dense (pstride 0), or a column panel per group S2
+  int64_t ldd, pstride;  //   (pstride apart, column j = its j-th boundary vertex)
+  const u32* D2t;        // D2 transposed, for swapped pairs
+  int64_t ldt;
+  const u32* R;
+  u32* XT;
+  int32_t* stats;
+  unsigned long long* mask;
+  unsigned long long* exec;  // 16 counters
+  CompStore cs;
+};
+
+// One side of the composition for the pair of a slot: 0 the first product,
+// 1 the second.
+struct MpSide {
+  int32_t g;      // the group whose boundary vertices are the K and whose closure rows are B
+  int32_t K;      // its boundary vertices
+  int32_t W;      // its vertices: columns of the product
+  int32_t rows;   // rows of the product
+  const u32* A;   // A[k * lda + row]
+  int64_t lda;
+};
+
+__device__ __forceinline__ MpSide mp_side(int side, const MpArgs& a, int32_t slot) {
+  const int2 pr = a.plist[a.pbase + slot];
+  const bool sw = (pr.y & PAIR_SWAP) != 0;
+  const int32_t s1 = pr.x, s2 = pr.y & ~PAIR_SWAP;
+  MpSide m;
+  m.g = side ? s2 : s1;
+  m.K = a.m2[m.g];
+  m.W = a.gV[m.g];
+  if (side) {
+    m.rows = a.gV[s1];
+    m.A = a.XT + (int64_t)slot * a.Kp * a.Vp;
+    m.lda = a.Vp;
+  } else {
+    // D2[B2(s1)][B2(s2)] (row a, column b); a swapped pair reads it from the
+    // transposed table (rows: level-2 ids)
+    m.rows = a.m2[s2];
+    m.A = sw ? a.D2t + (int64_t)a.b2off[s1] * a.ldt + a.b2off[s2]
+             : a.D2 + (int64_t)s2 * a.pstride + (int64_t)a.b2off[s1] * a.ldd +
+                   (a.pstride ? 0 : a.b2off[s2]);
+    m.lda = sw ? a.ldt : a.ldd;
+  }
+  return m;
+}
+
+// mn, mx of every k for the row tile of blockIdx.x (pair blockIdx.y), as
+// stats[((slot * Kp + k) * 2) * NT + tile] and NT further on.  r(x) = the minimum over up to 16
+// of the K rows, spread evenly.  Sixteen-byte loads, MP_SR / 4 lanes per k:
+// bound by reading A once (plus the sampled rows).  Rows that are INF for every
+// k (unreachable) are left out; a tile without any other row keeps each
+// column's arg only.  Where a row is INF in the sample only, the tile's
+// statistics are made to keep every k.
+template <int SIDE>
+__global__ __launch_bounds__(256) void k_mp_stats(MpArgs a) {
+  constexpr int SR = MP_SR<SIDE>, L = SR / 4, G = 256 / L;  // lanes per k, k per step
+  static_assert(L == 16 || L == 32, "the reduction's lanes");
+  __shared__ u32 smin[16][SR];
+  __shared__ int odd, live;
+  const int32_t slot = blockIdx.y, tile = blockIdx.x;
+  const MpSide m = mp_side(SIDE, a, slot);
+  int32_t* out = a.stats + (int64_t)slot * a.Kp * 2 * a.NT + tile;
+  auto put = [&](int32_t k, int32_t mn, int32_t mx) {
+    out[(int64_t)k * 2 * a.NT] = mn;
+    out[(int64_t)(k * 2 + 1) * a.NT] = mx;
+  };
+  const int32_t x0 = tile * SR, nx = min(m.rows - x0, SR);
+  if (nx <= 0) {  // k_mp_keep reads whole groups of row tiles
+    for (int32_t k = threadIdx.x; k < m.K; k += 256) put(k, MP_BIG, 0);
+    return;
+  }
+  if (threadIdx.x == 0) odd = live = 0;
+  const int l = threadIdx.x % L, kg = threadIdx.x / L, x = l * 4;
+  const u32* A = m.A + x0;
+  auto load = [&](int32_t k) -> uint4 {
+    const u32* p = A + (int64_t)k * m.lda + x;
+    if (x + 3 < nx) return *reinterpret_cast<const uint4*>(p);
+    return make_uint4(x < nx ? p[0] : INF, x + 1 < nx ? p[1] : INF, x + 2 < nx ? p[2] : INF, INF);
+  };
+  {
+    const int32_t ns = min(m.K, 16);
+    for (int i = kg; i < 16; i += G) {
+      uint4 v = make_uint4(INF, INF, INF, INF);
+      if (i < ns) v = load((int32_t)((int64_t)i * m.K / ns));
+      *reinterpret_cast<uint4*>(&smin[i][x]) = v;
     }
+  }
+  __syncthreads();
+  u32 r[4] = {INF, INF, INF, INF};
 #pragma unroll
-    for (int i = 0; i < 8; i++) {
-      if (lr[i] < 0) continue;
-      const int32_t rg = gr + lr[i];
-      const u32 u0 = ROWS_X ? (u32)bgrow[rg] * nY : (u32)bgrow[rg];
-      const u32 u1 = (u32)bgnb[rg], u2 = (u32)bglocal[rg];
-      const int32_t labr = CERT ? bglabel[rg] : 0;
+  for (int i = 0; i < 16; i++) {
+    const uint4 v = *reinterpret_cast<const uint4*>(&smin[i][x]);
+    r[0] = min(r[0], v.x);
+    r[1] = min(r[1], v.y);
+    r[2] = min(r[2], v.z);
+    r[3] = min(r[3], v.w);
+  }
+  bool bad = false;
+  if (r[0] < INF || r[1] < INF || r[2] < INF || r[3] < INF) live = 1;
+  constexpr int KQ = 4;  // k per lane and step
+  for (int32_t k0 = 0; k0 < m.K; k0 += G * KQ) {
+    uint4 v4[KQ];
 #pragma unroll
-      for (int jj = 0; jj < 4; jj++) {
-        if (t1[jj] == 0) continue;
-        const u32 v = c[i][h2 * 4 + jj];
-        // rowoff(x) |Y| + nb(x) rowoff(y) + loc(x) nb(y) + loc(y)
-        const u32 off = ROWS_X ? u0 + __umul24(u1, t0[jj]) + __umul24(u2, t1[jj]) + t2[jj]
-                               : t0[jj] + __umul24(t1[jj], u0) + __umul24(t2[jj], u1) + u2;
-        base[off] = v;
-        if (CERT) {
-          if (v < INF) best = max(best, v);
-          else wrong |= (u32)(collab[jj] == labr);
+    for (int q = 0; q < KQ; q++) v4[q] = load(min(k0 + q * G + kg, m.K - 1));
+#pragma unroll
+    for (int q = 0; q < KQ; q++) {
+      const int32_t k = k0 + q * G + kg;
+      int32_t mn = 0x7fffffff, mx = -0x7fffffff;
+      const u32 v[4] = {v4[q].x, v4[q].y, v4[q].z, v4[q].w};
+#pragma unroll
+      for (int j = 0; j < 4; j++) {
+        if (r[j] < INF) {
+          const int32_t d = (int32_t)(v[j] - r[j]);  // both in [0, INF]: no overflow
+          mn = min(mn, d);
+          mx = max(mx, d);
+        } else {
+          bad |= v[j] < INF;
+        }
+      }
+      // over the 16 (or 32) lanes of the k
+#define DPP_STEP(c)                                                        \
+  mn = min(mn, __builtin_amdgcn_update_dpp(mn, mn, c, 0xf, 0xf, false));   \
+  mx = max(mx, __builtin_amdgcn_update_dpp(mx, mx, c, 0xf, 0xf, false));
+      DPP_STEP(0xb1) DPP_STEP(0x4e) DPP_STEP(0x141) DPP_STEP(0x140)
+#undef DPP_STEP
+      if (L == 32) {
+        mn = min(mn, __shfl_xor(mn, 16));
+        mx = max(mx, __shfl_xor(mx, 16));
+      }
+      if (l == 0 && k < m.K)
+        put(k, max(min(mn, MP_BIG - MP_SHIFT) + MP_SHIFT, -MP_BIG - 1),
+            max(min(mx, MP_BIG - MP_SHIFT) + MP_SHIFT, 0));
+    }
+  }
+  if (bad) odd = 1;
+  __syncthreads();
+  if (odd || !live)
+    for (int32_t k = threadIdx.x; k < m.K; k += 256)
+      put(k, odd ? -MP_BIG - 1 : MP_BIG, odd ? MP_BIG : 0);
+}
+
+// The bit masks of the k to keep: mask[((slot * NT + row tile) * NC + column
+// tile) * NW + k / 64].  A wave takes 64 columns (one per lane) and MP_RG row
+// tiles, whose statistics are scalar loads; B is read twice, from L2.  exec
+// counts the relaxations of the product the masks leave.
+constexpr int MP_SEG = 64;  // mask words per LDS segment (4,096 k)
+
+// OR over the wave's lanes, in every lane.
+__device__ __forceinline__ u32 wave_or(u32 v) {
+  int x = (int)v;
+  x |= __builtin_amdgcn_update_dpp(0, x, 0xb1, 0xf, 0xf, false);   // quad_perm 1 0 3 2
+  x |= __builtin_amdgcn_update_dpp(0, x, 0x4e, 0xf, 0xf, false);   // quad_perm 2 3 0 1
+  x |= __builtin_amdgcn_update_dpp(0, x, 0x141, 0xf, 0xf, false);  // row_half_mirror
+  x |= __builtin_amdgcn_update_dpp(0, x, 0x140, 0xf, 0xf, false);  // row_mirror: OR of the row
+  return (u32)(__builtin_amdgcn_readlane(x, 0) | __builtin_amdgcn_readlane(x, 16) |
+               __builtin_amdgcn_readlane(x, 32) | __builtin_amdgcn_readlane(x, 48));
+}
+template <int SIDE>
+__global__ __launch_bounds__(256) void k_mp_keep(MpArgs a) {
+  constexpr int SR = MP_SR<SIDE>, RG = MP_RG<SIDE>;
+  __shared__ u32 seg[4][RG][MP_SEG * 2];
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  const int32_t slot = blockIdx.y;
+  const MpSide m = mp_side(SIDE, a, slot);
+  const int ncg = (a.NC + 3) / 4;
+  const int32_t tj = ((int32_t)blockIdx.x % ncg) * 4 + w, t0 = ((int32_t)blockIdx.x / ncg) * RG;
+  const int32_t p = tj * MP_T;
+  if (p >= m.W || t0 * SR >= m.rows) return;  // (no barrier below: waves are on their own)
+  const u32* B = a.R + (int64_t)m.g * a.Kp * a.Vp + min(p + lane, m.W - 1);
+  const int64_t ldb = a.Vp;
+  const cptr32 st = (cptr32)(a.stats + (int64_t)slot * a.Kp * 2 * a.NT + t0);
+  const int32_t K = m.K;
+  int32_t U[RG], arg[RG];
+#pragma unroll
+  for (int r = 0; r < RG; r++) {
+    U[r] = MP_ALL;
+    arg[r] = -1;
+  }
+  u32 bmin = INF;
+  constexpr int KU = 32 / RG;  // k per step (a step past K repeats the last k)
+  for (int32_t k0 = 0; k0 < K; k0 += KU) {
+    u32 b[KU];
+#pragma unroll
+    for (int q = 0; q < KU; q++) b[q] = B[(int64_t)min(k0 + q, K - 1) * ldb];
+#pragma unroll
+    for (int q = 0; q < KU; q++) {
+      const int32_t k = min(k0 + q, K - 1);
+      const cptr32 mx = st + (int64_t)(k * 2 + 1) * a.NT;
+      bmin = min(bmin, b[q]);
+      const int32_t bu = (int32_t)min(b[q], (u32)MP_BIG);
+#pragma unroll
+      for (int r = 0; r < RG; r++) {
+        const int32_t v = mx[r] + bu;
+        arg[r] = v < U[r] ? k : arg[r];
+        U[r] = min(U[r], v);
+      }
+    }
+  }
+  // a column that no k reaches, one of the K itself or past the end keeps nothing
+  const bool off = bmin >= INF || p + lane >= m.W ||
+                   (a.cs.rank && a.cs.rank[a.cs.g0[m.g] + p + lane] >= 0);
+  int32_t nU[RG];
+#pragma unroll
+  for (int r = 0; r < RG; r++) {
+    if (U[r] >= MP_BIG) {
+      U[r] = MP_ALL;
+      arg[r] = -1;
+    }
+    if (off) {
+      U[r] = MP_NONE;
+      arg[r] = -1;
+    }
+    nU[r] = -U[r];
+  }
+  const int32_t nrt = min(RG, (m.rows - t0 * SR + SR - 1) / SR);
+  u32 kept[RG];
+#pragma unroll
+  for (int r = 0; r < RG; r++) kept[r] = 0;
+  for (int32_t s0 = 0; s0 < K; s0 += MP_SEG * 64) {
+    const int32_t s1 = min(K, s0 + MP_SEG * 64);
+    for (int32_t k0 = s0; k0 < s1; k0 += 32) {
+      // bit 31 - q of a lane's word: its column needs k0 + q (the sign of
+      // mn + b - U)
+      u32 word[RG];
+#pragma unroll
+      for (int r = 0; r < RG; r++) word[r] = 0;
+#pragma unroll 1
+      for (int q0 = 0; q0 < 32; q0 += KU) {
+        int32_t b[KU];
+#pragma unroll
+        for (int q = 0; q < KU; q++)
+          b[q] = (int32_t)min(B[(int64_t)min(k0 + q0 + q, K - 1) * ldb], (u32)MP_BIG);
+#pragma unroll
+        for (int q = 0; q < KU; q++) {
+          const cptr32 mn = st + (int64_t)min(k0 + q0 + q, K - 1) * 2 * a.NT;
+#pragma unroll
+          for (int r = 0; r < RG; r++)
+            word[r] = __builtin_amdgcn_alignbit(word[r], (u32)(mn[r] + b[q] + nU[r]), 31);
+        }
+      }
+      const u32 valid = K - k0 >= 32 ? 0xffffffffu : (1u << (K - k0)) - 1;
+#pragma unroll
+      for (int r = 0; r < RG; r++) {
+        const u32 x = __builtin_bitreverse32(wave_or(word[r])) & valid;
+        if (lane == 0) seg[w][r][(k0 - s0) >> 5] = x;
+      }
+    }
+    const int32_t nh = (s1 - s0 + 31) >> 5;  // 32-bit words
+    if ((nh & 1) && lane < RG) seg[w][lane][nh] = 0;
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int r = 0; r < RG; r++)
+      if (arg[r] >= s0 && arg[r] < s1) atomicOr(&seg[w][r][(arg[r] - s0) >> 5], 1u << (arg[r] & 31));
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int r = 0; r < RG; r++) {
+      if (r >= nrt) break;
+      u32* out = reinterpret_cast<u32*>(
+          a.mask + (((int64_t)slot * a.NT + t0 + r) * a.NC + tj) * a.NW + (s0 >> 6));
+      for (int32_t i = lane; i < nh + (nh & 1); i += 64) {
+        const u32 x = seg[w][r][i];
+        out[i] = x;
+        kept[r] += __popc(x);
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+  // relaxations: pairs of k on whole tiles
+  unsigned long long n = 0;
+#pragma unroll
+  for (int r = 0; r < RG; r++) {
+    if (r >= nrt) break;
+    u32 x = kept[r];
+    for (int o = 32; o > 0; o >>= 1) x += (u32)__shfl_xor((int)x, o);
+    const u32 tiles = (u32)(min(m.rows - (t0 + r) * SR, SR) + MP_T - 1) / MP_T;
+    n += (unsigned long long)((x + 1) & ~1u) * (MP_T * MP_T) * tiles;
+  }
+  if (lane == 0 && n) atomicAdd(a.exec + ((blockIdx.x + blockIdx.y) & 15), n);
+}
+
+// The relaxations of one LDS step, its first n k (even): MP_KC rows of A's 64
+// rows, then as many of B's 64 columns.  Lane (ly, lx) = (lane / 8, lane % 8)
+// holds rows h*32 + ly*4 + a and columns h*32 + lx*4 + a of the tile, h < 2, a < 4.
+__device__ __forceinline__ void mp_wave_step(u32 (&c)[8][8], const u32* s, int n, int ly, int lx) {
+  const u32* ap = s + ly * 4;
+  const u32* bp = s + MP_KC * MP_T + lx * 4;
+#pragma unroll 1
+  for (int k = 0; k < n; k += 2) {
+    u32 a0[8], a1[8], b0[8], b1[8];
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+      const uint4 x0 = *reinterpret_cast<const uint4*>(ap + h * 32);
+      const uint4 x1 = *reinterpret_cast<const uint4*>(ap + MP_T + h * 32);
+      const uint4 y0 = *reinterpret_cast<const uint4*>(bp + h * 32);
+      const uint4 y1 = *reinterpret_cast<const uint4*>(bp + MP_T + h * 32);
+      a0[h * 4 + 0] = x0.x; a0[h * 4 + 1] = x0.y; a0[h * 4 + 2] = x0.z; a0[h * 4 + 3] = x0.w;
+      a1[h * 4 + 0] = x1.x; a1[h * 4 + 1] = x1.y; a1[h * 4 + 2] = x1.z; a1[h * 4 + 3] = x1.w;
+      b0[h * 4 + 0] = y0.x; b0[h * 4 + 1] = y0.y; b0[h * 4 + 2] = y0.z; b0[h * 4 + 3] = y0.w;
+      b1[h * 4 + 0] = y1.x; b1[h * 4 + 1] = y1.y; b1[h * 4 + 2] = y1.z; b1[h * 4 + 3] = y1.w;
+    }
+    ap += 2 * MP_T;
+    bp += 2 * MP_T;
+#pragma unroll
+    for (int i = 0; i < 8; i++)
+#pragma unroll
+      for (int j = 0; j < 8; j++) relax2(c[i][j], a0[i], b0[j], a1[i], b1[j]);
+  }
+}
+
+// Half h of a wave's tile through LDS, so that a wave stores 64 consecutive
+// columns (BYROW: rows h*32 .., lane = column) or rows (columns h*32 ..,
+// lane = row) at a time.
+constexpr int MP_ST = 68;  // row length of the staged half: 16-byte aligned, banks spread
+template <bool BYROW>
+__device__ __forceinline__ void mp_stage(const u32 (&c)[8][8], u32* s, int h, int ly, int lx) {
+#pragma unroll
+  for (int q = 0; q < 4; q++)
+#pragma unroll
+    for (int g = 0; g < 2; g++) {
+      uint4 v;
+      if (BYROW)
+        v = h ? make_uint4(c[4 + q][g * 4], c[4 + q][g * 4 + 1], c[4 + q][g * 4 + 2], c[4 + q][g * 4 + 3])
+              : make_uint4(c[q][g * 4], c[q][g * 4 + 1], c[q][g * 4 + 2], c[q][g * 4 + 3]);
+      else
+        v = h ? make_uint4(c[g * 4][4 + q], c[g * 4 + 1][4 + q], c[g * 4 + 2][4 + q], c[g * 4 + 3][4 + q])
+              : make_uint4(c[g * 4][q], c[g * 4 + 1][q], c[g * 4 + 2][q], c[g * 4 + 3][q]);
+      const int row = (BYROW ? ly : lx) * 4 + q, col = g * 32 + (BYROW ? lx : ly) * 4;
+      *reinterpret_cast<uint4*>(s + row * MP_ST + col) = v;
+    }
+}
+
+// What a lane holds of the query layout for the store of a tile: the terms of
+// its column (byte offsets) and of the row of the same number.
+struct MpTerms {
+  u32 lo, ln, ll;  // column (block's y): rowoff, |B|, local index, times 4
+  u32 uo, un, ul;  // row (block's x): rowoff, |B|, local index
+};
+
+// Stores the staged half: staged row q (of n) is the block's row u0 + q, the
+// lane's column its column l (-1: none), so the 64 stores are consecutive inside
+// a component's run.  Query layout: element (x, y) at rowoff(x) |Y| + nb(x)
+// rowoff(y) + loc(x) nb(y) + loc(y) (bytes below 2^32): the rows of one
+// component follow each other nb(y) apart.  h: which half, row q's terms in
+// lane h*32 + q.  Mg (not null: S1 = S2): the group's closure is folded in.
+// CERT: best and worst get the largest finite value plus one and the largest.
+template <bool CERT>
+__device__ __forceinline__ void mp_store_half(const u32* s, const MpTerms& t, u32* base, int h, int32_t n,
+                                              int32_t l, u32 nY, const u32* Mg, int32_t Vp, u32& best,
+                                              u32& worst) {
+  const int lane = threadIdx.x;
+  if (l < 0) return;
+  const u32* sp = s + lane;
+  for (int q = 0; q < n;) {
+    const int r = h * 32 + q;
+    const u32 uo = (u32)__builtin_amdgcn_readlane((int)t.uo, r), un = (u32)__builtin_amdgcn_readlane((int)t.un, r),
+              ul = (u32)__builtin_amdgcn_readlane((int)t.ul, r);
+    char* row = reinterpret_cast<char*>(base) + (uint64_t)uo * nY * 4;
+    u32 off = __umul24(un, t.lo) + (__umul24(ul, t.ln) + t.ll);
+    const int e = min(n, q + (int)(un - ul));  // the component's rows end there
+#pragma unroll 4
+    for (; q < e; q++) {
+      u32 v = *sp;
+      sp += MP_ST;
+      if (Mg) v = min(v, Mg[(int64_t)q * Vp + l]);
+      *reinterpret_cast<u32*>(row + off) = v;
+      off += t.ln;
+      if (CERT) {
+        best = max(best, (v + 1) & INF);
+        worst = max(worst, v);
+      }
+    }
+  }
+}
+
+// The same into the dense matrix of level 3, from its row `out`.
+__device__ __forceinline__ void mp_store_half_dense(const u32* s, u32* out, int64_t ldo, int32_t n,
+                                                    int32_t l, const u32* Mg, int32_t Vp) {
+  const int lane = threadIdx.x;
+#pragma unroll 4
+  for (int q = 0; q < n; q++) {
+    u32 v = s[q * MP_ST + lane];
+    if (l >= 0) {
+      if (Mg) v = min(v, Mg[(int64_t)q * Vp + l]);
+      out[q * ldo + l] = v;
+    }
+  }
+}
+
+// Pair slot and tile of a workgroup.  Workgroups go round-robin to the eight
+// XCDs (an L2 each) in order of their linear id: pairs c, c + 8, ... all stay on
+// XCD c, so its L2 serves the reuse of a pair's operands.  With few pairs that
+// would leave XCDs idle at the end (level 3, 36 pairs: 3.0 against 2.1 ms), so
+// there a pair's tiles spread over all of them, rotated by the pair (the tiles
+// past a group's last vertex would otherwise all fall to the same XCDs).
+constexpr int MP_XCD_PAIRS = 128;
+__device__ __forceinline__ void mp_place(const MpArgs& a, int32_t& slot, int32_t& tile) {
+  if (a.np >= MP_XCD_PAIRS) {
+    const u32 id = blockIdx.y * gridDim.x + blockIdx.x, q = id >> 3;
+    slot = (int32_t)(q / gridDim.x * 8 + (id & 7));
+    tile = (int32_t)(q % gridDim.x);
+  } else {
+    slot = blockIdx.y;
+    tile = (int32_t)((blockIdx.x + blockIdx.y) % gridDim.x);
+  }
+}
+
+// One wave per 64 x 64 tile of a product, over the kept k.  The two 256-byte
+// operand rows of a kept k go straight to LDS, into a ring of MP_RING steps of
+// MP_KC k; waves share nothing, so no barrier holds one up.  8 x 8
+// entries per lane: 128 VGPRs, 8.5 KB of LDS, four waves per SIMD.
+//
+// SIDE 0, the first product: rows b in B2(S2), columns x of S1, stored as XT.
+// SIDE 1: rows x of S1, columns y of S2, stored as the block D(S1, S2) (D(S2,
+// S1) for a swapped pair).  CERT: with the certificate.
+template <int SIDE, bool CERT>
+__global__ __launch_bounds__(64) SPQ_MP_ATTR void k_mp_prod(MpArgs a) {
+  __shared__ __attribute__((aligned(16))) u32 s[32 * MP_ST];
+  __shared__ uint16_t kl[256 + MP_KC];
+  static_assert(MP_RING * MP_KC * 2 * MP_T <= 32 * MP_ST, "the ring fits in the staging buffer");
+  static_assert(MP_KC == 4 && MP_RING == 4, "the waits below");
+  int32_t slot, tile;
+  mp_place(a, slot, tile);
+  if (slot >= a.np) return;
+  const MpSide m = mp_side(SIDE, a, slot);
+  const int32_t ti = tile / a.NC, tj = tile % a.NC;
+  const int32_t x0 = ti * MP_T, p0 = tj * MP_T;
+  if (x0 >= m.rows || p0 >= m.W) return;
+  const CompStore& cs = a.cs;
+  const int lane = threadIdx.x, ly = lane >> 3, lx = lane & 7;
+  const int2 pr = a.plist[a.pbase + slot];
+  const bool sw = (pr.y & PAIR_SWAP) != 0;
+  const int32_t s1 = pr.x, s2 = pr.y & ~PAIR_SWAP;
+  // the block's rows (of a swapped pair the tile's columns) and columns
+  const int32_t u0 = sw ? p0 : x0, ulim = sw ? m.W : m.rows;
+  const int32_t l0 = sw ? x0 : p0, llim = sw ? m.rows : m.W;
+  const int32_t gu = SIDE ? cs.g0[sw ? s2 : s1] : 0, gl = SIDE ? cs.g0[sw ? s1 : s2] : 0;
+  u32* base = nullptr;
+  MpTerms t{};
+  u32 c[8][8];
+  fill_inf(c);
+  {
+    const u32* A = m.A + x0;
+    const u32* B = a.R + (int64_t)m.g * a.Kp * a.Vp + p0;
+    const auto mk = (const __attribute__((address_space(4))) unsigned long long*)(
+        a.mask + (((int64_t)slot * a.NT + x0 / MP_SR<SIDE>) * a.NC + tj) * a.NW);
+    const int32_t nw = (m.K + 63) >> 6;
+    // the kept k of up to four mask words, padded by repeating the last to a whole
+    // chunk (harmless in a minimum); returns their number
+    auto list_window = [&](int32_t w0) -> int32_t {
+      int32_t n = 0, last = 0;
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        const unsigned long long word = w0 + i < nw ? mk[w0 + i] : 0ull;
+        if (word >> lane & 1)
+          kl[n + __builtin_amdgcn_mbcnt_hi((u32)(word >> 32), __builtin_amdgcn_mbcnt_lo((u32)word, 0))] =
+              (uint16_t)(i * 64 + lane);
+        if (word) last = i * 64 + 63 - __builtin_clzll(word);
+        n += __popcll(word);
+      }
+      if (lane < MP_KC) kl[n + lane] = (uint16_t)last;
+      return n;
+    };
+    // sixteen lanes fetch a row of 64 words (B, and A in the second product,
+    // whose rows are 16-byte aligned; A's in the first start anywhere: one
+    // word per lane)
+    const u32 acol = min((u32)lane, (u32)(m.rows - x0 - 1)) & 63u;
+    constexpr int LOADS = SIDE ? 2 : 1 + MP_KC;  // per step
+    auto load_step = [&](int32_t kw, int32_t st) {
+      u32* d = s + (st % MP_RING) * MP_KC * 2 * MP_T;
+      const u32 k = (u32)kw + kl[st * MP_KC + (lane >> 4)];
+      const u32* bp = B + (uint64_t)k * (u32)a.Vp + (lane & 15) * 4;
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)bp,
+                                       (__attribute__((address_space(3))) void*)(d + MP_KC * MP_T), 16, 0, 0);
+      if (SIDE) {
+        const u32* ap = A + (uint64_t)k * (u32)a.Vp + (lane & 15) * 4;
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)ap,
+                                         (__attribute__((address_space(3))) void*)d, 16, 0, 0);
+      } else {
+#pragma unroll
+        for (int i = 0; i < MP_KC; i++) {
+          const int32_t ki = __builtin_amdgcn_readlane((int)k, i * 16);
+          __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(A + (int64_t)ki * m.lda + acol),
+                                           (__attribute__((address_space(3))) void*)(d + i * MP_T), 4, 0, 0);
+        }
+      }
+    };
+    int32_t n = list_window(0);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int i = 0; i < MP_RING; i++)
+      if (i * MP_KC < n) load_step(0, i);
+    if (SIDE && !cs.dense) {  // the store's terms, before they are needed
+      base = cs.H + (sw ? cs.pairbase[(int64_t)s2 * cs.ngroups + s1]
+                        : cs.pairbase[(int64_t)s1 * cs.ngroups + s2]);
+      const int32_t ug = gu + min(u0 + lane, ulim - 1), lg = gl + min(l0 + lane, llim - 1);
+      const int4 um = cs.meta[ug], lm = cs.meta[lg];
+      t.lo = (u32)lm.x * 4;
+      t.ln = (u32)lm.y * 4;
+      t.ll = (u32)lm.z * 4;
+      t.uo = (u32)um.x;
+      t.un = (u32)um.y;
+      t.ul = (u32)um.z;
+    }
+    if (cs.rank) {  // the columns that are boundary vertices themselves
+      const int32_t rk = p0 + lane < m.W ? cs.rank[cs.g0[m.g] + p0 + lane] : -1;
+      if (__ballot(rk >= 0)) {
+#pragma unroll
+        for (int j = 0; j < 8; j++) {
+          const int32_t r = __shfl(rk, (j >> 2) * 32 + lx * 4 + (j & 3));
+          if (r < 0) continue;
+#pragma unroll
+          for (int h = 0; h < 2; h++) {
+            const int32_t x = h * 32 + ly * 4, nx = m.rows - x0 - x;
+            const u32* ap = A + (int64_t)r * m.lda + x;
+            if (nx >= 4) {
+              const uint4 v = *reinterpret_cast<const uint4*>(ap);
+              c[h * 4][j] = v.x;
+              c[h * 4 + 1][j] = v.y;
+              c[h * 4 + 2][j] = v.z;
+              c[h * 4 + 3][j] = v.w;
+            } else {
+              if (nx > 0) c[h * 4][j] = ap[0];
+              if (nx > 1) c[h * 4 + 1][j] = ap[1];
+              if (nx > 2) c[h * 4 + 2][j] = ap[2];
+            }
+          }
         }
       }
     }
-  }
-  if (CERT) cert_reduce(best, wrong, cert_bad, cert_mbg);
-}
-
-// c[i][j] = min(c[i][j], M[lr[i]][lc[j]]) for the valid pairs (M: a group's
-// closure, leading dimension ld).
-__device__ __forceinline__ void tile_min_gather(u32 (&c)[8][8], const u32* __restrict__ M, int64_t ld,
-                                                const int32_t (&lr)[8], const int32_t (&lc)[8]) {
+    for (int32_t w0 = 0;;) {
+      const int32_t ns = (n + MP_KC - 1) / MP_KC;
+#pragma unroll 1
+      for (int32_t st = 0; st < ns; st++) {
+        // step st has arrived (the loads behind it may still be in flight), and
+        // every LDS read of the step before it is over
+        const int32_t behind = ns - 1 - st;
+        if (behind >= 3)
+          asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(3 * LOADS) : "memory");
+        else if (behind == 2)
+          asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * LOADS) : "memory");
+        else if (behind == 1)
+          asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LOADS) : "memory");
+        else
+          asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        mp_wave_step(c, s + (st % MP_RING) * MP_KC * 2 * MP_T, min(MP_KC, (n - st * MP_KC + 1) & ~1), ly, lx);
+        // its slot is free once its LDS reads are over (their values are used above)
+        if (st + MP_RING < ns) {
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+          load_step(w0 * 64, st + MP_RING);
+        }
+      }
+      w0 += 4;
+      if (w0 >= nw) break;
+      n = list_window(w0);
+      __builtin_amdgcn_wave_barrier();
 #pragma unroll
-  for (int i = 0; i < 8; i++) {
-    if (lr[i] < 0) continue;
-    const u32* row = M + (int64_t)lr[i] * ld;
-#pragma unroll
-    for (int j = 0; j < 8; j++)
-      if (lc[j] >= 0) c[i][j] = min(c[i][j], row[lc[j]]);
-  }
-}
-
-// The composition's optional stores (the builds'; the test hooks pass
-// none): positions, and the query layout with the certificate or (level 3)
-// the dense BG2 matrix.
-struct CompStore {
-  const int32_t* pos;        // ngroups x Vrp, NULL: identity
-  int32_t Vgp, ngroups;      // Mg and b2list leading dimension; groups
-  const int32_t *b2list, *gbg0, *bgrow, *bgnb, *bglocal, *bglabel;
-  const u32* Mg;
-  const int64_t* pairbase;
-  u32* H;
-  u32 *cert_bad, *cert_mbg;
-  // dense store (level 3): element (x, y) of the pair block (S1, S2) at
-  // dense[(dbase[S1] + x) * ldo + dbase[S2] + y]; NULL: the query layout
-  u32* dense = nullptr;
-  int64_t ldo = 0;
-  const int32_t* dbase = nullptr;
-};
-
-// Stores tile c into a dense matrix: row i of the thread is vertex lr[i]
-// (-1: none), column j vertex lc[j], of the groups whose first rows are gx
-// (the block's rows) and gy; ROWS_X: c's rows are the block's rows, else its
-// columns.
-template <bool ROWS_X>
-__device__ __forceinline__ void store_dense(const u32 (&c)[8][8], u32* out, int64_t ldo, int64_t gx,
-                                            int64_t gy, const int32_t (&lr)[8], const int32_t (&lc)[8]) {
-#pragma unroll
-  for (int i = 0; i < 8; i++) {
-    if (lr[i] < 0) continue;
-#pragma unroll
-    for (int j = 0; j < 8; j++) {
-      if (lc[j] < 0) continue;
-      const int64_t off = ROWS_X ? (gx + lr[i]) * ldo + gy + lc[j] : (gx + lc[j]) * ldo + gy + lr[i];
-      out[off] = c[i][j];
+      for (int i = 0; i < MP_RING; i++)
+        if (i * MP_KC < n) load_step(w0 * 64, i);
     }
   }
-}
-
-// The first product's entries at S1's B2 positions (positions only):
-// XT[b][a] = D2[a][b], the product's minimum taken at a itself
-// (d_S1(a, a) = 0; D2 is closed), stored as XT and into the query layout
-// (CERT: with the certificate).  One tile: B2 rows ti*128.. of S2 x
-// positions tj*128.. of S1; Ab = D2[B2(s1)][B2(s2)] as the product reads it
-// (row a, column b, leading dimension lda); sAB holds 8,192 words.
-template <bool CERT>
-__device__ __forceinline__ void xt_copy_tile(int32_t s1, int32_t s2, bool sw, int ti, int tj,
-                                             int32_t ka, int32_t mb, int32_t P1, const u32* Ab,
-                                             int64_t lda, u32* xt, int32_t Vrp,
-                                             const int32_t* __restrict__ gV, const CompStore& cs,
-                                             u32* sAB) {
-  const int tx = tid_x(), ty = tid_y();
-  u32 c[8][8];
-  // c holds rows a (positions tj*128 ..) and columns b, and is stored
-  // transposed.  The D2 rows are read whole (a wave reads 256 contiguous
-  // bytes), 64 rows at a time through LDS.
-  const int32_t bl = (int32_t)threadIdx.x & 127, b = ti * 128 + bl;
+  __builtin_amdgcn_wave_barrier();
+  if (SIDE == 0) {
+    // XT rows b: 64 consecutive x per store (those past the group are unused)
+    u32* xt = a.XT + ((int64_t)slot * a.Kp + x0) * a.Vp + p0;
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+      mp_stage<true>(c, s, h, ly, lx);
+      __builtin_amdgcn_wave_barrier();
+      const int32_t n = min(m.rows - x0 - h * 32, 32);
+#pragma unroll 4
+      for (int q = 0; q < n; q++) xt[(int64_t)(h * 32 + q) * a.Vp + lane] = s[q * MP_ST + lane];
+      __builtin_amdgcn_wave_barrier();
+    }
+    return;
+  }
+  const u32* Mg = s1 == s2 ? cs.Mg + ((int64_t)s1 * a.Vp + u0) * a.Vp : nullptr;
+  const int32_t l = l0 + lane < llim ? l0 + lane : -1;
+  u32 best = 0, worst = 0;
 #pragma unroll
   for (int h = 0; h < 2; h++) {
-    for (int q = 0; q < 32; q++) {
-      const int32_t r = 2 * q + ((int32_t)threadIdx.x >> 7), pa = tj * 128 + h * 64 + r;
-      sAB[r * 128 + bl] = (pa < ka && b < mb) ? Ab[(int64_t)pa * lda + b] : INF;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int a = 0; a < 4; a++)
-#pragma unroll
-      for (int h2 = 0; h2 < 2; h2++) {
-        const uint4 v = *reinterpret_cast<const uint4*>(sAB + (ty * 4 + a) * 128 + h2 * 64 + tx * 4);
-        c[h * 4 + a][h2 * 4] = v.x;
-        c[h * 4 + a][h2 * 4 + 1] = v.y;
-        c[h * 4 + a][h2 * 4 + 2] = v.z;
-        c[h * 4 + a][h2 * 4 + 3] = v.w;
-      }
-    __syncthreads();
+    const int32_t n = min(ulim - u0 - h * 32, 32);
+    if (n <= 0) break;
+    if (sw)
+      mp_stage<false>(c, s, h, ly, lx);
+    else
+      mp_stage<true>(c, s, h, ly, lx);
+    __builtin_amdgcn_wave_barrier();
+    const u32* Mh = Mg ? Mg + (int64_t)h * 32 * a.Vp : nullptr;
+    if (cs.dense)
+      mp_store_half_dense(s, cs.dense + (int64_t)(gu + u0 + h * 32) * cs.ldo + gl, cs.ldo, n, l, Mh, a.Vp);
+    else
+      mp_store_half<CERT>(s, t, base, h, n, l, (u32)llim, Mh, a.Vp, best, worst);
+    __builtin_amdgcn_wave_barrier();
   }
-#pragma unroll
-  for (int j = 0; j < 8; j++) {
-    u32* row = xt + (int64_t)((j >> 2) * 64 + tx * 4 + (j & 3)) * Vrp + tj * 128;
-#pragma unroll
-    for (int h = 0; h < 2; h++)
-      if (tj * 128 + h * 64 + ty * 4 < P1)  // the product's tiles own the rest
-        *reinterpret_cast<uint4*>(row + h * 64 + ty * 4) =
-            make_uint4(c[h * 4][j], c[h * 4 + 1][j], c[h * 4 + 2][j], c[h * 4 + 3][j]);
-  }
-  int32_t lr[8], lc[8];
-#pragma unroll
-  for (int i = 0; i < 8; i++) {
-    const int32_t pa = tj * 128 + (i >> 2) * 64 + ty * 4 + (i & 3);
-    lr[i] = pa < ka ? cs.pos[(int64_t)s1 * Vrp + pa] : -1;
-  }
-#pragma unroll
-  for (int j = 0; j < 8; j++) {
-    const int32_t b = ti * 128 + (j >> 2) * 64 + tx * 4 + (j & 3);
-    lc[j] = b < mb ? cs.b2list[(int64_t)s2 * cs.Vgp + b] : -1;
-  }
-  // D(s1, s2)[a][b] = D2[a][b] (no closure term: d_S1 >= D2 on B2 pairs)
-  if (cs.dense) {
-    store_dense<true>(c, cs.dense, cs.ldo, cs.dbase[s1], cs.dbase[s2], lr, lc);
-    return;
-  }
-  u32* base = cs.H + (sw ? cs.pairbase[(int64_t)s2 * cs.ngroups + s1]
-                         : cs.pairbase[(int64_t)s1 * cs.ngroups + s2]);
-  const int32_t gr = cs.gbg0[s1], gc = cs.gbg0[s2];
-  if (sw)  // the stored block is (s2, s1): rows (group s1) are its columns
-    store_block<CERT, false>(c, base, gr, gc, lr, lc, (u32)gV[s1], cs.bgrow, cs.bgnb, cs.bglocal,
-                             cs.bglabel, cs.cert_bad, cs.cert_mbg);
-  else
-    store_block<CERT, true>(c, base, gr, gc, lr, lc, (u32)gV[s2], cs.bgrow, cs.bgnb, cs.bglocal,
-                            cs.bglabel, cs.cert_bad, cs.cert_mbg);
-}
-
-// XT (m2pmax x Vrp, rows b in B2(S2), columns: positions of S1) =
-//   min over a in B2(S1) of D2[a][b] + R_S1[a][x].
-// D2 rows are level-2 ids of the sources (all of BG2, or the share's rows),
-// leading dimension ldd.  pstride = 0: D2 is dense (column = level-2 id);
-// pstride > 0: D2 is cut into one column panel per group S2, pstride
-// elements apart, whose column j is B2(S2)'s j-th vertex: the (S1, S2) block
-// a product reads is then one contiguous run instead of rows ldd apart.
-// Rows b in [m2[S2], round16(m2[S2])) are stored as INF.  The composition
-// reads rows below round16(m2[S2]) and column tiles below S1's width only,
-// so tiles past those are neither computed nor written.
-//
-// A pair flagged PAIR_SWAP reads D2[B2(s1)][B2(s2)] from the transposed
-// table D2t (rows: level-2 ids, leading dimension ldt; with a column mask,
-// as D2t's columns past B2(s2) belong to other groups).  MODE 1 (2: with the
-// certificate) also stores the tile's entries into the query layout, as
-// D(s1, s2)[x][y] for y in B2(s2) (D(s2, s1)[y][x] for a swapped pair).
-template <int MODE>
-__global__ __launch_bounds__(256) SPQ_MP_ATTR void k_mp_xt(const int2* __restrict__ plist, int32_t pbase,
-                                               int32_t Vrp, int32_t m2pmax,
-                                               const int32_t* __restrict__ m2,
-                                               const int32_t* __restrict__ gV,
-                                               const int32_t* __restrict__ b2off,
-                                               const u32* __restrict__ BG2, int64_t ldd,
-                                               int64_t pstride, const u32* __restrict__ D2t,
-                                               int64_t ldt,
-                                               const u32* __restrict__ R, u32* __restrict__ XT,
-                                               CompStore cs) {
-  __shared__ __attribute__((aligned(16))) u32 sAB[4 * 16 * 128];
-  u32* sA = sAB;
-  u32* sB = sAB + 2 * 16 * 128;
-  const int2 pr = plist[pbase + (int32_t)blockIdx.y];
-  const bool sw = (pr.y & PAIR_SWAP) != 0;
-  const int32_t s1 = pr.x, s2 = pr.y & ~PAIR_SWAP;
-  const int64_t slot = blockIdx.y;
-  const bool skip = cs.pos != nullptr;
-  const int ntx = Vrp / 128, ntm = m2pmax / 128;
-  // with positions the grid holds twice ntm x ntx tiles: the product's,
-  // then as many for S1's B2 positions (copied, see xt_copy_tile), numbered
-  // alike, which keeps the product's tile order (the copies as extra
-  // columns of each row measured much slower)
-  int tile = comp_tile();
-  const bool copy = tile >= ntm * ntx;
-  if (copy) tile -= ntm * ntx;
-  const int ti = tile / ntx, tj = tile % ntx;
-  const int32_t ka = m2[s1], mb = m2[s2];
-  if (ti * 128 >= mb) return;
-  // with positions the product's tiles start past S1's B2 positions
-  const int32_t P1 = pos_first(ka, skip), W1 = pos_width(gV[s1], ka, skip);
-  // D2[B2(s1)][B2(s2)] as the product reads it (row a, column b)
-  const u32* Ab = sw ? D2t + (int64_t)b2off[s1] * ldt + b2off[s2]
-                     : BG2 + (int64_t)s2 * pstride + (int64_t)b2off[s1] * ldd + (pstride ? 0 : b2off[s2]);
-  const int64_t lda = sw ? ldt : ldd;
-  u32* xt = XT + (slot * m2pmax + ti * 128) * Vrp;
-  if (MODE > 0 && copy) {
-    if (tj * 128 < P1)
-      xt_copy_tile<MODE == 2>(s1, s2, sw, ti, tj, ka, mb, P1, Ab, lda, xt, Vrp, gV, cs, sAB);
-    return;
-  }
-  const int tx = tid_x(), ty = tid_y();
-  u32 c[8][8];
-  const int32_t p0 = P1 + tj * 128;  // first position of the tile
-  if (p0 >= W1) return;
-  fill_inf(c);
-  {
-    const u32* B = R + (int64_t)s1 * m2pmax * Vrp + p0;
-    // a panel holds INF past its group's B2 vertices: no column mask there
-    mp_stream128<true>(c, Ab + ti * 128, lda, B, Vrp, (ka + 15) / 16 * 16, ka,
-                       (pstride && !sw) ? 128 : mb - ti * 128, sA, sB, mb - ti * 128, W1 - p0);
-  }
-#pragma unroll
-  for (int h = 0; h < 2; h++)
-#pragma unroll
-    for (int a = 0; a < 4; a++) {
-      const int row = h * 64 + ty * 4 + a;
-      const bool live = ti * 128 + row < mb;
-#pragma unroll
-      for (int h2 = 0; h2 < 2; h2++) {
-        const int i = h * 4 + a, j = h2 * 4;
-        const int32_t p = p0 + h2 * 64 + tx * 4;  // a multiple of 4: the 4 lie in one row
-        if (p >= Vrp) continue;
-        uint4 v = live ? make_uint4(c[i][j], c[i][j + 1], c[i][j + 2], c[i][j + 3])
-                       : make_uint4(INF, INF, INF, INF);
-        *reinterpret_cast<uint4*>(xt + (int64_t)row * Vrp + p) = v;
+  if (CERT) {
+    // an INF somewhere: does it join vertices connected in G?  The stored
+    // entries again (this lane wrote them)
+    u32 wrong = 0;
+    if (worst >= INF) {
+      const int32_t lab = cs.bglabel[gl + l];
+      for (int32_t x = u0; x < min(ulim, u0 + MP_T); x++) {
+        const int4 um = cs.meta[gu + x];
+        const u32 off = __umul24((u32)um.y, t.lo) + (__umul24((u32)um.z, t.ln) + t.ll);
+        const u32 v = *reinterpret_cast<const u32*>(reinterpret_cast<const char*>(base) +
+                                                    (uint64_t)(u32)um.x * (u32)llim * 4 + off);
+        wrong |= (u32)(v >= INF && cs.bglabel[gu + x] == lab);
       }
     }
-  if (MODE == 0) return;
-  // rows: B2 vertices of s2; columns: positions of s1
-  int32_t lr[8], lc[8];
-#pragma unroll
-  for (int i = 0; i < 8; i++) {
-    const int32_t b = ti * 128 + (i >> 2) * 64 + ty * 4 + (i & 3);
-    lr[i] = b < mb ? cs.b2list[(int64_t)s2 * cs.Vgp + b] : -1;
+    cert_reduce(best ? best - 1 : 0, wrong, cs.cert_bad, cs.cert_mbg);
   }
-#pragma unroll
-  for (int j = 0; j < 8; j++)
-    lc[j] = pos_local(cs.pos, (int64_t)s1 * Vrp, p0 + (j >> 2) * 64 + tx * 4 + (j & 3), W1, gV[s1]);
-  // d_S1 between the two when S1 = S2: d_S1(b, x), the closure being symmetric
-  if (s1 == s2) tile_min_gather(c, cs.Mg + (int64_t)s1 * cs.Vgp * cs.Vgp, cs.Vgp, lr, lc);
-  if (cs.dense) {  // rows: the block's columns y
-    store_dense<false>(c, cs.dense, cs.ldo, cs.dbase[s1], cs.dbase[s2], lr, lc);
-    return;
-  }
-  u32* base = cs.H + (sw ? cs.pairbase[(int64_t)s2 * cs.ngroups + s1]
-                         : cs.pairbase[(int64_t)s1 * cs.ngroups + s2]);
-  const int32_t gr = cs.gbg0[s2], gc = cs.gbg0[s1];
-  if (sw)  // rows (group s2) are the block's rows
-    store_block<MODE == 2, true>(c, base, gr, gc, lr, lc, (u32)gV[s1], cs.bgrow, cs.bgnb, cs.bglocal,
-                                 cs.bglabel, cs.cert_bad, cs.cert_mbg);
-  else
-    store_block<MODE == 2, false>(c, base, gr, gc, lr, lc, (u32)gV[s2], cs.bgrow, cs.bgnb, cs.bglocal,
-                                  cs.bglabel, cs.cert_bad, cs.cert_mbg);
 }
 
-// D(S1,S2) tile for the pair of blockIdx.y, rows at positions of S1, columns
-// at positions of S2 past its B2 vertices (all of S2 without positions):
-//   min over b in B2(S2) of XT[b][x] + R_S2[b][y], and d_S1 when S1 = S2;
-// stored in the component-pair layout described at the top of the file.
-// CERT: the exactness certificate is fused into the store.
-template <bool CERT>
-__global__ __launch_bounds__(256) SPQ_MP_ATTR void k_mp_y(const int2* __restrict__ plist, int32_t pbase,
-                                              int32_t Vrp, int32_t m2pmax,
-                                              const int32_t* __restrict__ m2,
-                                              const int32_t* __restrict__ gV,
-                                              const u32* __restrict__ XT, const u32* __restrict__ R,
-                                              CompStore cs) {
-  __shared__ __attribute__((aligned(16))) u32 sA[2 * 16 * 128];
-  __shared__ __attribute__((aligned(16))) u32 sB[2 * 16 * 128];
-  const int2 pr = plist[pbase + (int32_t)blockIdx.y];
-  const bool sw = (pr.y & PAIR_SWAP) != 0;
-  const int32_t s1 = pr.x, s2 = pr.y & ~PAIR_SWAP;
-  const int64_t slot = blockIdx.y;
-  const int ntx = Vrp / 128;
-  const int tile = comp_tile();
-  const int ti = tile / ntx, tj = tile % ntx;
-  const bool skip = cs.pos != nullptr;
-  const int32_t V1 = gV[s1], V2 = gV[s2], kb = m2[s2];
-  const int32_t W1 = pos_width(V1, m2[s1], skip), W2 = pos_width(V2, kb, skip);
-  const int32_t c0 = pos_first(kb, skip) + tj * 128;  // first column position of the tile
-  if (ti * 128 >= W1 || c0 >= W2) return;
-  u32 c[8][8];
-  fill_inf(c);
-  const u32* At = XT + slot * m2pmax * Vrp + ti * 128;
-  const u32* B = R + (int64_t)s2 * m2pmax * Vrp + c0;
-  mp_stream128<false>(c, At, Vrp, B, Vrp, (kb + 15) / 16 * 16, kb, 0, sA, sB, W1 - ti * 128,
-                      W2 - c0);
-  const int tx = tid_x(), ty = tid_y();
-  int32_t lr[8], lc[8];
-#pragma unroll
-  for (int i = 0; i < 8; i++)
-    lr[i] = pos_local(cs.pos, (int64_t)s1 * Vrp, ti * 128 + (i >> 2) * 64 + ty * 4 + (i & 3), W1, V1);
-#pragma unroll
-  for (int j = 0; j < 8; j++)
-    lc[j] = pos_local(cs.pos, (int64_t)s2 * Vrp, c0 + (j >> 2) * 64 + tx * 4 + (j & 3), W2, V2);
-  // the group's own closure when S1 = S2, folded in after the product:
-  // taken in first, it kept a second copy of the tile live through the K loop
-  if (s1 == s2) tile_min_gather(c, cs.Mg + (int64_t)s1 * cs.Vgp * cs.Vgp, cs.Vgp, lr, lc);
-  u32* base = cs.H + (sw ? cs.pairbase[(int64_t)s2 * cs.ngroups + s1]
-                         : cs.pairbase[(int64_t)s1 * cs.ngroups + s2]);
-  const int32_t gr = cs.gbg0[s1], gc = cs.gbg0[s2];
-  if (sw)  // the stored block is (s2, s1): rows of s1 are its columns
-    store_block<CERT, false>(c, base, gr, gc, lr, lc, (u32)V1, cs.bgrow, cs.bgnb, cs.bglocal,
-                             cs.bglabel, cs.cert_bad, cs.cert_mbg);
-  else
-    store_block<CERT, true>(c, base, gr, gc, lr, lc, (u32)V2, cs.bgrow, cs.bgnb, cs.bglocal,
-                            cs.bglabel, cs.cert_bad, cs.cert_mbg);
+__global__ void k_zero_u64(int n, unsigned long long* p) {
+  if ((int)threadIdx.x < n) p[threadIdx.x] = 0ull;
 }
 
 // ------------------------------------------------------------- level 3
@@ -922,53 +1054,6 @@ __global__ void k_l3_edges(int64_t m, const int32_t* __restrict__ eu, const int3
     atomicMin(BG3 + a * V3p + b, (u32)w[e]);
     atomicMin(BG3 + b * V3p + a, (u32)w[e]);
   }
-}
-
-// D_BG2 tile for the super-group pair of blockIdx.y (T1 <= T2), rows at
-// positions of T1, columns at positions of T2 past its B3 vertices (all of
-// T2 without positions, pos NULL), into the dense matrix out (leading
-// dimension ldo, rows and columns from the super-groups' first BG2 ids
-// gbase).  XT and R have rows Vrp words long; Mg (the closures, leading
-// dimension Vgp) is folded in when T1 = T2.
-__global__ __launch_bounds__(256) SPQ_MP_ATTR void k_mp_y_dense(const int2* __restrict__ plist, int32_t pbase,
-                                                    int32_t Vgp, int32_t Vrp,
-                                                    int32_t m2pmax, const int32_t* __restrict__ m2,
-                                                    const int32_t* __restrict__ gV,
-                                                    const int32_t* __restrict__ gbase,
-                                                    const int32_t* __restrict__ pos,
-                                                    const u32* __restrict__ XT, const u32* __restrict__ R,
-                                                    const u32* __restrict__ Mg, u32* __restrict__ out,
-                                                    int64_t ldo) {
-  __shared__ __attribute__((aligned(16))) u32 sA[2 * 16 * 128];
-  __shared__ __attribute__((aligned(16))) u32 sB[2 * 16 * 128];
-  const int2 pr = plist[pbase + (int32_t)blockIdx.y];
-  const int32_t s1 = pr.x, s2 = pr.y;
-  const int64_t slot = blockIdx.y;
-  const int ntx = Vrp / 128;
-  const int tile = comp_tile();
-  const int ti = tile / ntx, tj = tile % ntx;
-  const bool skip = pos != nullptr;
-  const int32_t V1 = gV[s1], V2 = gV[s2], kb = m2[s2];
-  const int32_t W1 = pos_width(V1, m2[s1], skip), W2 = pos_width(V2, kb, skip);
-  const int32_t c0 = pos_first(kb, skip) + tj * 128;  // first column position of the tile
-  if (ti * 128 >= W1 || c0 >= W2) return;
-  u32 c[8][8];
-  fill_inf(c);
-  const u32* At = XT + slot * m2pmax * Vrp + ti * 128;
-  const u32* B = R + (int64_t)s2 * m2pmax * Vrp + c0;
-  mp_stream128<false>(c, At, Vrp, B, Vrp, (kb + 15) / 16 * 16, kb, 0, sA, sB, W1 - ti * 128,
-                      W2 - c0);
-  const int tx = tid_x(), ty = tid_y();
-  int32_t lr[8], lc[8];
-#pragma unroll
-  for (int i = 0; i < 8; i++)
-    lr[i] = pos_local(pos, (int64_t)s1 * Vrp, ti * 128 + (i >> 2) * 64 + ty * 4 + (i & 3), W1, V1);
-#pragma unroll
-  for (int j = 0; j < 8; j++)
-    lc[j] = pos_local(pos, (int64_t)s2 * Vrp, c0 + (j >> 2) * 64 + tx * 4 + (j & 3), W2, V2);
-  // the super-group's own closure when T1 = T2, folded in after the product
-  if (s1 == s2) tile_min_gather(c, Mg + (int64_t)s1 * Vgp * Vgp, Vgp, lr, lc);
-  store_dense<true>(c, out, ldo, gbase[s1], gbase[s2], lr, lc);
 }
 
 // One BG row (BG id x) gathered from the two-level store, for inspection.
@@ -1376,7 +1461,7 @@ static inline unsigned hblocks(int64_t items) {
 
 hipError_t launch_hier_level1(const HierArgs& a, hipStream_t s) {
   k_hier_vmeta<<<hblocks(a.V), 256, 0, s>>>(a.V, a.bgcomp, a.bgoff, a.nb, a.grp, a.gbg0,
-                                                              a.bgrow, a.bgnb, a.bggrp);
+                                                              a.bglocal, a.bgrow, a.bgnb, a.bggrp, a.meta);
   k_grp_init<<<dim3((unsigned)a.Vgp, (unsigned)a.ngroups), 256, 0, s>>>(
       a.Vgp, a.gbg0, a.gV, a.bgcomp, a.bglocal, a.bgoff, a.nb, a.P, a.moff, a.M, a.Mg);
   if (a.m > 0)
@@ -1394,16 +1479,14 @@ hipError_t launch_hier_level1(const HierArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// The groups' positions and R_S by position.
-static void launch_rpos(const HierArgs& a, hipStream_t s) {
-  k_pos_build<<<(unsigned)a.ngroups, 256, 0, s>>>(a.gbg0, a.gV, a.b2rank, a.b2list, a.m2, a.Vgp, a.Vrp,
-                                                  a.pos);
-  k_rpos_gather<<<dim3((unsigned)a.m2pmax, (unsigned)a.ngroups), 256, 0, s>>>(
-      a.Vgp, a.Vrp, a.m2pmax, a.m2, a.b2list, a.pos, a.Mg, a.R);
+// R_S of every group.
+static void launch_r(const HierArgs& a, hipStream_t s) {
+  k_r_gather<<<dim3((unsigned)a.m2pmax, (unsigned)a.ngroups), 256, 0, s>>>(a.Vgp, a.m2pmax, a.m2, a.b2list,
+                                                                            a.Mg, a.R);
 }
 
 hipError_t launch_hier_level2_prep(const HierArgs& a, hipStream_t s) {
-  launch_rpos(a, s);
+  launch_r(a, s);
   if (a.V2p > 0) {
     k_bg2_init<<<(unsigned)a.V2p, 256, 0, s>>>(a.V2, a.V2p, a.ngroups, a.b2off, a.b2list, a.Vgp, a.Mg,
                                                a.BG2);
@@ -1422,44 +1505,71 @@ hipError_t launch_hier_level2_close(const HierArgs& a, hipStream_t s) {
   return launch_dense_fw(a.BG2, a.V2p, 128, nt, s, nullptr, a.kc, a.pivot);
 }
 
+// Buffers and launch shapes of the composition's kernels (Kp: rows per slot,
+// Vp: row length; side 0 the first product's row tiles, 1 the second's).
+template <int SIDE>
+static int mp_row_tiles(int32_t rows) {
+  constexpr int step = MP_SR<SIDE> * MP_RG<SIDE>;
+  return (rows + step - 1) / step * MP_RG<SIDE>;
+}
+static int64_t mp_max_tiles(int32_t Kp, int32_t Vp) { return max(mp_row_tiles<0>(Kp), mp_row_tiles<1>(Vp)); }
+
+int64_t mp_stats_words(int32_t Kp, int32_t Vp) { return Kp * mp_max_tiles(Kp, Vp) * 2; }
+int64_t mp_mask_words(int32_t Kp, int32_t Vp) {
+  return mp_max_tiles(Kp, Vp) * (Vp / MP_T) * (Kp / 64);
+}
+
+template <int SIDE>
+static void mp_product(MpArgs a, bool cert, const MpWork& w, hipEvent_t* evt, hipStream_t s) {
+  const int32_t rows = SIDE ? a.Vp : a.Kp;
+  a.NT = mp_row_tiles<SIDE>(rows);
+  a.exec = w.exec + (SIDE && !a.cs.dense ? 16 : 0);
+  const unsigned np = (unsigned)a.np;
+  k_mp_stats<SIDE><<<dim3((unsigned)a.NT, np), 256, 0, s>>>(a);
+  k_mp_keep<SIDE><<<dim3((unsigned)((a.NC + 3) / 4 * (a.NT / MP_RG<SIDE>)), np), 256, 0, s>>>(a);
+  if (evt) (void)hipEventRecord(evt[0], s);
+  const dim3 g((unsigned)(rows / MP_T * a.NC), (np + 7) / 8 * 8);
+  if (SIDE && cert)
+    k_mp_prod<SIDE, SIDE == 1><<<g, 64, 0, s>>>(a);
+  else
+    k_mp_prod<SIDE, false><<<g, 64, 0, s>>>(a);
+  if (evt) (void)hipEventRecord(evt[1], s);
+}
+
+// The two products of one chunk; evt (optional): two events around the second.
+static void mp_chunk_products(const MpArgs& a, bool first, bool cert, const MpWork& w, hipEvent_t* evt,
+                              hipStream_t s) {
+  if (first) mp_product<0>(a, cert, w, nullptr, s);
+  mp_product<1>(a, cert, w, evt, s);
+}
+
 // Composition over the pair list a.plist (a.npairs pairs), a.chunk pairs per
 // launch of each product.  evt (optional) gets a pair of events around every
-// k_mp_y launch.  The share's BG2 rows come from its Bellman-Ford (DT^T).
+// second product.  The share's BG2 rows come from its Bellman-Ford (DT^T).
 static hipError_t compose_level2(const HierArgs& a, const int32_t* bglabel, u32* cert_bad,
                                  u32* cert_mbg, hipStream_t s) {
-  const int32_t Vrp = a.pos ? a.Vrp : a.Vgp;
-  const int ntx = Vrp / 128, ntm = a.m2pmax / 128;
-  const CompStore cs{a.pos,     a.Vgp,    a.ngroups, a.b2list, a.gbg0,   a.bgrow,  a.bgnb,
-                     a.bglocal, bglabel,  a.Mg,      a.pairbase, a.H,    cert_bad, cert_mbg};
-  const int64_t ldd = a.d2pstride ? a.d2ld : a.V2p;
+  MpArgs m{};
+  m.plist = a.plist;
+  m.Vp = a.Vgp;
+  m.Kp = a.m2pmax;
+  m.NC = m.Vp / MP_T;
+  m.NW = m.Kp / 64;
+  m.m2 = a.m2; m.gV = a.gV; m.b2off = a.b2off;
+  m.D2 = a.BG2; m.ldd = a.d2pstride ? a.d2ld : a.V2p; m.pstride = a.d2pstride;
+  m.D2t = a.D2t; m.ldt = a.d2tld;
+  m.R = a.R; m.XT = a.XT; m.stats = a.work.stats; m.mask = a.work.mask;
+  m.cs = CompStore{a.gbg0, a.b2rank, a.meta, a.Mg, a.ngroups, a.pairbase, a.H, bglabel,
+                   cert_bad, cert_mbg, nullptr, 0};
   for (int32_t p0 = 0, c = 0; p0 < a.npairs; p0 += a.chunk, c++) {
-    const unsigned np = (unsigned)min(a.chunk, a.npairs - p0);
-    // with positions the first product's grid holds the copied tiles too
-    const dim3 gx((unsigned)(ntm * ntx * (a.pos ? 2 : 1)), np), gy((unsigned)(ntx * ntx), np);
-    if (a.V2p > 0) {
-      if (!a.pos)
-        k_mp_xt<0><<<gx, 256, 0, s>>>(a.plist, p0, Vrp, a.m2pmax, a.m2, a.gV, a.b2off, a.BG2, ldd,
-                                      a.d2pstride, a.D2t, a.d2tld, a.R, a.XT, cs);
-      else if (bglabel)
-        k_mp_xt<2><<<gx, 256, 0, s>>>(a.plist, p0, Vrp, a.m2pmax, a.m2, a.gV, a.b2off, a.BG2, ldd,
-                                      a.d2pstride, a.D2t, a.d2tld, a.R, a.XT, cs);
-      else
-        k_mp_xt<1><<<gx, 256, 0, s>>>(a.plist, p0, Vrp, a.m2pmax, a.m2, a.gV, a.b2off, a.BG2, ldd,
-                                      a.d2pstride, a.D2t, a.d2tld, a.R, a.XT, cs);
-    }
-    if (a.evt) {
-      hipError_t e = hipEventRecord(a.evt[2 * c], s);
-      if (e != hipSuccess) return e;
-    }
-    if (bglabel)
-      k_mp_y<true><<<gy, 256, 0, s>>>(a.plist, p0, Vrp, a.m2pmax, a.m2, a.gV, a.XT, a.R, cs);
-    else
-      k_mp_y<false><<<gy, 256, 0, s>>>(a.plist, p0, Vrp, a.m2pmax, a.m2, a.gV, a.XT, a.R, cs);
-    if (a.evt) {
-      hipError_t e = hipEventRecord(a.evt[2 * c + 1], s);
-      if (e != hipSuccess) return e;
-    }
+    m.pbase = p0;
+    m.np = min(a.chunk, a.npairs - p0);
+    mp_chunk_products(m, a.V2p > 0, bglabel != nullptr, a.work, a.evt ? a.evt + 2 * c : nullptr, s);
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_mp_zero(const MpWork& w, hipStream_t s) {
+  k_zero_u64<<<1, 64, 0, s>>>(MP_EXEC, w.exec);
   return hipGetLastError();
 }
 
@@ -1472,7 +1582,8 @@ hipError_t launch_flat_store(int32_t V, int64_t Vp, const u32* BG, const int32_t
                              const int32_t* gbg0, int32_t* bgrow, int32_t* bgnb, int32_t* bggrp,
                              const int32_t* bglocal, u32* H, hipStream_t s) {
   if (V <= 0) return hipSuccess;
-  k_hier_vmeta<<<hblocks(V), 256, 0, s>>>(V, bgcomp, bgoff, nb, grp, gbg0, bgrow, bgnb, bggrp);
+  k_hier_vmeta<<<hblocks(V), 256, 0, s>>>(V, bgcomp, bgoff, nb, grp, gbg0, bglocal, bgrow, bgnb, bggrp,
+                                          nullptr);
   k_flat_store<<<(unsigned)V, 256, 0, s>>>(V, Vp, BG, bgrow, bgnb, bglocal, H);
   return hipGetLastError();
 }
@@ -1497,15 +1608,8 @@ hipError_t launch_level3_a(const L3Args& a, hipStream_t s) {
 }
 
 hipError_t launch_level3_b(const L3Args& a, hipStream_t s) {
-  if (a.pos3) {  // the super-groups' positions and R_T by position
-    k_pos_build<<<(unsigned)a.nT, 256, 0, s>>>(a.tbase, a.tsize, a.b3rank, a.b3list, a.m3, a.V3gp,
-                                               a.V3rp, a.pos3);
-    k_rpos_gather<<<dim3((unsigned)a.m3pmax, (unsigned)a.nT), 256, 0, s>>>(
-        a.V3gp, a.V3rp, a.m3pmax, a.m3, a.b3list, a.pos3, a.M3, a.R3);
-  } else {
-    k_r_gather<<<dim3((unsigned)a.m3pmax, (unsigned)a.nT), 256, 0, s>>>(a.V3gp, a.m3pmax, a.m3,
+  k_r_gather<<<dim3((unsigned)a.m3pmax, (unsigned)a.nT), 256, 0, s>>>(a.V3gp, a.m3pmax, a.m3,
                                                                          a.b3list, a.M3, a.R3);
-  }
   if (a.V3p > 0) {
     k_bg2_init<<<(unsigned)a.V3p, 256, 0, s>>>(a.V3, a.V3p, a.nT, a.b3off, a.b3list, a.V3gp, a.M3,
                                                a.BG3);
@@ -1524,30 +1628,21 @@ hipError_t launch_level3_b(const L3Args& a, hipStream_t s) {
 }
 
 hipError_t launch_level3_compose(const L3Args& a, hipStream_t s) {
-  // with positions (the build): the first product copies T1's B3 positions
-  // (the grid's second half) and stores the B3 columns of T2 into BG2, the
-  // second runs over T2's other vertices; without (the test hook): plain
-  const int32_t Vrp = a.pos3 ? a.V3rp : a.V3gp;
-  const int ntx = Vrp / 128, ntm = a.m3pmax / 128;
-  CompStore cs{};
-  if (a.pos3) {
-    cs.pos = a.pos3; cs.Vgp = a.V3gp; cs.ngroups = a.nT; cs.b2list = a.b3list; cs.Mg = a.M3;
-    cs.dense = a.BG2; cs.ldo = a.V2p; cs.dbase = a.tbase;
-  }
+  MpArgs m{};
+  m.plist = a.plist;
+  m.Vp = a.V3gp;
+  m.Kp = a.m3pmax;
+  m.NC = m.Vp / MP_T;
+  m.NW = m.Kp / 64;
+  m.m2 = a.m3; m.gV = a.tsize; m.b2off = a.b3off;
+  m.D2 = a.BG3; m.ldd = a.V3p;
+  m.R = a.R3; m.XT = a.XT3; m.stats = a.work.stats; m.mask = a.work.mask;
+  m.cs.g0 = a.tbase; m.cs.rank = a.b3rank; m.cs.Mg = a.M3; m.cs.ngroups = a.nT;
+  m.cs.dense = a.BG2; m.cs.ldo = a.V2p;
   for (int32_t p0 = 0; p0 < a.npairs; p0 += a.chunk) {
-    const unsigned np = (unsigned)min(a.chunk, a.npairs - p0);
-    if (a.V3p > 0) {
-      const dim3 gx((unsigned)(ntm * ntx * (a.pos3 ? 2 : 1)), np);
-      if (a.pos3)
-        k_mp_xt<1><<<gx, 256, 0, s>>>(a.plist, p0, Vrp, a.m3pmax, a.m3, a.tsize, a.b3off, a.BG3, a.V3p, 0,
-                                      nullptr, 0, a.R3, a.XT3, cs);
-      else
-        k_mp_xt<0><<<gx, 256, 0, s>>>(a.plist, p0, Vrp, a.m3pmax, a.m3, a.tsize, a.b3off, a.BG3, a.V3p, 0,
-                                      nullptr, 0, a.R3, a.XT3, cs);
-    }
-    k_mp_y_dense<<<dim3((unsigned)(ntx * ntx), np), 256, 0, s>>>(
-        a.plist, p0, a.V3gp, Vrp, a.m3pmax, a.m3, a.tsize, a.tbase, a.pos3, a.XT3, a.R3, a.M3, a.BG2,
-        a.V2p);
+    m.pbase = p0;
+    m.np = min(a.chunk, a.npairs - p0);
+    mp_chunk_products(m, a.V3p > 0, false, a.work, nullptr, s);
   }
   return hipGetLastError();
 }
@@ -1564,7 +1659,7 @@ hipError_t launch_hier_row(const HierArgs& a, int32_t x, u32* out, hipStream_t s
 namespace spq {
 
 hipError_t launch_share_prepare(const HierArgs& a, const ShareBlocks& b, hipStream_t s) {
-  launch_rpos(a, s);
+  launch_r(a, s);
   k_blk_init<<<dim3((unsigned)b.bpmax, (unsigned)b.nblk), 256, 0, s>>>(a.Vgp, b.bpmax, b.bfirst,
                                                                        a.b2off, a.b2list, a.Mg,
                                                                        b.A);

@@ -75,6 +75,21 @@ struct QueryArgs {
   int32_t share_comps;  // > 0: only sources v1 in components [0, share_comps)
 };
 
+// Scratch of the composition's pruning (hier.hip): per pair of a launch
+// mp_stats_words int32 and mp_mask_words 64-bit words; MP_EXEC counters of
+// executed relaxations (16 of every other product, then 16 of the level-2
+// second product).
+struct MpWork {
+  int32_t* stats = nullptr;
+  unsigned long long* mask = nullptr;
+  unsigned long long* exec = nullptr;
+};
+constexpr int MP_EXEC = 32;
+// Kp: rows per XT slot (a multiple of 128), Vp: their length (likewise)
+int64_t mp_stats_words(int32_t Kp, int32_t Vp);
+int64_t mp_mask_words(int32_t Kp, int32_t Vp);
+hipError_t launch_mp_zero(const MpWork& w, hipStream_t s);  // clears the counters
+
 // Two-level BG (hier.hip).
 struct HierArgs {
   int32_t V, ngroups, Vgp, m2pmax, V2, kc;
@@ -92,11 +107,7 @@ struct HierArgs {
   int32_t *b2list, *b2rank, *m2;   // ngroups x Vgp, [V], [ngroups]
   const int32_t* b2off;            // [ngroups+1]
   u32 *R, *XT, *BG2, *H;
-  // the composition's positions (ngroups x Vrp, see hier.hip; NULL: local
-  // indices, R and XT of leading dimension Vgp, every column in the second
-  // product)
-  int32_t* pos = nullptr;
-  int32_t Vrp = 0;
+  int4* meta = nullptr;            // [V] row offset, |B|, local index of every BG vertex
   // BG2 as the first product reads it: dense (d2pstride = 0, leading
   // dimension V2p), or one column panel per group (share: S2p x m2pmax,
   // leading dimension d2ld = m2pmax, panels d2pstride apart)
@@ -112,7 +123,8 @@ struct HierArgs {
   const u32* D2t = nullptr;        // D2 transposed (rows: level-2 ids; the share's DT)
   int64_t d2tld = 0;               //   its leading dimension
   int32_t npairs, chunk;           //   their count, pairs per launch (XT slots)
-  hipEvent_t* evt;                 // NULL, or 2 per composition launch (k_mp_y)
+  MpWork work;
+  hipEvent_t* evt;                 // NULL, or 2 per composition launch (second product)
   // exactness certificate fused into the composition (NULL: off)
   const int32_t* bglabel;
   u32 *cert_bad, *cert_mbg;
@@ -205,12 +217,9 @@ struct L3Args {
   uint8_t* flag3;                      // [V2]
   int32_t *b3list, *b3rank, *m3;       // nT x V3gp, [V2], [nT]
   const int32_t* b3off;                // [nT+1]
-  u32 *R3, *BG3;                       // nT x m3pmax x V3rp, V3p x V3p
-  u32* XT3;                            // chunk x m3pmax x V3rp
-  // the super-groups' positions (nT x V3rp, as the groups' at level 2;
-  // NULL: local indices, V3rp = V3gp)
-  int32_t* pos3 = nullptr;
-  int32_t V3rp = 0;
+  u32 *R3, *BG3;                       // nT x m3pmax x V3gp, V3p x V3p
+  u32* XT3;                            // chunk x m3pmax x V3gp
+  MpWork work;
   const int2* plist;                   // super-group pairs T1 <= T2
   int32_t npairs, chunk;               //   their count, pairs per launch
 };
