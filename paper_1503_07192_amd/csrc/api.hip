@@ -454,7 +454,7 @@ static spq_status build_share(spq_index* X, spq::HierArgs& ha, int64_t m, bool p
   X->h_boff[NB] = X->V2;
   X->bpmax = (int32_t)std::max<int64_t>(128, round_up(bmax, 128));
   const int32_t BP = X->bpmax;
-  if (multi) X->relax_bg_exec += NB * spq::dense_fw_exec_relax(BP / 128, 128, X->cpivot);
+  if (multi) X->relax_bg_exec += NB * spq::dense_fw_exec_relax(BP / 128, 128, X->cpivot, nullptr, NB);
   HIP_TRY(hipMemcpyAsync(X->b2off, X->h_b2off.data(), sizeof(int32_t) * (G + 1), hipMemcpyHostToDevice, s));
   HIP_TRY(dalloc(&X->boff, NB + 1));
   HIP_TRY(dalloc(&X->bsize, NB));
@@ -630,6 +630,15 @@ static spq_status build_share(spq_index* X, spq::HierArgs& ha, int64_t m, bool p
   HIP_TRY(spq::launch_mp_zero(X->mp, s));
   HIP_TRY(spq::launch_share_compose(ha, X->DT, s));
   return SPQ_OK;
+}
+
+// End of the run of consecutive big components of one padded size that starts
+// at c (closed as one batch; single: one at a time); c if c is not big.
+static int32_t big_run(const spq_index* X, int32_t c, bool single) {
+  if (X->h_cnt[c] <= spq::BIG_COMP) return c;
+  int32_t c2 = c + 1;
+  while (!single && c2 < X->k && c2 - c < 65535 && X->h_cnt[c2] > spq::BIG_COMP && X->h_P[c2] == X->h_P[c]) c2++;
+  return c2;
 }
 
 // Connected components of G and their label on every BG vertex (needed by the
@@ -850,7 +859,6 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
     X->max_nb = std::max(X->max_nb, X->h_nb[c]);
     X->relax_comp += (double)X->h_cnt[c] * X->h_cnt[c] * X->h_cnt[c];
     if (big) {
-      X->relax_comp_exec += spq::dense_fw_exec_relax(X->h_P[c] / 128, 128, X->cpivot);
       X->nbig++;
     } else {
       // one workgroup runs the blocked rounds on 64-tiles, i <= j interior tiles only
@@ -858,6 +866,13 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
       X->relax_comp_exec += (double)ntc * 64.0 * 64.0 * 64.0 *
                             (1.0 + (ntc - 1) + (double)(ntc - 1) * ntc / 2.0);
     }
+  }
+  // the big components, by the runs that are closed together (plain: one each)
+  for (int32_t c = 0; c < k;) {
+    const int32_t c2 = big_run(X, c, plain);
+    if (c2 > c)
+      X->relax_comp_exec += (c2 - c) * spq::dense_fw_exec_relax(X->h_P[c] / 128, 128, X->cpivot, nullptr, c2 - c);
+    c = std::max(c2, c + 1);
   }
   X->V = X->h_bgoff[k];
   X->relax_bg = (double)X->V * X->V * X->V;
@@ -954,7 +969,7 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
     if (X->Vgp > 32768)
       return guard(fail(SPQ_EINVAL, "a group holds more than 32,768 BG vertices: lower "
                                     "group_comps or group_bg"));
-    X->relax_bg_exec = X->ngroups * spq::dense_fw_exec_relax(X->Vgp / 128, 128, X->cpivot);
+    X->relax_bg_exec = X->ngroups * spq::dense_fw_exec_relax(X->Vgp / 128, 128, X->cpivot, nullptr, X->ngroups);
   }
   X->h_order.resize(k);
   std::iota(X->h_order.begin(), X->h_order.end(), 0);
@@ -1066,13 +1081,11 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
       // runs of consecutive big components of one padded size lie back to
       // back in M (offsets follow the ids): one batched closure per run
       for (int32_t c = 0; c < k && e == hipSuccess;) {
-        if (X->h_cnt[c] <= spq::BIG_COMP) {
+        const int32_t c2 = big_run(X, c, false), P = X->h_P[c];
+        if (c2 == c) {
           c++;
           continue;
         }
-        const int32_t P = X->h_P[c];
-        int32_t c2 = c + 1;
-        while (c2 < k && c2 - c < 65535 && X->h_cnt[c2] > spq::BIG_COMP && X->h_P[c2] == P) c2++;
         e = spq::launch_dense_fw_batch(X->M + X->h_moff[c], P, 128, P / 128, c2 - c, (int64_t)P * P, st,
                                        nullptr, inner_kc, X->cpivot);
         c = c2;
@@ -1261,7 +1274,7 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
       X->V3p = round_up(X->V3, 128);
       X->m3pmax = (int32_t)std::max<int64_t>(128, round_up(m3max, 128));
       // executed relaxations of level 3's closures
-      X->relax_bg_exec += nT * spq::dense_fw_exec_relax(V3gp / 128, 128, X->cpivot);
+      X->relax_bg_exec += nT * spq::dense_fw_exec_relax(V3gp / 128, 128, X->cpivot, nullptr, nT);
       if (X->V3p > 0) X->relax_bg_exec += spq::dense_fw_exec_relax(X->V3p / 128, 128, X->cpivot);
       TRY(hipMemcpyAsync(X->b3off, X->h_b3off.data(), sizeof(int32_t) * (nT + 1),
                          hipMemcpyHostToDevice, s));

@@ -14,8 +14,9 @@ namespace spq {
 // Blocked Floyd-Warshall on one symmetric matrix of nt x nt tiles, in rounds
 // over pivot blocks of one, two or four tiles (the tiles left at the end form
 // smaller blocks):
-//   close    the pivot block: k_fw_diag for one tile; a larger block by the
-//            same rounds on the sub-matrix, over blocks of half its size
+//   close    the pivot block: k_fw_diag for one tile; a larger block by
+//            squarings (k_fw_square) or, in large batches, by the same rounds on
+//            the sub-matrix, over blocks of half its size
 //   panel    tile (a, j), a in the block, j outside it: tile (a, j) =
 //            D (x) tile (a, j), stored twice (as (a, j) and transposed as
 //            (j, a)); k_fw_inner part 3 (k_fw_panel in fw_rounds, the
@@ -29,8 +30,8 @@ namespace spq {
 // A batch of equally sized matrices (one-tile blocks only) is handled by
 // blockIdx.y: matrix y starts gstride elements after matrix y-1.
 template <int T>
-__global__ __launch_bounds__(256) void k_fw_diag(u32* __restrict__ A, int64_t ld, int r,
-                                                 int64_t gstride) {
+__global__ __launch_bounds__(256) void k_fw_diag64(u32* __restrict__ A, int64_t ld, int r,
+                                                   int64_t gstride) {
   __shared__ __attribute__((aligned(16))) u32 rb[4 * T];
   A += (int64_t)blockIdx.y * gstride;
   u32 t[T / 16][T / 16];
@@ -38,6 +39,65 @@ __global__ __launch_bounds__(256) void k_fw_diag(u32* __restrict__ A, int64_t ld
   tile_load<T>(t, D, ld);
   fw_tile<T>(t, rb);
   tile_store<T>(t, D, ld);
+}
+
+// A 128-tile by 1,024 threads, 4 x 4 entries each (rows ty*4 + a, columns tx*4 +
+// a): fw_tile's two pivots per barrier, with four waves per SIMD to cover the
+// LDS reads and the barrier.  Bound by one CU's VALU (768 cycles for each of the
+// 64 steps' relaxations).  A grid32-sized closure through it 0.87 -> 0.62 ms;
+// 256 threads of 8 x 8, one wave per SIMD, took 53 us a tile.
+__global__ __launch_bounds__(1024) void k_fw_diag128(u32* __restrict__ A, int64_t ld, int r,
+                                                     int64_t gstride) {
+  constexpr int T = 128;
+  __shared__ __attribute__((aligned(16))) u32 rb[4 * T];
+  u32* D = A + (int64_t)blockIdx.y * gstride + (int64_t)r * T * ld + (int64_t)r * T;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  u32 c[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    const uint4 v = *reinterpret_cast<const uint4*>(D + (int64_t)(ty * 4 + i) * ld + tx * 4);
+    c[i][0] = v.x; c[i][1] = v.y; c[i][2] = v.z; c[i][3] = v.w;
+  }
+  auto put = [&](u32* buf, int i) {
+    *reinterpret_cast<uint4*>(buf + tx * 4) = make_uint4(c[i][0], c[i][1], c[i][2], c[i][3]);
+  };
+  for (int k = 0; k < T; k += 2) {
+    u32* buf = rb + ((k >> 1) & 1) * 2 * T;
+    if (ty == k >> 2) {  // rows k, k + 1
+      if (k & 2) {
+        put(buf, 2);
+        put(buf + T, 3);
+      } else {
+        put(buf, 0);
+        put(buf + T, 1);
+      }
+    }
+    __syncthreads();
+    const u32 s = buf[T + k];  // M[k+1][k]
+    const uint4 x = *reinterpret_cast<const uint4*>(buf + tx * 4);
+    const uint4 y = *reinterpret_cast<const uint4*>(buf + T + tx * 4);
+    const uint4 p = *reinterpret_cast<const uint4*>(buf + ty * 4);
+    const uint4 q = *reinterpret_cast<const uint4*>(buf + T + ty * 4);
+    const u32 kc[4] = {x.x, x.y, x.z, x.w}, kr[4] = {p.x, p.y, p.z, p.w};
+    const u32 k1c[4] = {min(y.x, s + x.x), min(y.y, s + x.y), min(y.z, s + x.z), min(y.w, s + x.w)};
+    const u32 k1r[4] = {min(q.x, s + p.x), min(q.y, s + p.y), min(q.z, s + p.z), min(q.w, s + p.w)};
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+#pragma unroll
+      for (int j = 0; j < 4; j++) relax2(c[i][j], kr[i], kc[j], k1r[i], k1c[j]);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; i++)
+    *reinterpret_cast<uint4*>(D + (int64_t)(ty * 4 + i) * ld + tx * 4) =
+        make_uint4(c[i][0], c[i][1], c[i][2], c[i][3]);
+}
+
+template <int T>
+static void fw_diag(u32* A, int64_t ld, int r, int batch, int64_t gstride, hipStream_t s) {
+  if (T == 128)
+    k_fw_diag128<<<dim3(1, batch), 1024, 0, s>>>(A, ld, r, gstride);
+  else
+    k_fw_diag64<64><<<dim3(1, batch), 256, 0, s>>>(A, ld, r, gstride);
 }
 
 template <int T>
@@ -173,6 +233,96 @@ __global__ __launch_bounds__(256) SPQ_INNER_ATTR void k_fw_inner(u32* __restrict
   if (i != j) tile_store_t<T>(t, A + (int64_t)j * T * ld + (int64_t)i * T, ld);
 }
 
+// One squaring of the B x B block at A (B = 32 nb), in place: every entry takes
+// the minimum over two-step walks.  After ceil(log2(B - 1)) squarings any walk of
+// the block's at most B - 1 steps is covered: the closure, without the serial
+// chain of B pivots in one workgroup.  In place is exact in any
+// interleaving: every value read is the length of a real walk and at most the
+// old value.  One workgroup per 32 x 32 tile i <= j (the other triangle gets the
+// transpose); its four waves take a quarter of the K each, 4 x 4 entries per
+// lane, operand rows straight to LDS 16 at a time, double buffered: 32 KB, which
+// fits beside a running interior launch.  Bound by launch and load latency: a
+// 256-wide block closes in 8 launches of 8.7 us (70 us; the rounds over its two
+// 128-tiles took 258: two diagonal tiles of 52 us and four one-tile products of 39
+// us in a row).
+__global__ __launch_bounds__(256) void k_fw_square(u32* A, int64_t ld, int nb, int64_t gstride) {
+  constexpr int KC = 16;
+  __shared__ __attribute__((aligned(16))) u32 sm[4][2][2][KC * 32];
+  A += (int64_t)blockIdx.y * gstride;
+  int bi, bj;
+  tri_index((int)blockIdx.x, nb, bi, bj);
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int ly = lane >> 3, lx = lane & 7, kn = nb * 8;  // K rows per wave
+  const u32* Ar = A + (int64_t)(w * kn + ly) * ld + bi * 32 + lx * 4;
+  const u32* Br = A + (int64_t)(w * kn + ly) * ld + bj * 32 + lx * 4;
+  // eight lanes fetch a row's 32 words: a wave's load fills eight rows
+  auto load = [&](int k, int buf) {
+#pragma unroll
+    for (int i = 0; i < KC / 8; i++) {
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(Ar + (int64_t)(k + i * 8) * ld),
+                                       (__attribute__((address_space(3))) void*)(&sm[w][buf][0][i * 256]), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(Br + (int64_t)(k + i * 8) * ld),
+                                       (__attribute__((address_space(3))) void*)(&sm[w][buf][1][i * 256]), 16, 0, 0);
+    }
+  };
+  // thread t keeps four entries of the tile for the end
+  const int er = threadIdx.x >> 3, ec = (threadIdx.x & 7) * 4;
+  u32* Cp = A + (int64_t)(bi * 32 + er) * ld + bj * 32 + ec;
+  load(0, 0);
+  const uint4 old = *reinterpret_cast<const uint4*>(Cp);
+  u32 c[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; i++)
+#pragma unroll
+    for (int j = 0; j < 4; j++) c[i][j] = INF;
+  for (int k = 0; k < kn; k += KC) {
+    const int buf = (k / KC) & 1;
+    // the chunk has arrived, and every LDS read of the other buffer is over
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    if (k + KC < kn) load(k + KC, buf ^ 1);
+    const u32 *sa = sm[w][buf][0] + ly * 4, *sb = sm[w][buf][1] + lx * 4;
+#pragma unroll
+    for (int q = 0; q < KC; q += 2) {
+      const uint4 a0 = *reinterpret_cast<const uint4*>(sa + q * 32);
+      const uint4 a1 = *reinterpret_cast<const uint4*>(sa + q * 32 + 32);
+      const uint4 b0 = *reinterpret_cast<const uint4*>(sb + q * 32);
+      const uint4 b1 = *reinterpret_cast<const uint4*>(sb + q * 32 + 32);
+      const u32 av[4] = {a0.x, a0.y, a0.z, a0.w}, aw[4] = {a1.x, a1.y, a1.z, a1.w};
+      const u32 bv[4] = {b0.x, b0.y, b0.z, b0.w}, bw[4] = {b1.x, b1.y, b1.z, b1.w};
+#pragma unroll
+      for (int i = 0; i < 4; i++)
+#pragma unroll
+        for (int j = 0; j < 4; j++) relax2(c[i][j], av[i], bv[j], aw[i], bw[j]);
+    }
+  }
+  __syncthreads();
+  u32* red = &sm[0][0][0][0];  // [4][32][32]: the waves' minima
+#pragma unroll
+  for (int i = 0; i < 4; i++)
+    *reinterpret_cast<uint4*>(red + w * 1024 + (ly * 4 + i) * 32 + lx * 4) =
+        make_uint4(c[i][0], c[i][1], c[i][2], c[i][3]);
+  __syncthreads();
+  uint4 v = old;
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    const uint4 x = *reinterpret_cast<const uint4*>(red + i * 1024 + er * 32 + ec);
+    v.x = min(v.x, x.x);
+    v.y = min(v.y, x.y);
+    v.z = min(v.z, x.z);
+    v.w = min(v.w, x.w);
+  }
+  *reinterpret_cast<uint4*>(Cp) = v;
+  if (bi == bj) return;
+  u32* tr = red + 4096;  // [32][33]
+  tr[(ec + 0) * 33 + er] = v.x;
+  tr[(ec + 1) * 33 + er] = v.y;
+  tr[(ec + 2) * 33 + er] = v.z;
+  tr[(ec + 3) * 33 + er] = v.w;
+  __syncthreads();
+  *reinterpret_cast<uint4*>(A + (int64_t)(bj * 32 + er) * ld + bi * 32 + ec) =
+      make_uint4(tr[er * 33 + ec], tr[er * 33 + ec + 1], tr[er * 33 + ec + 2], tr[er * 33 + ec + 3]);
+}
+
 #ifndef SPQ_INNER_KC
 #define SPQ_INNER_KC 16
 #endif
@@ -181,7 +331,7 @@ template <int T, int KC>
 static hipError_t fw_rounds(u32* A, int64_t ld, int nt, int batch, int64_t gstride, hipStream_t s,
                            hipEvent_t* ev) {
   for (int r = 0; r < nt; r++) {
-    k_fw_diag<T><<<dim3(1, batch), 256, 0, s>>>(A, ld, r, gstride);
+    fw_diag<T>(A, ld, r, batch, gstride, s);
     if (nt > 1) {
       k_fw_panel<T><<<dim3(nt - 1, batch), 256, 0, s>>>(A, ld, r, gstride);
       if (ev) {
@@ -198,6 +348,10 @@ static hipError_t fw_rounds(u32* A, int64_t ld, int nt, int batch, int64_t gstri
   }
   LAUNCH_CHECK();
 }
+
+// Workgroups of a squaring launch, and 128-tiles of an interior launch, up to
+// which the block closure and the split into 64-tiles above are taken.
+constexpr int64_t SQUARE_WGS = 1024, SPLIT_TILES = 512;
 
 // Pivot blocks of a single matrix: pivot_tiles (1, 2 or 4) tiles each; the
 // tiles left at the end form blocks of two and one.
@@ -235,20 +389,89 @@ template <int T, int KC>
 static hipError_t fw_rounds_blocks(u32* A, int64_t ld, int nt, int pivot_tiles, FwBatch bt,
                                    hipStream_t s, hipEvent_t* ev);
 
-// Closes the diagonal block: one tile in one workgroup (k_fw_diag); a block
-// of two or four tiles by the rounds of this file on the sub-matrix, over
-// blocks of half its size.  Every launch of a block closure is small (one to
-// six workgroups of 32 KB LDS at most), so beside a running interior launch
-// it finds room on a CU at once; one workgroup holding two tiles in LDS
-// (130 KB) waited for a whole CU to drain, about as long as the interior.
+// Squarings that close a block of n vertices.
+static int fw_squarings(int n) {
+  int q = 0;
+  while ((1 << q) < n - 1) q++;
+  return q;
+}
+
+// Whether the pivot blocks of `pt` tiles of a batch are closed by squarings:
+// they execute more relaxations than the rounds over half-size blocks (8 x 256^3
+// / 2 against 6 x 128^3 for two 128-tiles) but in short launches of many
+// workgroups.  While a launch is at most four workgroups per CU they are the faster
+// way: 70 against 258 us for one 256-row block, 16 blocks in a batch 130 against
+// about 270 (a batch of 128 such blocks: 850 against about 300).
+static bool fw_by_squaring(int tile, int pt, int batch) {
+  return pt > 1 && tri_count(pt * tile / 32) * batch <= SQUARE_WGS;
+}
+
+static void fw_square_all(u32* D, int64_t ld, int n, FwBatch bt, hipStream_t s) {
+  for (int q = fw_squarings(n); q > 0; q--)
+    k_fw_square<<<dim3((unsigned)tri_count(n / 32), (unsigned)bt.batch), 256, 0, s>>>(D, ld, n / 32,
+                                                                                     bt.gstride);
+}
+
+// A whole matrix of up to 512 vertices is one block.
+static bool fw_all_squaring(int tile, int nt, int pt, int batch) {
+  return pt > 1 && nt > 1 && nt * tile <= 512 && fw_by_squaring(tile, nt, batch);
+}
+
+// Closes the diagonal block: one tile in one workgroup (fw_diag); a block of
+// two or four tiles by squarings or by the rounds of this file on the
+// sub-matrix, over blocks of half its size.  Every launch of a block closure is
+// small (32 KB LDS at most), so beside a running interior launch it finds room
+// on a CU at once; one workgroup holding two tiles in LDS (130 KB) waited for
+// a whole CU to drain, about as long as the interior.
 template <int T, int KC>
 static hipError_t fw_close(u32* A, int64_t ld, FwBlock b, FwBatch bt, hipStream_t s) {
   if (b.pt == 1) {
-    k_fw_diag<T><<<dim3(1, bt.batch), 256, 0, s>>>(A, ld, b.c0, bt.gstride);
+    fw_diag<T>(A, ld, b.c0, bt.batch, bt.gstride, s);
     return hipGetLastError();
   }
-  return fw_rounds_blocks<T, KC>(A + (int64_t)b.c0 * T * ld + (int64_t)b.c0 * T, ld, b.pt, b.pt / 2,
-                                 bt, s, nullptr);
+  u32* D = A + (int64_t)b.c0 * T * ld + (int64_t)b.c0 * T;
+  if (fw_by_squaring(T, b.pt, bt.batch)) {
+    fw_square_all(D, ld, b.pt * T, bt, s);
+    return hipGetLastError();
+  }
+  return fw_rounds_blocks<T, KC>(D, ld, b.pt, b.pt / 2, bt, s, nullptr);
+}
+
+// One launch of the interior kernel, part as in inner_tile, on `count` T-tiles
+// per matrix.  A launch that leaves most CUs idle runs on 64-tiles instead: four
+// times the workgroups, each with a quarter of the serial work (116 tiles of 128
+// through 256 pivot rows 77 us, as 464 of 64 32 us; up to 512 tiles, two per CU,
+// measured no slower split).
+template <int T, int KC>
+static void inner_launch(u32* A, int64_t ld, int nt, FwBlock b, int part, int nn, int64_t count,
+                         FwBatch bt, hipStream_t s) {
+  const dim3 grid((unsigned)count, (unsigned)bt.batch);
+  if (b.pt == 1)
+    k_fw_inner<T, KC, 1><<<grid, 256, 0, s>>>(A, ld, b.c0, nt, bt.gstride, part, nn);
+  else if (b.pt == 2)
+    k_fw_inner<T, KC, 2><<<grid, 256, 0, s>>>(A, ld, b.c0, nt, bt.gstride, part, nn);
+  else if (b.pt == 4)
+    k_fw_inner<T, KC, 4><<<grid, 256, 0, s>>>(A, ld, b.c0, nt, bt.gstride, part, nn);
+  else if constexpr (T == 64 && KC == 16)  // four 128-tiles, split
+    k_fw_inner<T, KC, 8><<<grid, 256, 0, s>>>(A, ld, b.c0, nt, bt.gstride, part, nn);
+}
+
+static int64_t part_count(int nt, FwBlock b, int part, int nn) {
+  return part == 3 ? (int64_t)b.pt * (nt - b.pt) : inner_count(nt, b, part, nn);
+}
+
+template <int T, int KC>
+static hipError_t fw_inner(u32* A, int64_t ld, int nt, FwBlock b, int part, int nn, FwBatch bt,
+                           hipStream_t s) {
+  const int64_t count = part_count(nt, b, part, nn);
+  if (count <= 0) return hipSuccess;
+  if (T == 128 && count * bt.batch <= SPLIT_TILES) {
+    const FwBlock h{b.c0 * 2, b.pt * 2};
+    inner_launch<64, 16>(A, ld, nt * 2, h, part, nn * 2, part_count(nt * 2, h, part, nn * 2), bt, s);
+  } else {
+    inner_launch<T, KC>(A, ld, nt, b, part, nn, count, bt, s);
+  }
+  return hipGetLastError();
 }
 
 // The panel of block b: tiles (a, j), a in the block, j outside it, by the
@@ -256,30 +479,7 @@ static hipError_t fw_close(u32* A, int64_t ld, FwBlock b, FwBatch bt, hipStream_
 // reason as above).
 template <int T, int KC>
 static hipError_t fw_panel(u32* A, int64_t ld, int nt, FwBlock b, FwBatch bt, hipStream_t s) {
-  if (nt <= b.pt) return hipSuccess;
-  const dim3 grid((unsigned)(b.pt * (nt - b.pt)), (unsigned)bt.batch);
-  if (b.pt == 1)
-    k_fw_inner<T, KC, 1><<<grid, 256, 0, s>>>(A, ld, b.c0, nt, bt.gstride, 3, 0);
-  else if (b.pt == 2)
-    k_fw_inner<T, KC, 2><<<grid, 256, 0, s>>>(A, ld, b.c0, nt, bt.gstride, 3, 0);
-  else
-    k_fw_inner<T, KC, 4><<<grid, 256, 0, s>>>(A, ld, b.c0, nt, bt.gstride, 3, 0);
-  return hipGetLastError();
-}
-
-template <int T, int KC>
-static hipError_t fw_inner(u32* A, int64_t ld, int nt, FwBlock b, int part, int nn, FwBatch bt,
-                           hipStream_t s) {
-  const int64_t count = inner_count(nt, b, part, nn);
-  if (count <= 0) return hipSuccess;
-  const dim3 grid((unsigned)count, (unsigned)bt.batch);
-  if (b.pt == 1)
-    k_fw_inner<T, KC, 1><<<grid, 256, 0, s>>>(A, ld, b.c0, nt, bt.gstride, part, nn);
-  else if (b.pt == 2)
-    k_fw_inner<T, KC, 2><<<grid, 256, 0, s>>>(A, ld, b.c0, nt, bt.gstride, part, nn);
-  else
-    k_fw_inner<T, KC, 4><<<grid, 256, 0, s>>>(A, ld, b.c0, nt, bt.gstride, part, nn);
-  return hipGetLastError();
+  return fw_inner<T, KC>(A, ld, nt, b, 3, 0, bt, s);
 }
 
 #define CHK(x)                              \
@@ -377,6 +577,10 @@ static hipError_t dense_lookahead(u32* A, int64_t ld, int tile, int nt, FwBatch 
                                   hipEvent_t* ev, int kc, int pivot) {
   if (nt <= 0 || bt.batch <= 0) return hipSuccess;
   const int pt = pivot_tiles_of(tile, pivot);
+  if (!ev && fw_all_squaring(tile, nt, pt, bt.batch)) {
+    fw_square_all(A, ld, nt * tile, bt, s);
+    return hipGetLastError();
+  }
   if (kc == 0) kc = SPQ_INNER_KC;
   if (tile == 64)
     return kc == 32 ? fw_rounds_lookahead<64, 32>(A, ld, nt, pt, bt, s, side, p1, sync, ev)
@@ -407,6 +611,10 @@ hipError_t launch_dense_fw_batch(u32* A, int64_t ld, int tile, int nt, int batch
   const int pt = pivot_tiles_of(tile, pivot);
   if (pt > 1) {
     const FwBatch bt{batch, gstride};
+    if (!ev && fw_all_squaring(tile, nt, pt, batch)) {
+      fw_square_all(A, ld, nt * tile, bt, s);
+      return hipGetLastError();
+    }
     if (tile == 64)
       return kc == 32 ? fw_rounds_blocks<64, 32>(A, ld, nt, pt, bt, s, ev)
                       : fw_rounds_blocks<64, 16>(A, ld, nt, pt, bt, s, ev);
@@ -420,18 +628,26 @@ hipError_t launch_dense_fw_batch(u32* A, int64_t ld, int tile, int nt, int batch
                   : fw_rounds<128, 16>(A, ld, nt, batch, gstride, s, ev);
 }
 
-// Executed relaxations: per round the diagonal block (one tile: T^3; more:
-// the rounds over half-size blocks on it), the panel (each of its tiles K =
-// block rows) and the upper-triangle interior tiles; `inner` gets the
-// interior part.
-double dense_fw_exec_relax(int64_t nt, int tile, int pivot, double* inner) {
+// Executed relaxations of a matrix closed in a batch of `batch`: per round the
+// pivot block (one tile: T^3; more: squarings, or the rounds over half-size
+// blocks on it), the panel (each of its tiles K = block rows) and the
+// upper-triangle interior tiles; `inner` gets the interior part.
+static double square_relax(int64_t n) {
+  return (double)fw_squarings((int)n) * (double)tri_count(n / 32) * 1024.0 * (double)n;
+}
+
+double dense_fw_exec_relax(int64_t nt, int tile, int pivot, double* inner, int batch) {
   const double t3 = (double)tile * tile * tile;
   const int ptiles = pivot_tiles_of(tile, pivot);
+  if (inner) *inner = 0;
+  if (fw_all_squaring(tile, (int)nt, ptiles, batch)) return square_relax(nt * tile);
   std::vector<FwBlock> blk(fw_blocks((int)nt, ptiles, nullptr));
   fw_blocks((int)nt, ptiles, blk.data());
   double all = 0, in = 0;
   for (const FwBlock& b : blk) {
-    all += b.pt == 1 ? t3 : dense_fw_exec_relax(b.pt, tile, b.pt / 2 * tile, nullptr);
+    all += b.pt == 1                            ? t3
+           : fw_by_squaring(tile, b.pt, batch) ? square_relax(b.pt * tile)
+                                                : dense_fw_exec_relax(b.pt, tile, b.pt / 2 * tile, nullptr, batch);
     if (nt <= b.pt) continue;
     all += (double)b.pt * (nt - b.pt) * b.pt * t3;
     const double x = (double)tri_count(nt - b.pt) * b.pt * t3;

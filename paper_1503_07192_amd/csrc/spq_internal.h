@@ -291,9 +291,9 @@ hipError_t launch_dense_fw_batch_lookahead(u32* A, int64_t ld, int tile, int nt,
                                            hipEvent_t* sync, hipEvent_t* ev, int kc, int pivot);
 // rounds of a single-matrix closure (pivot blocks)
 int fw_rounds_count(int nt, int tile, int pivot);
-// relaxations executed by launch_dense_fw (diagonal, panel and upper-triangle
+// relaxations executed per matrix by launch_dense_fw and its batches (diagonal, panel and upper-triangle
 // interior tiles of every round); *inner (optional) = the interior part
-double dense_fw_exec_relax(int64_t nt, int tile, int pivot = 0, double* inner = nullptr);
+double dense_fw_exec_relax(int64_t nt, int tile, int pivot = 0, double* inner = nullptr, int batch = 1);
 hipError_t launch_query(const QueryArgs& a, hipStream_t s);
 // VALU rate probes (probe.hip): kind 0 v_add_u32, 1 v_min3_u32, 2 the
 // relaxation loop on LDS operands; out: blocks * 256 words
