@@ -56,10 +56,15 @@ typedef struct {
                           HIP events (see spq_stats) */
   int32_t plain;       /* 1: one kernel launch per component for APSP(C)
                           instead of one launch for all (comparison path) */
-  int32_t bg_method;   /* 0 auto (flat up to 32,768 BG vertices), 1 flat
-                          Floyd-Warshall on all of BG, 2 two-level */
+  int32_t bg_method;   /* 0 auto (up to 32,768 BG vertices, and with bg_tile
+                          and bg_pivot 0, whichever method is estimated
+                          faster from the partition's cuts, or flat; above,
+                          two-level), 1 flat Floyd-Warshall on all of BG,
+                          2 two-level */
   int32_t group_comps; /* two-level: consecutive components per group
-                          (0 = auto: about 4,096 BG vertices per group).  A
+                          (0 = auto: up to 131,072 BG vertices the power of
+                          two estimated fastest, above about 4,096 BG
+                          vertices per group).  A
                           share build with 100 groups or more cuts a group
                           that is wider (in 128-tiles of BG vertices) than
                           the 99th percentile into halves of consecutive
@@ -87,11 +92,12 @@ typedef struct {
                           SPQ_PATHS: keep the graph's adjacency (20 bytes per
                           edge) for spq_query_paths */
   int32_t level3_groups; /* two-level: BG2 (the graph of the group boundaries)
-                          is closed by flat Floyd-Warshall, or, above 16,384
-                          BG2 vertices, by the same construction once more on
-                          super-groups of consecutive groups (level 3).
-                          0 auto (about 4,096 BG2 vertices per super-group),
-                          -1 never, g > 0 always, g groups per super-group.
+                          is closed by flat Floyd-Warshall, or by the same
+                          construction once more on super-groups of
+                          consecutive groups (level 3).  0 auto (whichever is
+                          estimated faster, over powers of two of groups per
+                          super-group), -1 never, g > 0 always, g groups per
+                          super-group.
                           Share mode never builds BG2: there it sets the
                           blocks of its Bellman-Ford over BG2, g consecutive
                           groups per block (closed together, so a round

@@ -202,7 +202,8 @@ struct spq_index {
   int32_t *P = nullptr, *order = nullptr, *bgcomp = nullptr, *bglocal = nullptr;
   int32_t *cnt = nullptr, *fill = nullptr;
   int64_t* moff = nullptr;
-  uint8_t* flag = nullptr;
+  u32* flag = nullptr;
+  u32 h_marks[32] = {};  // boundary vertices by mark (k_edges_scan)
   unsigned long long *sumc = nullptr, *total = nullptr;
   u32 *err = nullptr, *members = nullptr, *M = nullptr, *BG = nullptr;
   u32* vrec = nullptr;
@@ -641,6 +642,90 @@ static int32_t big_run(const spq_index* X, int32_t c, bool single) {
   return c2;
 }
 
+// What the closures and the composition are estimated to take, in seconds
+// (MI355X): each is its executed relaxations at the measured rate plus a time
+// per round or launch sequence.  Used to choose between methods whose results
+// are the same.  Measured beside them: flat closures of 860 / 1,596 / 3,740 /
+// 6,780 / 15,548 / 27,900 vertices 0.5 / 0.9 / 2.7 / 8.3 / 60 / 324 ms, two-tile
+// closures of 1,792 / 5,512 / 7,680 vertices 0.9 / 5.8 / 10 ms, batches of 16 of 1,792
+// and 8 of 3,712 vertices 2.8 and 10 ms, compositions of 7.0e9 entries through
+// 230 vertices 42 ms and of 3.9e8 through 480 5 ms.
+static double flat_seconds(double v) {
+  if (v <= 512) return 7e-5;
+  return std::ceil(v / 512) * 2.4e-4 + v * v * v / 2 / 33e12 + v * v * 8 / 2.5e12;
+}
+static double closure_seconds(double v, double batch) {
+  if (v <= 512 && batch <= 13) return v <= 32 ? 2e-5 : 1e-4;
+  return std::ceil(v / 256) * (batch > 1 ? 1.5e-4 : 1.1e-4) + batch * v * v * v / 2 / 28e12;
+}
+static double compose_seconds(double entries, double through) {
+  return 2.5e-4 + entries * through / 38e12 + entries * 4 / 2.5e12;
+}
+
+// Boundary vertices of the partition into runs of `comps` components, counted
+// for the power of two at or below it (at least as many).
+static double cut_vertices(const spq_index* X, double comps) {
+  int j = 0;
+  while (j < 31 && (double)(2ll << j) <= comps) j++;
+  double c = 0;
+  for (int i = j + 1; i < 32; i++) c += X->h_marks[i];
+  return c;
+}
+
+// How to close BG2 (v2 vertices of G groups of `comps` components; b2off: the
+// groups' first BG2 ids, NULL while only their number is known): gpt = 0 by one
+// flat closure, else by level 3 on super-groups of gpt groups (a power of two).
+struct Bg2Plan {
+  int32_t gpt;
+  double seconds;
+};
+static Bg2Plan bg2_plan(const spq_index* X, int32_t G, double comps, double v2, const int32_t* b2off) {
+  Bg2Plan best{0, closure_seconds(v2, 1)};
+  for (int32_t gpt = 2; gpt < G; gpt *= 2) {
+    const double nT = std::ceil((double)G / gpt);
+    double size = v2 / G * gpt;  // of the widest super-group: all are padded to it
+    if (b2off)
+      for (int32_t g = 0; g < G; g += gpt) size = std::max(size, (double)(b2off[std::min(g + gpt, G)] - b2off[g]));
+    if (size * size * nT > v2 * v2) continue;  // (more memory than BG2 itself)
+    const double v3 = std::min(v2, cut_vertices(X, comps * gpt));
+    const double t = 3e-4 + closure_seconds(size, nT) + closure_seconds(v3, 1) +
+                     compose_seconds(v2 * v2 / 2, v3 / nT);
+    if (t < best.seconds) best = Bg2Plan{gpt, t};
+  }
+  return best;
+}
+
+// The fastest two-level plan over powers of two of components per group (cpg =
+// 0: none), with groups of at most 4,096 BG vertices.  Measured builds, planned
+// against the flat closure or groups of about 4,096: 1,596 BG vertices 0.75 - 0.90
+// against 1.28 ms, 6,780 2.0 - 2.6 against 8.7, 27,900 5.8 - 14 against 327, 38,426
+// 10.7 against 27; partitions that cut everywhere (shuffled) stay flat.  Above
+// PLAN_MAX BG vertices the groups stay at about 4,096.
+constexpr int32_t PLAN_MAX = 131072;
+struct TwoLevelPlan {
+  int32_t cpg;
+  double seconds;
+};
+static TwoLevelPlan plan_two_level(const spq_index* X) {
+  TwoLevelPlan best{0, 1e30};
+  const double V = X->V;
+  std::vector<int32_t> size(X->h_nb);  // BG vertices of every run of cpg components
+  for (int64_t cpg = 1; cpg < X->k; cpg *= 2) {
+    const int32_t G = (int32_t)size.size(), widest = *std::max_element(size.begin(), size.end());
+    if (widest > 4096) break;
+    if (G <= 1024 && (double)G * widest * widest <= V * V) {
+      const double v2 = cut_vertices(X, (double)cpg);
+      const double t = 3e-4 + closure_seconds(widest, G) + bg2_plan(X, G, (double)cpg, v2, nullptr).seconds +
+                       compose_seconds(V * V / 2, v2 / G);
+      if (t < best.seconds) best = TwoLevelPlan{(int32_t)cpg, t};
+    }
+    for (size_t i = 0; 2 * i < size.size(); i++)
+      size[i] = size[2 * i] + (2 * i + 1 < size.size() ? size[2 * i + 1] : 0);
+    size.resize((size.size() + 1) / 2);
+  }
+  return best;
+}
+
 // Connected components of G and their label on every BG vertex (needed by the
 // exactness certificate).  Synchronous: one small readback per round.
 static spq_status cc_labels(spq_index* X, int64_t m, const int32_t* eu, const int32_t* ev,
@@ -726,12 +811,14 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
   bool profile = false, plain = false;
   int32_t method_opt = 0, group_comps = 0, share_comps = 0, inner_kc = 0;
   bool lookahead = true, use_graph = false, use_paths = false;
+  bool plain_flat = true;  // no option of the flat closure is set
   int32_t level3_opt = 0, group_bg = 0, pivot = 0;
   if (opts) {
     if (opts->bg_tile != 0 && opts->bg_tile != 64 && opts->bg_tile != 128)
       return fail(SPQ_EINVAL, "bg_tile must be 0, 64 or 128");
     if (opts->bg_tile) tile = opts->bg_tile;
     pivot = opts->bg_pivot;
+    plain_flat = opts->bg_tile == 0 && pivot == 0;
     if (pivot != 0 && pivot != tile && pivot != 2 * tile && pivot != 4 * tile)
       return fail(SPQ_EINVAL, "bg_pivot must be 0 or 1, 2 or 4 tiles");
     profile = opts->profile != 0;
@@ -797,32 +884,35 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
   TRY(dalloc(&X->nb, k));
   TRY(dalloc(&X->flag, n));
   TRY(dalloc(&X->sumc, k));
-  TRY(dalloc(&X->total, 1));
+  TRY(dalloc(&X->total, 1 + 16));  // the total weight, then the marks' counts
   TRY(dalloc(&X->err, 1));
   TRY(hipMemsetAsync(X->cnt, 0, sizeof(int32_t) * k, s));
   TRY(hipMemsetAsync(X->nb, 0, sizeof(int32_t) * k, s));
-  TRY(hipMemsetAsync(X->flag, 0, n, s));
+  TRY(hipMemsetAsync(X->flag, 0, sizeof(u32) * (size_t)n, s));
   TRY(hipMemsetAsync(X->sumc, 0, sizeof(unsigned long long) * k, s));
-  TRY(hipMemsetAsync(X->total, 0, sizeof(unsigned long long), s));
+  TRY(hipMemsetAsync(X->total, 0, 17 * sizeof(unsigned long long), s));
   TRY(hipMemsetAsync(X->err, 0, sizeof(u32), s));
   spq::PartArgs pa{};
   pa.n = n; pa.k = k; pa.m = m;
   pa.eu = eu; pa.ev = ev; pa.w = w; pa.part = part;
   pa.cnt = X->cnt; pa.nb = X->nb; pa.flag = X->flag; pa.sumc = X->sumc;
   pa.total = X->total; pa.err = X->err;
+  pa.marks = reinterpret_cast<u32*>(X->total + 1);
   TRY(spq::launch_partition_scan(pa, s));
   u32 herr = 0;
-  unsigned long long htotal = 0;
+  unsigned long long htotals[17] = {};
   X->h_cnt.resize(k);
   X->h_nb.resize(k);
   X->h_sumc.resize(k);
   TRY(hipMemcpyAsync(&herr, X->err, sizeof(u32), hipMemcpyDeviceToHost, s));
-  TRY(hipMemcpyAsync(&htotal, X->total, sizeof(htotal), hipMemcpyDeviceToHost, s));
+  TRY(hipMemcpyAsync(htotals, X->total, sizeof(htotals), hipMemcpyDeviceToHost, s));
   TRY(hipMemcpyAsync(X->h_cnt.data(), X->cnt, sizeof(int32_t) * k, hipMemcpyDeviceToHost, s));
   TRY(hipMemcpyAsync(X->h_nb.data(), X->nb, sizeof(int32_t) * k, hipMemcpyDeviceToHost, s));
   TRY(hipMemcpyAsync(X->h_sumc.data(), X->sumc, sizeof(unsigned long long) * k,
                      hipMemcpyDeviceToHost, s));
   TRY(hipStreamSynchronize(s));
+  const unsigned long long htotal = htotals[0];
+  std::memcpy(X->h_marks, htotals + 1, sizeof(X->h_marks));
   if (herr & spq::ERR_PART) return guard(fail(SPQ_EINVAL, "part[v] outside [0, k)"));
   if (herr & spq::ERR_VERTEX) return guard(fail(SPQ_EINVAL, "edge endpoint outside [0, n)"));
   if (herr & spq::ERR_WEIGHT) return guard(fail(SPQ_EINVAL, "edge weight outside [0, SPQ_INF)"));
@@ -879,6 +969,16 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
   X->method = method_opt ? method_opt : (X->V > 32768 || share_comps > 0 ? 2 : 1);
   X->share_comps = share_comps;
   int32_t cpg = k;
+  if (share_comps == 0 && group_comps == 0 && group_bg == 0 && X->V <= PLAN_MAX &&
+      (X->method == 2 || (method_opt == 0 && plain_flat))) {
+    // the estimated fastest grouping, and (up to 32,768 BG vertices) that or the
+    // flat closure, which keeps a fifth's doubt
+    const TwoLevelPlan p = plan_two_level(X);
+    if (p.cpg > 0 && (X->method == 2 || p.seconds < 0.8 * flat_seconds(X->V))) {
+      X->method = 2;
+      group_comps = p.cpg;
+    }
+  }
   if (X->method == 2) {
     if (group_comps > 0) {
       cpg = std::min(group_comps, k);
@@ -1171,18 +1271,10 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
         X->h_elems += (int64_t)X->h_gV[a1] * X->h_gV[a2];
       }
     if (!bands_match(X, G, false)) return guard(fail(SPQ_EDEVICE, "internal: band layout"));
-    // level 3: BG2 above 16,384 vertices (or as asked) is closed by super-groups
+    // level 3 (super-groups of gpt groups): as asked, or where it is estimated
+    // to close BG2 faster than one flat closure
     if (X->V2 > 0 && level3_opt >= 0) {
-      int32_t gpt = 0;
-      if (level3_opt > 0) {
-        gpt = std::min(level3_opt, G);
-      } else if (X->V2 > 16384) {
-        // about 4,096 BG2 vertices per super-group, a power of two of groups
-        const double avg = (double)X->V2 / G;
-        gpt = 1;
-        while (gpt * 2 <= G && gpt * 2 * avg <= 4096.0 * 1.41) gpt *= 2;
-        if (gpt >= G) gpt = 0;
-      }
+      const int32_t gpt = level3_opt > 0 ? std::min(level3_opt, G) : bg2_plan(X, G, (double)k / G, X->V2, X->h_b2off.data()).gpt;
       if (gpt > 0) {
         X->gpt = gpt;
         X->nT = (G + gpt - 1) / gpt;

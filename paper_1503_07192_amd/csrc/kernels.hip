@@ -28,10 +28,12 @@ __global__ void k_count_part(int32_t n, const int32_t* __restrict__ part, int32_
 
 // Validates the edges, marks the boundary (Section 2: a vertex with a
 // neighbour in another component) and sums the weights: per component for
-// edges inside it, and in total.
+// edges inside it, and in total.  A vertex's mark is 1 + the highest bit in
+// which its component's id differs from a neighbour's: mark > j means that it
+// is on the boundary of the partition into runs of 2^j components too.
 __global__ void k_edges_scan(int64_t m, const int32_t* __restrict__ eu, const int32_t* __restrict__ ev,
                              const int32_t* __restrict__ w, int32_t n, const int32_t* __restrict__ part,
-                             int32_t k, uint8_t* __restrict__ flag, unsigned long long* __restrict__ sumc,
+                             int32_t k, u32* flag, unsigned long long* __restrict__ sumc,
                              unsigned long long* __restrict__ total, u32* __restrict__ err) {
   unsigned long long acc = 0;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < m;
@@ -48,8 +50,9 @@ __global__ void k_edges_scan(int64_t m, const int32_t* __restrict__ eu, const in
     int32_t pu = part[u], pv = part[v];
     if (pu < 0 || pu >= k || pv < 0 || pv >= k) continue;  // reported by k_count_part
     if (pu != pv) {
-      flag[u] = 1;
-      flag[v] = 1;
+      const u32 mark = 32 - (u32)__clz(pu ^ pv);
+      if (flag[u] < mark) atomicMax(flag + u, mark);
+      if (flag[v] < mark) atomicMax(flag + v, mark);
     } else if (u != v) {
       atomicAdd(&sumc[pu], (unsigned long long)x);
     }
@@ -60,23 +63,33 @@ __global__ void k_edges_scan(int64_t m, const int32_t* __restrict__ eu, const in
   if ((threadIdx.x & 63) == 0 && acc) atomicAdd(total, acc);
 }
 
-__global__ void k_count_boundary(int32_t n, const int32_t* __restrict__ part,
-                                 const uint8_t* __restrict__ flag, int32_t* __restrict__ nb) {
-  int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= n) return;
-  if (flag[v]) atomicAdd(&nb[part[v]], 1);
+// Boundary vertices per component, and how many carry each mark.
+__global__ __launch_bounds__(256) void k_count_boundary(int32_t n, const int32_t* __restrict__ part,
+                                                        const u32* __restrict__ flag,
+                                                        int32_t* __restrict__ nb, u32* __restrict__ marks) {
+  __shared__ u32 h[32];
+  if (threadIdx.x < 32) h[threadIdx.x] = 0;
+  __syncthreads();
+  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const u32 f = v < n ? flag[v] : 0;
+  if (f) {
+    atomicAdd(&nb[part[v]], 1);
+    atomicAdd(&h[f], 1u);
+  }
+  __syncthreads();
+  if (threadIdx.x < 32 && h[threadIdx.x]) atomicAdd(marks + threadIdx.x, h[threadIdx.x]);
 }
 
 // Groups the vertices by component (arbitrary order inside a component); the
 // boundary flag rides in bit 31.
-__global__ void k_members(int32_t n, const int32_t* __restrict__ part, const uint8_t* __restrict__ flag,
+__global__ void k_members(int32_t n, const int32_t* __restrict__ part, const u32* __restrict__ flag,
                           const int32_t* __restrict__ off, int32_t* __restrict__ fill,
                           u32* __restrict__ members) {
   int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (v >= n) return;
   int32_t c = part[v];
   int32_t slot = atomicAdd(&fill[c], 1);
-  members[off[c] + slot] = (u32)v | ((u32)flag[v] << 31);
+  members[off[c] + slot] = (u32)v | (flag[v] ? 0x80000000u : 0u);
 }
 
 // Renumbering (Section 4, Fig. 1): inside each component the boundary vertices
@@ -600,7 +613,7 @@ hipError_t launch_partition_scan(const PartArgs& a, hipStream_t s) {
     k_edges_scan<<<g, 256, 0, s>>>(a.m, a.eu, a.ev, a.w, a.n, a.part, a.k, a.flag, a.sumc, a.total,
                                    a.err);
   }
-  if (a.n > 0) k_count_boundary<<<blocks_for(a.n), 256, 0, s>>>(a.n, a.part, a.flag, a.nb);
+  if (a.n > 0) k_count_boundary<<<blocks_for(a.n), 256, 0, s>>>(a.n, a.part, a.flag, a.nb, a.marks);
   LAUNCH_CHECK();
 }
 

@@ -22,7 +22,8 @@ struct PartArgs {
   const int32_t *eu, *ev, *w, *part;
   int32_t* cnt;               // [k] vertices per component
   int32_t* nb;                // [k] boundary vertices per component
-  uint8_t* flag;              // [n] boundary flag
+  u32* flag;                  // [n] boundary mark (k_edges_scan), 0: no boundary vertex
+  u32* marks;                 // [32] vertices with each mark
   unsigned long long* sumc;   // [k] weight of the edges inside each component
   unsigned long long* total;  // [1] weight of all edges
   u32* err;                   // [1] ERR_* bits
