@@ -1167,7 +1167,7 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
   // ---- Phase 2: APSP(C) for every component
   spq::CompArgs ca{};
   ca.k = k; ca.m = m; ca.eu = eu; ca.ev = ev; ca.w = w; ca.comp = X->comp; ca.local = X->local;
-  ca.P = X->P; ca.moff = X->moff; ca.M = X->M;
+  ca.P = X->P; ca.moff = X->moff; ca.M = X->M; ca.elems = X->comp_elems;
   auto phase2 = [&](hipStream_t st) -> hipError_t {
     hipError_t e = spq::launch_components(ca, st);
     if (plain) {

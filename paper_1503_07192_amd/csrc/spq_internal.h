@@ -50,7 +50,7 @@ constexpr int VREC_WORDS = 12;
 
 struct CompArgs {
   int32_t k;
-  int64_t m;
+  int64_t m, elems;  // edges; elements of all matrices
   const int32_t *eu, *ev, *w, *comp, *local, *P;
   const int64_t* moff;
   u32* M;
