@@ -633,13 +633,71 @@ static spq_status build_share(spq_index* X, spq::HierArgs& ha, int64_t m, bool p
   return SPQ_OK;
 }
 
-// End of the run of consecutive big components of one padded size that starts
-// at c (closed as one batch; single: one at a time); c if c is not big.
-static int32_t big_run(const spq_index* X, int32_t c, bool single) {
-  if (X->h_cnt[c] <= spq::BIG_COMP) return c;
-  int32_t c2 = c + 1;
-  while (!single && c2 < X->k && c2 - c < 65535 && X->h_cnt[c2] > spq::BIG_COMP && X->h_P[c2] == X->h_P[c]) c2++;
-  return c2;
+// End of the run of big components of one padded side that starts at place i of
+// the closure's order (closed as one batch).
+static int32_t big_run(const spq_index* X, int32_t i) {
+  int32_t e = i + 1;
+  while (e < X->nbig && e - i < 65535 && X->h_P[X->h_order[e]] == X->h_P[X->h_order[i]]) e++;
+  return e;
+}
+
+// Which components are closed by the multi-workgroup rounds ("big": all of more
+// than BIG_COMP vertices, and of more than MID_COMP those of a padded size whose
+// batch is estimated faster than one workgroup each), every component's padded
+// side, the order of their closure (big ones first, by size) and the executed
+// relaxations.  One workgroup takes 1.2e-11 s per P^3 whatever else runs (1,024
+// vertices 12.7 ms, 640 3.3, 448 1.2, 256 0.28), four fit a CU, and all of them
+// together run at 20 Trelax/s; a batch takes about 0.35 ms per two tiles of its
+// side and 28 Trelax/s.  64 components of 1,024 vertices: 12.7 -> 2.2 ms, 4 of them
+// 12.3 -> 0.57, 121 of 625 3.3 -> 1.2, 128 of 781 on average 13.0 -> 3.7; 169 of 400
+// stay with one workgroup each (1.23 ms, as a batch 1.34).
+static void plan_components(spq_index* X, bool plain) {
+  const int32_t k = X->k;
+  struct Size {
+    double count = 0, cubes = 0, widest = 0;
+  };
+  std::map<int32_t, Size> sizes;  // by padded side in 128-tiles; cubes, widest: padded to 64
+  for (int32_t c = 0; c < k; c++)
+    if (X->h_cnt[c] > spq::MID_COMP) {
+      Size& z = sizes[(X->h_cnt[c] + 127) / 128];
+      const double p = (double)round_up(X->h_cnt[c], spq::COMP_TILE);
+      z.count++;
+      z.cubes += p * p * p;
+      z.widest = std::max(z.widest, p);
+    }
+  std::map<int32_t, bool> big;
+  for (const auto& z : sizes) {
+    const double p = z.first * 128.0, w = z.second.widest;
+    const double one = std::max(1.2e-11 * w * w * w, z.second.cubes / 2 / 20e12);
+    const double all = std::ceil(z.first / 2.0) * 3.5e-4 + z.second.count * p * p * p / 2 / 28e12;
+    big[z.first] = all < one;
+  }
+  std::vector<uint8_t> isbig(k, 0);
+  for (int32_t c = 0; c < k; c++) {
+    const int32_t n = X->h_cnt[c];
+    isbig[c] = n > spq::BIG_COMP || (n > spq::MID_COMP && big[(n + 127) / 128]);
+    X->h_P[c] = (int32_t)round_up(n, isbig[c] ? 128 : spq::COMP_TILE);
+  }
+  X->h_order.resize(k);
+  std::iota(X->h_order.begin(), X->h_order.end(), 0);
+  std::stable_sort(X->h_order.begin(), X->h_order.end(), [&](int32_t a, int32_t b) {
+    return isbig[a] != isbig[b] ? isbig[a] > isbig[b] : X->h_P[a] > X->h_P[b];
+  });
+  for (int32_t c = 0; c < k; c++) X->nbig += isbig[c];
+  for (int32_t i = 0; i < k;) {
+    const int32_t p = X->h_P[X->h_order[i]];
+    if (i < X->nbig) {
+      const int32_t e = plain ? i + 1 : big_run(X, i);
+      X->relax_comp_exec += (e - i) * spq::dense_fw_exec_relax(p / 128, 128, X->cpivot, nullptr, e - i);
+      i = e;
+    } else {
+      // one workgroup runs the blocked rounds on 64-tiles, i <= j interior tiles only
+      const int64_t nt = p / spq::COMP_TILE;
+      X->relax_comp_exec += (double)nt * 64.0 * 64.0 * 64.0 *
+                            (1.0 + (nt - 1) + (double)(nt - 1) * nt / 2.0);
+      i++;
+    }
+  }
 }
 
 // What the closures and the composition are estimated to take, in seconds
@@ -936,33 +994,15 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
   X->h_bgoff.assign(k + 1, 0);
   X->h_P.resize(k);
   X->h_moff.resize(k);
+  plan_components(X, plain);
   for (int32_t c = 0; c < k; c++) {
     X->h_off[c + 1] = X->h_off[c] + X->h_cnt[c];
     X->h_bgoff[c + 1] = X->h_bgoff[c] + X->h_nb[c];
-    // components above BIG_COMP vertices are closed by the multi-workgroup
-    // blocked rounds (128-tiles); the rest one workgroup each
-    const bool big = X->h_cnt[c] > spq::BIG_COMP;
-    X->h_P[c] = (int32_t)round_up(X->h_cnt[c], big ? 128 : spq::COMP_TILE);
     X->h_moff[c] = X->comp_elems;
     X->comp_elems += (int64_t)X->h_P[c] * X->h_P[c];
     X->max_comp = std::max(X->max_comp, X->h_cnt[c]);
     X->max_nb = std::max(X->max_nb, X->h_nb[c]);
     X->relax_comp += (double)X->h_cnt[c] * X->h_cnt[c] * X->h_cnt[c];
-    if (big) {
-      X->nbig++;
-    } else {
-      // one workgroup runs the blocked rounds on 64-tiles, i <= j interior tiles only
-      const int64_t ntc = X->h_P[c] / spq::COMP_TILE;
-      X->relax_comp_exec += (double)ntc * 64.0 * 64.0 * 64.0 *
-                            (1.0 + (ntc - 1) + (double)(ntc - 1) * ntc / 2.0);
-    }
-  }
-  // the big components, by the runs that are closed together (plain: one each)
-  for (int32_t c = 0; c < k;) {
-    const int32_t c2 = big_run(X, c, plain);
-    if (c2 > c)
-      X->relax_comp_exec += (c2 - c) * spq::dense_fw_exec_relax(X->h_P[c] / 128, 128, X->cpivot, nullptr, c2 - c);
-    c = std::max(c2, c + 1);
   }
   X->V = X->h_bgoff[k];
   X->relax_bg = (double)X->V * X->V * X->V;
@@ -1071,10 +1111,6 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
                                     "group_comps or group_bg"));
     X->relax_bg_exec = X->ngroups * spq::dense_fw_exec_relax(X->Vgp / 128, 128, X->cpivot, nullptr, X->ngroups);
   }
-  X->h_order.resize(k);
-  std::iota(X->h_order.begin(), X->h_order.end(), 0);
-  std::stable_sort(X->h_order.begin(), X->h_order.end(),
-                   [&](int32_t a, int32_t b) { return X->h_P[a] > X->h_P[b]; });
 
   // ---- index memory
   TRY(dalloc(&X->comp, n));
@@ -1178,17 +1214,11 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
                                  inner_kc, X->cpivot);
       }
     } else {
-      // runs of consecutive big components of one padded size lie back to
-      // back in M (offsets follow the ids): one batched closure per run
-      for (int32_t c = 0; c < k && e == hipSuccess;) {
-        const int32_t c2 = big_run(X, c, false), P = X->h_P[c];
-        if (c2 == c) {
-          c++;
-          continue;
-        }
-        e = spq::launch_dense_fw_batch(X->M + X->h_moff[c], P, 128, P / 128, c2 - c, (int64_t)P * P, st,
-                                       nullptr, inner_kc, X->cpivot);
-        c = c2;
+      for (int32_t i = 0; i < X->nbig && e == hipSuccess;) {
+        const int32_t i2 = big_run(X, i), P = X->h_P[X->h_order[i]];
+        e = spq::launch_dense_fw_list(X->M, P, 128, P / 128, i2 - i, X->order + i, X->moff, st, inner_kc,
+                                      X->cpivot);
+        i = i2;
       }
     }
     if (e != hipSuccess) return e;

@@ -27,13 +27,22 @@ namespace spq {
 // 128 for 128-tiles): the fixed cost of a tile (loading and storing C) is
 // spread over twice the relaxations, and there are half as many rounds.
 //
-// A batch of equally sized matrices (one-tile blocks only) is handled by
-// blockIdx.y: matrix y starts gstride elements after matrix y-1.
+// A batch of equally sized matrices is handled by blockIdx.y: matrix y starts
+// gstride elements after matrix y-1, or (components of one padded size) at
+// moff[order[y]].
+struct FwAt {
+  int64_t gstride;
+  const int32_t* order;
+  const int64_t* moff;
+};
+__device__ __forceinline__ u32* fw_at(u32* A, const FwAt& at) {
+  return A + (at.order ? at.moff[at.order[blockIdx.y]] : (int64_t)blockIdx.y * at.gstride);
+}
+
 template <int T>
-__global__ __launch_bounds__(256) void k_fw_diag64(u32* __restrict__ A, int64_t ld, int r,
-                                                   int64_t gstride) {
+__global__ __launch_bounds__(256) void k_fw_diag64(u32* __restrict__ A, int64_t ld, int r, FwAt at) {
   __shared__ __attribute__((aligned(16))) u32 rb[4 * T];
-  A += (int64_t)blockIdx.y * gstride;
+  A = fw_at(A, at);
   u32 t[T / 16][T / 16];
   u32* D = A + (int64_t)r * T * ld + (int64_t)r * T;
   tile_load<T>(t, D, ld);
@@ -46,11 +55,10 @@ __global__ __launch_bounds__(256) void k_fw_diag64(u32* __restrict__ A, int64_t 
 // LDS reads and the barrier.  Bound by one CU's VALU (768 cycles for each of the
 // 64 steps' relaxations).  A grid32-sized closure through it 0.87 -> 0.62 ms;
 // 256 threads of 8 x 8, one wave per SIMD, took 53 us a tile.
-__global__ __launch_bounds__(1024) void k_fw_diag128(u32* __restrict__ A, int64_t ld, int r,
-                                                     int64_t gstride) {
+__global__ __launch_bounds__(1024) void k_fw_diag128(u32* __restrict__ A, int64_t ld, int r, FwAt at) {
   constexpr int T = 128;
   __shared__ __attribute__((aligned(16))) u32 rb[4 * T];
-  u32* D = A + (int64_t)blockIdx.y * gstride + (int64_t)r * T * ld + (int64_t)r * T;
+  u32* D = fw_at(A, at) + (int64_t)r * T * ld + (int64_t)r * T;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   u32 c[4][4];
 #pragma unroll
@@ -93,19 +101,18 @@ __global__ __launch_bounds__(1024) void k_fw_diag128(u32* __restrict__ A, int64_
 }
 
 template <int T>
-static void fw_diag(u32* A, int64_t ld, int r, int batch, int64_t gstride, hipStream_t s) {
+static void fw_diag(u32* A, int64_t ld, int r, int batch, FwAt at, hipStream_t s) {
   if (T == 128)
-    k_fw_diag128<<<dim3(1, batch), 1024, 0, s>>>(A, ld, r, gstride);
+    k_fw_diag128<<<dim3(1, batch), 1024, 0, s>>>(A, ld, r, at);
   else
-    k_fw_diag64<64><<<dim3(1, batch), 256, 0, s>>>(A, ld, r, gstride);
+    k_fw_diag64<64><<<dim3(1, batch), 256, 0, s>>>(A, ld, r, at);
 }
 
 template <int T>
-__global__ __launch_bounds__(256) void k_fw_panel(u32* __restrict__ A, int64_t ld, int r,
-                                                  int64_t gstride) {
+__global__ __launch_bounds__(256) void k_fw_panel(u32* __restrict__ A, int64_t ld, int r, FwAt at) {
   __shared__ __attribute__((aligned(16))) u32 sD[T * T];
   __shared__ __attribute__((aligned(16))) u32 sB[T * T];
-  A += (int64_t)blockIdx.y * gstride;
+  A = fw_at(A, at);
   const int j = (int)blockIdx.x + ((int)blockIdx.x >= r);
   u32 t[T / 16][T / 16];
   tile_load<T>(t, A + (int64_t)r * T * ld + (int64_t)r * T, ld);
@@ -182,12 +189,12 @@ __device__ __forceinline__ void inner_tile(int part, int b, int c0, int nt, int 
 
 template <int T, int KC, int PT>
 __global__ __launch_bounds__(256) SPQ_INNER_ATTR void k_fw_inner(u32* __restrict__ A, int64_t ld, int c0, int nt,
-                                                                int64_t gstride, int part, int nn) {
+                                                                FwAt at, int part, int nn) {
   constexpr int Q = KC * T / 4 / 256;  // uint4 per thread per operand chunk
   static_assert(Q >= 1 && KC * T / 4 % 256 == 0, "chunk must split evenly");
   __shared__ __attribute__((aligned(16))) u32 sA[2][KC * T];
   __shared__ __attribute__((aligned(16))) u32 sB[2][KC * T];
-  A += (int64_t)blockIdx.y * gstride;
+  A = fw_at(A, at);
   int i, j;
   inner_tile<PT>(part, (int)blockIdx.x, c0, nt, nn, i, j);
   const u32* Ar = A + (int64_t)c0 * T * ld + (int64_t)i * T;  // block rows, tile column i
@@ -245,10 +252,10 @@ __global__ __launch_bounds__(256) SPQ_INNER_ATTR void k_fw_inner(u32* __restrict
 // 256-wide block closes in 8 launches of 8.7 us (70 us; the rounds over its two
 // 128-tiles took 258: two diagonal tiles of 52 us and four one-tile products of 39
 // us in a row).
-__global__ __launch_bounds__(256) void k_fw_square(u32* A, int64_t ld, int nb, int64_t gstride) {
+__global__ __launch_bounds__(256) void k_fw_square(u32* A, int64_t ld, int nb, FwAt at) {
   constexpr int KC = 16;
   __shared__ __attribute__((aligned(16))) u32 sm[4][2][2][KC * 32];
-  A += (int64_t)blockIdx.y * gstride;
+  A = fw_at(A, at);
   int bi, bj;
   tri_index((int)blockIdx.x, nb, bi, bj);
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -328,18 +335,18 @@ __global__ __launch_bounds__(256) void k_fw_square(u32* A, int64_t ld, int nb, i
 #endif
 
 template <int T, int KC>
-static hipError_t fw_rounds(u32* A, int64_t ld, int nt, int batch, int64_t gstride, hipStream_t s,
+static hipError_t fw_rounds(u32* A, int64_t ld, int nt, int batch, FwAt at, hipStream_t s,
                            hipEvent_t* ev) {
   for (int r = 0; r < nt; r++) {
-    fw_diag<T>(A, ld, r, batch, gstride, s);
+    fw_diag<T>(A, ld, r, batch, at, s);
     if (nt > 1) {
-      k_fw_panel<T><<<dim3(nt - 1, batch), 256, 0, s>>>(A, ld, r, gstride);
+      k_fw_panel<T><<<dim3(nt - 1, batch), 256, 0, s>>>(A, ld, r, at);
       if (ev) {
         hipError_t e = hipEventRecord(ev[2 * r], s);
         if (e != hipSuccess) return e;
       }
       k_fw_inner<T, KC, 1><<<dim3((unsigned)((nt - 1) * nt / 2), batch), 256, 0, s>>>(
-          A, ld, r, nt, gstride, 0, 1);
+          A, ld, r, nt, at, 0, 1);
       if (ev) {
         hipError_t e = hipEventRecord(ev[2 * r + 1], s);
         if (e != hipSuccess) return e;
@@ -379,10 +386,10 @@ static int64_t inner_count(int nt, FwBlock b, int part, int nn) {
   return tri_count(nt - b.pt - nn);
 }
 
-// `batch` equally sized matrices, gstride elements apart (blockIdx.y)
+// `batch` equally sized matrices (blockIdx.y)
 struct FwBatch {
   int batch;
-  int64_t gstride;
+  FwAt at;
 };
 
 template <int T, int KC>
@@ -409,7 +416,7 @@ static bool fw_by_squaring(int tile, int pt, int batch) {
 static void fw_square_all(u32* D, int64_t ld, int n, FwBatch bt, hipStream_t s) {
   for (int q = fw_squarings(n); q > 0; q--)
     k_fw_square<<<dim3((unsigned)tri_count(n / 32), (unsigned)bt.batch), 256, 0, s>>>(D, ld, n / 32,
-                                                                                     bt.gstride);
+                                                                                     bt.at);
 }
 
 // A whole matrix of up to 512 vertices is one block.
@@ -426,7 +433,7 @@ static bool fw_all_squaring(int tile, int nt, int pt, int batch) {
 template <int T, int KC>
 static hipError_t fw_close(u32* A, int64_t ld, FwBlock b, FwBatch bt, hipStream_t s) {
   if (b.pt == 1) {
-    fw_diag<T>(A, ld, b.c0, bt.batch, bt.gstride, s);
+    fw_diag<T>(A, ld, b.c0, bt.batch, bt.at, s);
     return hipGetLastError();
   }
   u32* D = A + (int64_t)b.c0 * T * ld + (int64_t)b.c0 * T;
@@ -447,13 +454,13 @@ static void inner_launch(u32* A, int64_t ld, int nt, FwBlock b, int part, int nn
                          FwBatch bt, hipStream_t s) {
   const dim3 grid((unsigned)count, (unsigned)bt.batch);
   if (b.pt == 1)
-    k_fw_inner<T, KC, 1><<<grid, 256, 0, s>>>(A, ld, b.c0, nt, bt.gstride, part, nn);
+    k_fw_inner<T, KC, 1><<<grid, 256, 0, s>>>(A, ld, b.c0, nt, bt.at, part, nn);
   else if (b.pt == 2)
-    k_fw_inner<T, KC, 2><<<grid, 256, 0, s>>>(A, ld, b.c0, nt, bt.gstride, part, nn);
+    k_fw_inner<T, KC, 2><<<grid, 256, 0, s>>>(A, ld, b.c0, nt, bt.at, part, nn);
   else if (b.pt == 4)
-    k_fw_inner<T, KC, 4><<<grid, 256, 0, s>>>(A, ld, b.c0, nt, bt.gstride, part, nn);
+    k_fw_inner<T, KC, 4><<<grid, 256, 0, s>>>(A, ld, b.c0, nt, bt.at, part, nn);
   else if constexpr (T == 64 && KC == 16)  // four 128-tiles, split
-    k_fw_inner<T, KC, 8><<<grid, 256, 0, s>>>(A, ld, b.c0, nt, bt.gstride, part, nn);
+    k_fw_inner<T, KC, 8><<<grid, 256, 0, s>>>(A, ld, b.c0, nt, bt.at, part, nn);
 }
 
 static int64_t part_count(int nt, FwBlock b, int part, int nn) {
@@ -592,26 +599,25 @@ static hipError_t dense_lookahead(u32* A, int64_t ld, int tile, int nt, FwBatch 
 hipError_t launch_dense_fw_lookahead(u32* A, int64_t ld, int tile, int nt, hipStream_t s,
                                      hipStream_t side, hipEvent_t* sync, hipEvent_t* ev, int kc,
                                      int pivot, hipStream_t p1) {
-  return dense_lookahead(A, ld, tile, nt, FwBatch{1, 0}, s, side, p1, sync, ev, kc, pivot);
+  return dense_lookahead(A, ld, tile, nt, FwBatch{1, FwAt{}}, s, side, p1, sync, ev, kc, pivot);
 }
 
 hipError_t launch_dense_fw_batch_lookahead(u32* A, int64_t ld, int tile, int nt, int batch,
                                            int64_t gstride, hipStream_t s, hipStream_t side,
                                            hipEvent_t* sync, hipEvent_t* ev, int kc, int pivot) {
-  return dense_lookahead(A, ld, tile, nt, FwBatch{batch, gstride}, s, side, nullptr, sync, ev, kc,
+  return dense_lookahead(A, ld, tile, nt, FwBatch{batch, FwAt{gstride, nullptr, nullptr}}, s, side, nullptr, sync, ev, kc,
                          pivot);
 }
 #undef CHK
 
 // kc: K chunk of the interior-tile kernel (16 or 32; 0 = SPQ_INNER_KC)
-hipError_t launch_dense_fw_batch(u32* A, int64_t ld, int tile, int nt, int batch, int64_t gstride,
-                                 hipStream_t s, hipEvent_t* ev, int kc, int pivot) {
-  if (nt <= 0 || batch <= 0) return hipSuccess;
+static hipError_t dense_rounds(u32* A, int64_t ld, int tile, int nt, FwBatch bt, hipStream_t s,
+                               hipEvent_t* ev, int kc, int pivot) {
+  if (nt <= 0 || bt.batch <= 0) return hipSuccess;
   if (kc == 0) kc = SPQ_INNER_KC;
   const int pt = pivot_tiles_of(tile, pivot);
   if (pt > 1) {
-    const FwBatch bt{batch, gstride};
-    if (!ev && fw_all_squaring(tile, nt, pt, batch)) {
+    if (!ev && fw_all_squaring(tile, nt, pt, bt.batch)) {
       fw_square_all(A, ld, nt * tile, bt, s);
       return hipGetLastError();
     }
@@ -622,10 +628,20 @@ hipError_t launch_dense_fw_batch(u32* A, int64_t ld, int tile, int nt, int batch
                     : fw_rounds_blocks<128, 16>(A, ld, nt, pt, bt, s, ev);
   }
   if (tile == 64)
-    return kc == 32 ? fw_rounds<64, 32>(A, ld, nt, batch, gstride, s, ev)
-                    : fw_rounds<64, 16>(A, ld, nt, batch, gstride, s, ev);
-  return kc == 32 ? fw_rounds<128, 32>(A, ld, nt, batch, gstride, s, ev)
-                  : fw_rounds<128, 16>(A, ld, nt, batch, gstride, s, ev);
+    return kc == 32 ? fw_rounds<64, 32>(A, ld, nt, bt.batch, bt.at, s, ev)
+                    : fw_rounds<64, 16>(A, ld, nt, bt.batch, bt.at, s, ev);
+  return kc == 32 ? fw_rounds<128, 32>(A, ld, nt, bt.batch, bt.at, s, ev)
+                  : fw_rounds<128, 16>(A, ld, nt, bt.batch, bt.at, s, ev);
+}
+
+hipError_t launch_dense_fw_batch(u32* A, int64_t ld, int tile, int nt, int batch, int64_t gstride,
+                                 hipStream_t s, hipEvent_t* ev, int kc, int pivot) {
+  return dense_rounds(A, ld, tile, nt, FwBatch{batch, FwAt{gstride, nullptr, nullptr}}, s, ev, kc, pivot);
+}
+
+hipError_t launch_dense_fw_list(u32* A, int64_t ld, int tile, int nt, int batch, const int32_t* order,
+                                const int64_t* moff, hipStream_t s, int kc, int pivot) {
+  return dense_rounds(A, ld, tile, nt, FwBatch{batch, FwAt{0, order, moff}}, s, nullptr, kc, pivot);
 }
 
 // Executed relaxations of a matrix closed in a batch of `batch`: per round the

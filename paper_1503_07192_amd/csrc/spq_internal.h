@@ -12,9 +12,10 @@ enum : u32 { ERR_PART = 1u, ERR_VERTEX = 2u, ERR_WEIGHT = 4u };
 
 // Component tables are padded to a multiple of this side.
 constexpr int COMP_TILE = 64;
-// Components with more vertices are closed by the multi-workgroup blocked
-// rounds (padded to 128) instead of one workgroup each.
-constexpr int BIG_COMP = 1024;
+// Components with more vertices are always closed by the multi-workgroup blocked
+// rounds (padded to 128, equal sizes in a batch) instead of one workgroup each;
+// above the second size where that is estimated faster (api.hip).
+constexpr int BIG_COMP = 1024, MID_COMP = 256;
 
 struct PartArgs {
   int32_t n, k;
@@ -280,6 +281,9 @@ hipError_t launch_dense_fw(u32* A, int64_t ld, int tile, int nt, hipStream_t s, 
 // `batch` matrices of the same shape, gstride elements apart
 hipError_t launch_dense_fw_batch(u32* A, int64_t ld, int tile, int nt, int batch, int64_t gstride,
                                  hipStream_t s, hipEvent_t* ev, int kc = 0, int pivot = 0);
+// `batch` matrices of the same shape at A + moff[order[i]] (device arrays)
+hipError_t launch_dense_fw_list(u32* A, int64_t ld, int tile, int nt, int batch, const int32_t* order,
+                                const int64_t* moff, hipStream_t s, int kc = 0, int pivot = 0);
 // Same closure with a lookahead over two streams (side: created by the caller,
 // default priority; sync: two events), or three with p1 (part 1 of every
 // round beside part 2; sync: three events).
