@@ -478,20 +478,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
 }
 
 // ------------------------------------------------------------------ paths --
-// One shortest path per half-wave, walked back from t to s on the graph's
+// One shortest path per wave, walked back from t to s on the graph's
 // adjacency: at vertex c (dist(s, c) = D), any neighbour u over an edge of
 // weight w with dist(s, u) + w = D lies on a shortest s-c path, so the walk
-// steps to it, preferring dist(s, u) < D; every dist(s, u) is an Algorithm 2
-// query on the index.  With positive weights dist falls at every step and the
-// walk reaches s.  A zero-weight edge allows a step at equal distance; such a
-// step avoids the last 8 vertices of the walk and its last 16 dead ends, and
-// a vertex with no step at all is a dead end the walk backs out of.  A walk
-// that backs out past t, or runs 4 max_len + 1,024 steps, is reported (-3).
-// Lane 0 writes the vertices (t first) and reverses them at the end, so the
-// path reads s .. t.
+// steps to it, preferring dist(s, u) < D.  With positive weights dist falls at
+// every step and the walk reaches s.  A zero-weight edge allows a step at equal
+// distance; such a step avoids the last 8 vertices of the walk and its last 16
+// dead ends, and a vertex with no step at all is a dead end the walk backs out
+// of.  A walk that backs out past t, or runs 4 max_len + 1,024 steps, is reported
+// (-3).  Lane 0 writes the vertices (t first); they are reversed at the end, so
+// the path reads s .. t.
 //   lens[i]: vertices on the path (>= 1), 0 no path, -1 bad pair (an id
 //   outside [0, n), or v1 outside a share), -2 the walk needed more than
 //   max_len vertices, -3 it found no way off a zero-weight plateau
+//
+// The walk is a chain of dependent loads, so a step is kept to two of them.
+// Eight neighbours at a time, eight lanes each: first the edge weight, the
+// record and the row pointers of every neighbour, then its row of APSP(C) and its
+// own neighbours, ready for the next step.  dist(s, u) is Algorithm 2 with its
+// first stage, t_X(b) = min over b1 of dist_Cs(s, b1) + dist_BG(b1, b), kept in
+// LDS for the last two components X the walk has met: the B(Cs) x B(X) block is
+// read once per component entered instead of once per neighbour.  500 paths of
+// 170 vertices on average (256 x 256 grid, 8 x 8 blocks): 4.1 ms with a half-wave
+// per path that queried each neighbour in turn, now 0.78 (20,000 paths: 10.7, now 4.1).
 __device__ __forceinline__ u32 hw_dist_to(int32_t s, int32_t u, int32_t n, const u32* vrec,
                                           const u32* M, const u32* H, int32_t share_comps, int l) {
   bool ok;
@@ -500,28 +509,94 @@ __device__ __forceinline__ u32 hw_dist_to(int32_t s, int32_t u, int32_t n, const
   return ok ? hw_pair_dist(rec, l, M, H, share_comps) : 0xffffffffu;
 }
 
-__global__ __launch_bounds__(256) void k_paths(
-    int64_t q, const int32_t* __restrict__ v1, const int32_t* __restrict__ v2, int32_t max_len,
-    int32_t n, const u32* __restrict__ vrec, const u32* __restrict__ M, const u32* __restrict__ H,
+constexpr int PATH_NB = 1024;  // |B(C)| up to which first-stage minima are kept in LDS
+
+__device__ __forceinline__ int64_t lane64(int64_t x, int lane) {
+  return (int64_t)(((uint64_t)(u32)__builtin_amdgcn_readlane((int)(x >> 32), lane) << 32) |
+                   (u32)__builtin_amdgcn_readlane((int)x, lane));
+}
+
+__global__ __launch_bounds__(64) void k_paths(
+    const int32_t* __restrict__ v1, const int32_t* __restrict__ v2, int32_t max_len, int32_t n,
+    const u32* __restrict__ vrec, const u32* __restrict__ M, const u32* __restrict__ H,
     int32_t share_comps, const int64_t* __restrict__ rowptr, const int2* __restrict__ adj,
-    const int32_t* __restrict__ wts, int32_t* __restrict__ paths, int32_t* __restrict__ lens) {
-  const int64_t qi = (int64_t)blockIdx.x * 8 + (threadIdx.x >> 5);
-  const int l = threadIdx.x & 31;
-  if (qi >= q) return;  // whole half-waves only
+    const int32_t* __restrict__ wts, int32_t* paths, int32_t* __restrict__ lens) {
+  __shared__ __attribute__((aligned(16))) u32 tb[2][PATH_NB + 32];
+  const int64_t qi = blockIdx.x;
+  const int l = threadIdx.x, sl = l >> 3, sj = l & 7;
   const int32_t s = v1[qi], t = v2[qi];
   int32_t* out = paths + qi * (int64_t)max_len;
   int32_t code = 0;
   u32 dcur = 0xffffffffu;
-  if (s >= 0 && s < n && t >= 0 && t < n) dcur = hw_dist_to(s, t, n, vrec, M, H, share_comps, l);
+  if (s >= 0 && s < n && t >= 0 && t < n) dcur = hw_dist_to(s, t, n, vrec, M, H, share_comps, l & 31);
   if (dcur == 0xffffffffu) code = -1;
   int32_t len = 0;
   if (code == 0 && dcur < INF) {
+    const uint4* rs = reinterpret_cast<const uint4*>(vrec + (int64_t)s * VREC_WORDS);
+    const uint4 s0 = rs[0], s1 = rs[1], s2 = rs[2];
+    const u32* row_s = M + ((uint64_t)s0.x | ((uint64_t)s0.y << 32));
+    const int32_t comp_s = (int32_t)s0.z, nb_s = (int32_t)s1.y;
+    int32_t cc[2] = {-1, -1};  // components whose minima tb[0], tb[1] hold
+    int last = 0;              // the one used last
+
+    // t_X into tb[buf], X the component of the vertex with records r1, r2
+    // (words 4-7, 8-11; uniform)
+    auto first_stage = [&](int buf, const uint4& r1, const uint4& r2) {
+      const int32_t nb = (int32_t)r1.y;
+      __syncthreads();  // the last reads of tb[buf]
+      // the store keeps group pairs S1 <= S2 (a share its own S1 against all)
+      const bool sw = share_comps == 0 && s1.z > r1.z;
+      if (!sw) {
+        const int64_t band = (int64_t)((uint64_t)s2.z | ((uint64_t)s2.w << 32));
+        const u32* blk = H + band + (int64_t)s2.x * ((int64_t)r1.x - (share_comps ? 0 : (int64_t)s1.x)) +
+                         (int64_t)s1.w * r2.x + (int64_t)nb_s * r1.w;
+        for (int32_t c0 = 0; c0 < nb; c0 += 64) {  // rows b1, a lane per column
+          const bool on = c0 + l < nb;
+          const u32* p = blk + min(c0 + l, nb - 1);
+          u32 m = INF;
+          int32_t r = 0;
+          for (; r + 8 <= nb_s; r += 8) {
+            u32 v[8];
+#pragma unroll
+            for (int i = 0; i < 8; i++) v[i] = p[(int64_t)(r + i) * nb];
+#pragma unroll
+            for (int i = 0; i < 8; i++) m = min(m, v[i] + row_s[r + i]);
+          }
+          for (; r < nb_s; r++) m = min(m, p[(int64_t)r * nb] + row_s[r]);
+          if (on) tb[buf][c0 + l] = m;
+        }
+      } else {
+        const int64_t band = (int64_t)((uint64_t)r2.z | ((uint64_t)r2.w << 32));
+        const u32* blk = H + band + (int64_t)r2.x * ((int64_t)s1.x - (int64_t)r1.x) + (int64_t)r1.w * s2.x +
+                         (int64_t)nb * s1.w;
+        for (int32_t c0 = 0; c0 < nb; c0 += 64) {  // columns b1, a lane per row
+          const bool on = c0 + l < nb;
+          const u32* p = blk + (int64_t)min(c0 + l, nb - 1) * nb_s;
+          u32 m = INF;
+          int32_t r = 0;
+          for (; r + 8 <= nb_s; r += 8) {
+            u32 v[8];
+#pragma unroll
+            for (int i = 0; i < 8; i++) v[i] = p[r + i];
+#pragma unroll
+            for (int i = 0; i < 8; i++) m = min(m, v[i] + row_s[r + i]);
+          }
+          for (; r < nb_s; r++) m = min(m, p[r] + row_s[r]);
+          if (on) tb[buf][c0 + l] = m;
+        }
+      }
+      if (l < 32) tb[buf][nb + l] = INF;
+      __syncthreads();
+    };
+
     // lanes 0-7: the vertices at path positions p (slot p mod 8) of the last
     // 8 pushed; lanes 0-15: the last 16 dead ends
     int32_t cur = t, recent = l == 0 ? t : -1, dead = -1, ndead = 0;
     if (l == 0) out[0] = t;
     len = 1;
     const int64_t iter_cap = 4 * (int64_t)max_len + 1024;
+    int64_t e0 = rowptr[cur], e1 = rowptr[cur + 1];
+    int2 a = sl < e1 - e0 ? adj[e0 + sl] : make_int2(-1, 0);  // my eight lanes' neighbour
     for (int64_t iter = 0; cur != s; iter++) {
       if (iter > iter_cap) {
         code = -3;
@@ -529,24 +604,100 @@ __global__ __launch_bounds__(256) void k_paths(
       }
       int32_t next = -1;
       u32 dnext = INF;
-      const int64_t e1 = rowptr[cur + 1];
-      for (int64_t e = rowptr[cur]; e < e1; e++) {
-        const int2 a = adj[e];
+      int from = -1;  // lane of the neighbour stepped to, its neighbours prefetched
+      int64_t rp0 = 0, rp1 = 0;
+      int2 pa = make_int2(-1, 0);
+      for (int64_t p0 = e0; p0 < e1; p0 += 8) {  // eight neighbours at a time
+        if (p0 > e0) a = p0 + sl < e1 ? adj[p0 + sl] : make_int2(-1, 0);
+        const bool in = a.x >= 0 && a.x != cur;
+        const int32_t u = in ? a.x : cur;
         const u32 w = (u32)wts[a.y];
-        if (w > dcur || a.x == cur) continue;
-        const u32 du = hw_dist_to(s, a.x, n, vrec, M, H, share_comps, l);
-        if (du >= INF || du + w != dcur) continue;
-        if (du < dcur) {
-          next = a.x;
-          dnext = du;
+        const uint4* rp = reinterpret_cast<const uint4*>(vrec + (int64_t)u * VREC_WORDS);
+        const uint4 r0 = rp[0], r1 = rp[1], r2 = rp[2];
+        rp0 = rowptr[u];
+        rp1 = rowptr[u + 1];
+        pa = rp0 + sj < rp1 ? adj[rp0 + sj] : make_int2(-1, 0);
+        u32 du = INF;
+        unsigned long long todo = __ballot(in && w <= dcur), strict = 0, level = 0;
+        while (todo) {
+          // the component of the next neighbours to look at: one whose minima are
+          // in LDS, else the first one's
+          unsigned long long mine = 0;
+          int buf = last;
+          mine = __ballot((int32_t)r0.z == cc[last]) & todo;
+          if (!mine) {
+            buf = last ^ 1;
+            mine = __ballot((int32_t)r0.z == cc[last ^ 1]) & todo;
+          }
+          if (!mine) {
+            const int f = __ffsll(todo) - 1;
+            const int32_t x = __builtin_amdgcn_readlane((int)r0.z, f);
+            const int32_t nb = __builtin_amdgcn_readlane((int)r1.y, f);
+            mine = __ballot((int32_t)r0.z == x) & todo;
+            if (nb <= PATH_NB) {
+              uint4 b1, b2;
+              b1.x = __builtin_amdgcn_readlane((int)r1.x, f); b1.y = nb;
+              b1.z = __builtin_amdgcn_readlane((int)r1.z, f); b1.w = __builtin_amdgcn_readlane((int)r1.w, f);
+              b2.x = __builtin_amdgcn_readlane((int)r2.x, f); b2.y = 0;
+              b2.z = __builtin_amdgcn_readlane((int)r2.z, f); b2.w = __builtin_amdgcn_readlane((int)r2.w, f);
+              buf = last ^ 1;
+              first_stage(buf, b1, b2);
+              cc[buf] = x;
+            } else {
+              buf = -1;
+            }
+          }
+          const bool me = mine >> l & 1;
+          if (buf >= 0) {
+            last = buf;
+            const u32* row = M + ((uint64_t)r0.x | ((uint64_t)r0.y << 32));
+            const int32_t nb = (int32_t)r1.y;
+            u32 best = INF;
+            if (me) {
+              for (int32_t b = sj * 4; b < nb; b += 32) {
+                const uint4 v = *reinterpret_cast<const uint4*>(row + b);
+                const uint4 x = *reinterpret_cast<const uint4*>(&tb[buf][b]);
+                best = min(min(best, min(v.x + x.x, v.y + x.y)), min(v.z + x.z, v.w + x.w));
+              }
+              if ((int32_t)r0.z == comp_s) best = min(best, row_s[r0.w]);
+            }
+            for (int o = 4; o > 0; o >>= 1) best = min(best, (u32)__shfl_xor((int)best, o));
+            if (me) du = min(best, INF);
+          } else {
+            // a component too wide for LDS: two neighbours at a time, one per half-wave
+            for (unsigned long long m = mine; m;) {
+              const int f = __ffsll(m) - 1;
+              m &= ~(0xffull << (f & ~7));
+              const int g = m ? __ffsll(m) - 1 : f;
+              m &= ~(0xffull << (g & ~7));
+              const int32_t x = __builtin_amdgcn_readlane(u, f), y = __builtin_amdgcn_readlane(u, g);
+              const u32 d = hw_dist_to(s, l < 32 ? x : y, n, vrec, M, H, share_comps, l & 31);
+              const u32 dx = __builtin_amdgcn_readlane((int)d, 0), dy = __builtin_amdgcn_readlane((int)d, 32);
+              if (sl == f >> 3) du = dx;
+              if (sl == g >> 3) du = dy;
+            }
+          }
+          strict |= __ballot(me && du < dcur && du + w == dcur);
+          level |= __ballot(me && du < INF && du == dcur && w == 0);
+          todo &= ~mine;
+          // of several the first in the adjacency's order: later ones need no look
+          if (strict) todo &= (1ull << (__ffsll(strict) - 1)) - 1;
+        }
+        if (strict) {
+          from = __ffsll(strict) - 1;
+          next = __builtin_amdgcn_readlane(u, from);
+          dnext = (u32)__builtin_amdgcn_readlane((int)du, from);
           break;
         }
-        if (next < 0) {  // a zero-weight step: not to a recent vertex or a dead end
-          const uint64_t seen = __ballot((l < 8 && recent == a.x) || (l < 16 && dead == a.x));
-          if (((seen >> (threadIdx.x & 32)) & 0xffffu) == 0) {
-            next = a.x;
-            dnext = du;
+        // a zero-weight step: not to a recent vertex or a dead end
+        for (unsigned long long m = level; m && next < 0;) {
+          const int f = __ffsll(m) - 1;
+          const int32_t x = __builtin_amdgcn_readlane(u, f);
+          if (!__ballot((l < 8 && recent == x) || (l < 16 && dead == x))) {
+            next = x;
+            dnext = dcur;
           }
+          m &= ~(0xffull << (f & ~7));
         }
       }
       if (next >= 0) {
@@ -559,6 +710,14 @@ __global__ __launch_bounds__(256) void k_paths(
         dcur = dnext;
         if (l == 0) out[len] = cur;
         len++;
+        if (from >= 0) {
+          e0 = lane64(rp0, from);
+          e1 = lane64(rp1, from);
+          const int src = (from & ~7) + sl;
+          a.x = __shfl(pa.x, src);
+          a.y = __shfl(pa.y, src);
+          continue;
+        }
       } else {
         // a dead end (only on zero-weight plateaus): mark it, step back
         if (l == (ndead & 15)) dead = cur;
@@ -569,23 +728,23 @@ __global__ __launch_bounds__(256) void k_paths(
         }
         int32_t prev = 0;
         if (l == 0) prev = out[len - 1];  // written by this lane
-        cur = __shfl(prev, 0, 32);
-        dcur = hw_dist_to(s, cur, n, vrec, M, H, share_comps, l);
+        cur = __builtin_amdgcn_readlane(prev, 0);
+        dcur = hw_dist_to(s, cur, n, vrec, M, H, share_comps, l & 31);
       }
+      e0 = rowptr[cur];
+      e1 = rowptr[cur + 1];
+      a = sl < e1 - e0 ? adj[e0 + sl] : make_int2(-1, 0);
     }
   }
-  if (l == 0) {
-    if (code == 0 && len > 0) {
-      for (int32_t i = 0, j = len - 1; i < j; i++, j--) {
-        const int32_t x = out[i];
-        out[i] = out[j];
-        out[j] = x;
-      }
-      lens[qi] = len;
-    } else {
-      lens[qi] = code;
+  if (code == 0 && len > 0) {
+    __threadfence();  // lane 0's stores, before the other lanes' loads
+    for (int32_t i = l; i < len - 1 - i; i += 64) {
+      const int32_t j = len - 1 - i, x = out[i];
+      out[i] = out[j];
+      out[j] = x;
     }
   }
+  if (l == 0) lens[qi] = code == 0 && len > 0 ? len : code;
 }
 
 // Adjacency of G for the path walk: both directions of every edge that is not
@@ -746,9 +905,11 @@ hipError_t launch_adjacency(int32_t n, int64_t m, const int32_t* eu, const int32
 hipError_t launch_paths(const QueryArgs& a, int32_t max_len, const int64_t* rowptr, const int2* adj,
                         const int32_t* wts, int32_t* paths, int32_t* lens, hipStream_t s) {
   if (a.q <= 0) return hipSuccess;
-  const int64_t blocks = (a.q + 7) / 8;  // 8 paths per workgroup
-  k_paths<<<(unsigned)blocks, 256, 0, s>>>(a.q, a.v1, a.v2, max_len, a.n, a.vrec, a.M, a.H,
-                                           a.share_comps, rowptr, adj, wts, paths, lens);
+  constexpr int64_t STEP = 1 << 24;  // 2^30 threads a launch
+  for (int64_t q0 = 0; q0 < a.q; q0 += STEP)
+    k_paths<<<(unsigned)std::min(a.q - q0, STEP), 64, 0, s>>>(a.v1 + q0, a.v2 + q0, max_len, a.n, a.vrec,
+                                                              a.M, a.H, a.share_comps, rowptr, adj, wts,
+                                                              paths + q0 * max_len, lens + q0);
   LAUNCH_CHECK();
 }
 
