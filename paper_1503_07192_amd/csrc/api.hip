@@ -232,6 +232,7 @@ struct spq_index {
   int32_t npairs = 0, chunk = 0;
   u32 *M3 = nullptr, *R3 = nullptr, *XT3 = nullptr, *BG3 = nullptr;
   spq::MpWork mp, mp3;                  // composition scratch, level 2 and 3
+  u32* fw_flags = nullptr;  // the dense closures' scratch flags
   unsigned long long* mp_exec = nullptr;  // executed relaxations of the products
   // share mode
   int32_t share_comps = 0, share_groups = 0, S2 = 0, bf_rounds = 0;
@@ -309,7 +310,7 @@ struct spq_index {
                     xe, xcount, boff, bsize, bfirst, gblk,
                     eu_own, ev_own, w_own, tbase, tsize, b3list, b3rank, m3, b3off, flag3,
                     M3, R3, XT3, BG3, plist, plist3, rowptr, adj, adeg, w_copy, meta,
-                    mp.stats, mp.mask, mp3.stats, mp3.mask, mp_exec};
+                    mp.stats, mp.mask, mp3.stats, mp3.mask, mp_exec, fw_flags};
     for (void* p : ptrs) pool_release(p);
   }
 };
@@ -944,6 +945,7 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
   TRY(dalloc(&X->sumc, k));
   TRY(dalloc(&X->total, 1 + 16));  // the total weight, then the marks' counts
   TRY(dalloc(&X->err, 1));
+  TRY(dalloc(&X->fw_flags, spq::FW_FLAGS));
   TRY(hipMemsetAsync(X->cnt, 0, sizeof(int32_t) * k, s));
   TRY(hipMemsetAsync(X->nb, 0, sizeof(int32_t) * k, s));
   TRY(hipMemsetAsync(X->flag, 0, sizeof(u32) * (size_t)n, s));
@@ -1211,13 +1213,13 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
       for (int32_t b = 0; b < X->nbig && e == hipSuccess; b++) {
         const int32_t c = X->h_order[b];
         e = spq::launch_dense_fw(X->M + X->h_moff[c], X->h_P[c], 128, X->h_P[c] / 128, st, nullptr,
-                                 inner_kc, X->cpivot);
+                                 inner_kc, X->cpivot, X->fw_flags);
       }
     } else {
       for (int32_t i = 0; i < X->nbig && e == hipSuccess;) {
         const int32_t i2 = big_run(X, i), P = X->h_P[X->h_order[i]];
         e = spq::launch_dense_fw_list(X->M, P, 128, P / 128, i2 - i, X->order + i, X->moff, st, inner_kc,
-                                      X->cpivot);
+                                      X->cpivot, X->fw_flags);
         i = i2;
       }
     }
@@ -1240,6 +1242,7 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
   // ---- Phase 3: BG and its all-pairs distances
   if (X->method == 2) {
     spq::HierArgs ha{};
+    ha.fw_flags = X->fw_flags;
     const int32_t G = X->ngroups, V = X->V, Vgp = X->Vgp;
     TRY(dalloc(&X->Mg, (int64_t)G * Vgp * Vgp));
     TRY(dalloc(&X->flag2, V));
@@ -1372,6 +1375,7 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
       // level-3 boundary flags depend on the edges only and are only ever set
       TRY(hipMemsetAsync(X->flag3, 0, X->V2, s));
       spq::L3Args la{};
+      la.fw_flags = X->fw_flags;
       la.nT = nT; la.gpt = X->gpt; la.V3gp = V3gp; la.kc = inner_kc; la.pivot = X->cpivot; la.m = m; la.V2p = X->V2p;
       la.eu = eu; la.ev = ev; la.w = w; la.comp = X->comp; la.local = X->local; la.bgoff = X->bgoff;
       la.grp = X->grp; la.b2off = X->b2off; la.b2rank = X->b2rank; la.BG2 = X->BG2;
@@ -1456,9 +1460,9 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
     if (e != hipSuccess) return e;
     if (la)
       e = spq::launch_dense_fw_lookahead(X->BG, X->Vp, tile, X->Vp / tile, st, X->side, X->la_sync,
-                                         pev, inner_kc, X->pivot, X->part1);
+                                         pev, inner_kc, X->pivot, X->part1, X->fw_flags);
     else
-      e = spq::launch_dense_fw(X->BG, X->Vp, tile, X->Vp / tile, st, pev, inner_kc, X->pivot);
+      e = spq::launch_dense_fw(X->BG, X->Vp, tile, X->Vp / tile, st, pev, inner_kc, X->pivot, X->fw_flags);
     if (e != hipSuccess) return e;
     return spq::launch_flat_store(V, X->Vp, X->BG, X->bgcomp, X->bgoff, X->nb, X->grp, X->gbg0,
                                   X->bgrow, X->bgnb, X->bggrp, X->bglocal, X->H, st);

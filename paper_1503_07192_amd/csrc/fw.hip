@@ -34,6 +34,7 @@ struct FwAt {
   int64_t gstride;
   const int32_t* order;
   const int64_t* moff;
+  u32* flags;  // FW_FLAGS words (any content), or null: see k_fw_square
 };
 __device__ __forceinline__ u32* fw_at(u32* A, const FwAt& at) {
   return A + (at.order ? at.moff[at.order[blockIdx.y]] : (int64_t)blockIdx.y * at.gstride);
@@ -252,9 +253,27 @@ __global__ __launch_bounds__(256) SPQ_INNER_ATTR void k_fw_inner(u32* __restrict
 // 256-wide block closes in 8 launches of 8.7 us (70 us; the rounds over its two
 // 128-tiles took 258: two diagonal tiles of 52 us and four one-tile products of 39
 // us in a row).
-__global__ __launch_bounds__(256) void k_fw_square(u32* A, int64_t ld, int nb, FwAt at) {
+//
+// q: which of the nq squarings.  Few hops inside a block suffice in most graphs
+// (blocks of closed cliques: 2 or 3 squarings of 8), and once a squaring of the
+// whole batch lowers nothing the block is closed: flags[q] is raised by one that
+// does, and the ones after the first that does not end at once.  Launch 0 clears
+// the flags from 1 on, launch 2 flag 0 (read by launch 1) for the next closure.
+// The next round's closure runs beside this round's interior and is the longer
+// of the two where matrices are small: its waves go first on a SIMD they share
+// (13 -> 9 us a launch).  Both: the closures of a 27,900-vertex BG in three levels
+// 1.5 of 14.0 ms less, a 400,000-vertex graph's 1.6 of 74.2.
+__global__ __launch_bounds__(256) void k_fw_square(u32* A, int64_t ld, int nb, FwAt at, int q, int nq) {
   constexpr int KC = 16;
   __shared__ __attribute__((aligned(16))) u32 sm[4][2][2][KC * 32];
+  if (at.flags) {
+    if (blockIdx.x == 0 && blockIdx.y == 0) {
+      if (q == 0 && threadIdx.x >= 1 && (int)threadIdx.x < nq) at.flags[threadIdx.x] = 0;
+      if (q == 2 && threadIdx.x == 0) at.flags[0] = 0;
+    }
+    if (q > 0 && at.flags[q - 1] == 0) return;
+  }
+  __builtin_amdgcn_s_setprio(3);
   A = fw_at(A, at);
   int bi, bj;
   tri_index((int)blockIdx.x, nb, bi, bj);
@@ -318,6 +337,7 @@ __global__ __launch_bounds__(256) void k_fw_square(u32* A, int64_t ld, int nb, F
     v.z = min(v.z, x.z);
     v.w = min(v.w, x.w);
   }
+  if (at.flags && (v.x != old.x || v.y != old.y || v.z != old.z || v.w != old.w)) at.flags[q] = 1;
   *reinterpret_cast<uint4*>(Cp) = v;
   if (bi == bj) return;
   u32* tr = red + 4096;  // [32][33]
@@ -414,9 +434,10 @@ static bool fw_by_squaring(int tile, int pt, int batch) {
 }
 
 static void fw_square_all(u32* D, int64_t ld, int n, FwBatch bt, hipStream_t s) {
-  for (int q = fw_squarings(n); q > 0; q--)
-    k_fw_square<<<dim3((unsigned)tri_count(n / 32), (unsigned)bt.batch), 256, 0, s>>>(D, ld, n / 32,
-                                                                                     bt.at);
+  const int nq = fw_squarings(n);
+  for (int q = 0; q < nq; q++)
+    k_fw_square<<<dim3((unsigned)tri_count(n / 32), (unsigned)bt.batch), 256, 0, s>>>(D, ld, n / 32, bt.at,
+                                                                                     q, nq);
 }
 
 // A whole matrix of up to 512 vertices is one block.
@@ -575,8 +596,8 @@ int fw_rounds_count(int nt, int tile, int pivot) {
 }
 
 hipError_t launch_dense_fw(u32* A, int64_t ld, int tile, int nt, hipStream_t s, hipEvent_t* ev,
-                           int kc, int pivot) {
-  return launch_dense_fw_batch(A, ld, tile, nt, 1, 0, s, ev, kc, pivot);
+                           int kc, int pivot, u32* flags) {
+  return launch_dense_fw_batch(A, ld, tile, nt, 1, 0, s, ev, kc, pivot, flags);
 }
 
 static hipError_t dense_lookahead(u32* A, int64_t ld, int tile, int nt, FwBatch bt, hipStream_t s,
@@ -598,15 +619,15 @@ static hipError_t dense_lookahead(u32* A, int64_t ld, int tile, int nt, FwBatch 
 
 hipError_t launch_dense_fw_lookahead(u32* A, int64_t ld, int tile, int nt, hipStream_t s,
                                      hipStream_t side, hipEvent_t* sync, hipEvent_t* ev, int kc,
-                                     int pivot, hipStream_t p1) {
-  return dense_lookahead(A, ld, tile, nt, FwBatch{1, FwAt{}}, s, side, p1, sync, ev, kc, pivot);
+                                     int pivot, hipStream_t p1, u32* flags) {
+  return dense_lookahead(A, ld, tile, nt, FwBatch{1, FwAt{0, nullptr, nullptr, flags}}, s, side, p1, sync, ev, kc, pivot);
 }
 
 hipError_t launch_dense_fw_batch_lookahead(u32* A, int64_t ld, int tile, int nt, int batch,
                                            int64_t gstride, hipStream_t s, hipStream_t side,
-                                           hipEvent_t* sync, hipEvent_t* ev, int kc, int pivot) {
-  return dense_lookahead(A, ld, tile, nt, FwBatch{batch, FwAt{gstride, nullptr, nullptr}}, s, side, nullptr, sync, ev, kc,
-                         pivot);
+                                           hipEvent_t* sync, hipEvent_t* ev, int kc, int pivot, u32* flags) {
+  return dense_lookahead(A, ld, tile, nt, FwBatch{batch, FwAt{gstride, nullptr, nullptr, flags}}, s, side,
+                         nullptr, sync, ev, kc, pivot);
 }
 #undef CHK
 
@@ -635,13 +656,14 @@ static hipError_t dense_rounds(u32* A, int64_t ld, int tile, int nt, FwBatch bt,
 }
 
 hipError_t launch_dense_fw_batch(u32* A, int64_t ld, int tile, int nt, int batch, int64_t gstride,
-                                 hipStream_t s, hipEvent_t* ev, int kc, int pivot) {
-  return dense_rounds(A, ld, tile, nt, FwBatch{batch, FwAt{gstride, nullptr, nullptr}}, s, ev, kc, pivot);
+                                 hipStream_t s, hipEvent_t* ev, int kc, int pivot, u32* flags) {
+  return dense_rounds(A, ld, tile, nt, FwBatch{batch, FwAt{gstride, nullptr, nullptr, flags}}, s, ev, kc,
+                      pivot);
 }
 
 hipError_t launch_dense_fw_list(u32* A, int64_t ld, int tile, int nt, int batch, const int32_t* order,
-                                const int64_t* moff, hipStream_t s, int kc, int pivot) {
-  return dense_rounds(A, ld, tile, nt, FwBatch{batch, FwAt{0, order, moff}}, s, nullptr, kc, pivot);
+                                const int64_t* moff, hipStream_t s, int kc, int pivot, u32* flags) {
+  return dense_rounds(A, ld, tile, nt, FwBatch{batch, FwAt{0, order, moff, flags}}, s, nullptr, kc, pivot);
 }
 
 // Executed relaxations of a matrix closed in a batch of `batch`: per round the

@@ -1471,9 +1471,9 @@ hipError_t launch_hier_level1(const HierArgs& a, hipStream_t s) {
   hipError_t e = (a.side && ntg > 1)
                      ? launch_dense_fw_batch_lookahead(a.Mg, a.Vgp, 128, ntg, a.ngroups,
                                                        (int64_t)a.Vgp * a.Vgp, s, a.side, a.sync,
-                                                       nullptr, a.kc, a.pivot)
+                                                       nullptr, a.kc, a.pivot, a.fw_flags)
                      : launch_dense_fw_batch(a.Mg, a.Vgp, 128, ntg, a.ngroups, (int64_t)a.Vgp * a.Vgp,
-                                             s, nullptr, a.kc, a.pivot);
+                                             s, nullptr, a.kc, a.pivot, a.fw_flags);
   if (e != hipSuccess) return e;
   k_b2_scan<<<(unsigned)a.ngroups, 256, 0, s>>>(a.gbg0, a.gV, a.flag2, a.Vgp, a.b2list, a.b2rank, a.m2);
   return hipGetLastError();
@@ -1501,8 +1501,9 @@ hipError_t launch_hier_level2_close(const HierArgs& a, hipStream_t s) {
   if (a.V2p <= 0) return hipSuccess;
   const int nt = (int)(a.V2p / 128);
   if (a.side && nt > 1)
-    return launch_dense_fw_lookahead(a.BG2, a.V2p, 128, nt, s, a.side, a.sync, nullptr, a.kc, a.pivot);
-  return launch_dense_fw(a.BG2, a.V2p, 128, nt, s, nullptr, a.kc, a.pivot);
+    return launch_dense_fw_lookahead(a.BG2, a.V2p, 128, nt, s, a.side, a.sync, nullptr, a.kc, a.pivot,
+                                     nullptr, a.fw_flags);
+  return launch_dense_fw(a.BG2, a.V2p, 128, nt, s, nullptr, a.kc, a.pivot, a.fw_flags);
 }
 
 // Buffers and launch shapes of the composition's kernels (Kp: rows per slot,
@@ -1595,9 +1596,9 @@ hipError_t launch_level3_a(const L3Args& a, hipStream_t s) {
   hipError_t e = (a.side && ntt > 1)
                      ? launch_dense_fw_batch_lookahead(a.M3, a.V3gp, 128, ntt, a.nT,
                                                        (int64_t)a.V3gp * a.V3gp, s, a.side, a.sync,
-                                                       nullptr, a.kc, a.pivot)
+                                                       nullptr, a.kc, a.pivot, a.fw_flags)
                      : launch_dense_fw_batch(a.M3, a.V3gp, 128, ntt, a.nT, (int64_t)a.V3gp * a.V3gp,
-                                             s, nullptr, a.kc, a.pivot);
+                                             s, nullptr, a.kc, a.pivot, a.fw_flags);
   if (e != hipSuccess) return e;
   if (a.m > 0)
     k_l3_edges<<<hblocks(a.m), 256, 0, s>>>(a.m, a.eu, a.ev, a.w, a.comp, a.local, a.bgoff, a.grp,
@@ -1620,8 +1621,8 @@ hipError_t launch_level3_b(const L3Args& a, hipStream_t s) {
     const int nt = (int)(a.V3p / 128);
     hipError_t e = (a.side && nt > 1)
                        ? launch_dense_fw_lookahead(a.BG3, a.V3p, 128, nt, s, a.side, a.sync, nullptr,
-                                                   a.kc, a.pivot)
-                       : launch_dense_fw(a.BG3, a.V3p, 128, nt, s, nullptr, a.kc, a.pivot);
+                                                   a.kc, a.pivot, nullptr, a.fw_flags)
+                       : launch_dense_fw(a.BG3, a.V3p, 128, nt, s, nullptr, a.kc, a.pivot, a.fw_flags);
     if (e != hipSuccess) return e;
   }
   return launch_level3_compose(a, s);
@@ -1668,7 +1669,8 @@ hipError_t launch_share_prepare(const HierArgs& a, const ShareBlocks& b, hipStre
       k_blk_edges<<<hblocks(a.m), 256, 0, s>>>(a.m, a.eu, a.ev, a.w, a.comp, a.local, a.bgoff, a.grp,
                                                b.gblk, b.bfirst, a.b2off, a.b2rank, b.bpmax, b.A);
     hipError_t e = launch_dense_fw_batch(b.A, b.bpmax, 128, b.bpmax / 128, b.nblk,
-                                         (int64_t)b.bpmax * b.bpmax, s, nullptr, a.kc, a.pivot);
+                                         (int64_t)b.bpmax * b.bpmax, s, nullptr, a.kc, a.pivot,
+                                         a.fw_flags);
     if (e != hipSuccess) return e;
   }
   k_dt_init<<<(unsigned)a.V2p, 256, 0, s>>>(a.V2, a.S2, a.S2p, b.nblk, b.boff, b.bpmax, b.A, a.DT);

@@ -126,6 +126,7 @@ struct HierArgs {
   int64_t d2tld = 0;               //   its leading dimension
   int32_t npairs, chunk;           //   their count, pairs per launch (XT slots)
   MpWork work;
+  u32* fw_flags = nullptr;         // launch_dense_fw's flags
   hipEvent_t* evt;                 // NULL, or 2 per composition launch (second product)
   // exactness certificate fused into the composition (NULL: off)
   const int32_t* bglabel;
@@ -222,6 +223,7 @@ struct L3Args {
   u32 *R3, *BG3;                       // nT x m3pmax x V3gp, V3p x V3p
   u32* XT3;                            // chunk x m3pmax x V3gp
   MpWork work;
+  u32* fw_flags = nullptr;         // launch_dense_fw's flags
   const int2* plist;                   // super-group pairs T1 <= T2
   int32_t npairs, chunk;               //   their count, pairs per launch
 };
@@ -275,25 +277,31 @@ hipError_t launch_comp_fw(int32_t count, const int32_t* order, const int32_t* P,
 hipError_t launch_bg_assembly(const BgArgs& a, hipStream_t s);
 // ev: NULL, or two events per round recorded around its interior-tile
 // launch(es); kc: K chunk of the interior-tile kernel, 16 or 32 (0 = default);
-// pivot: rows per pivot block, the tile (or 0) or twice the tile (see fw.hip)
+// pivot: rows per pivot block, the tile (or 0) or twice the tile (see fw.hip);
+// flags: FW_FLAGS device words of any content, not shared with a closure that may
+// run at the same time, with which squarings past the last useful one end at once
+constexpr int FW_FLAGS = 16;
 hipError_t launch_dense_fw(u32* A, int64_t ld, int tile, int nt, hipStream_t s, hipEvent_t* ev,
-                           int kc = 0, int pivot = 0);
+                           int kc = 0, int pivot = 0, u32* flags = nullptr);
 // `batch` matrices of the same shape, gstride elements apart
 hipError_t launch_dense_fw_batch(u32* A, int64_t ld, int tile, int nt, int batch, int64_t gstride,
-                                 hipStream_t s, hipEvent_t* ev, int kc = 0, int pivot = 0);
+                                 hipStream_t s, hipEvent_t* ev, int kc = 0, int pivot = 0,
+                                 u32* flags = nullptr);
 // `batch` matrices of the same shape at A + moff[order[i]] (device arrays)
 hipError_t launch_dense_fw_list(u32* A, int64_t ld, int tile, int nt, int batch, const int32_t* order,
-                                const int64_t* moff, hipStream_t s, int kc = 0, int pivot = 0);
+                                const int64_t* moff, hipStream_t s, int kc = 0, int pivot = 0,
+                                u32* flags = nullptr);
 // Same closure with a lookahead over two streams (side: created by the caller,
 // default priority; sync: two events), or three with p1 (part 1 of every
 // round beside part 2; sync: three events).
 hipError_t launch_dense_fw_lookahead(u32* A, int64_t ld, int tile, int nt, hipStream_t s,
                                      hipStream_t side, hipEvent_t* sync, hipEvent_t* ev, int kc,
-                                     int pivot = 0, hipStream_t p1 = nullptr);
+                                     int pivot = 0, hipStream_t p1 = nullptr, u32* flags = nullptr);
 // the lookahead closure of `batch` matrices, gstride elements apart
 hipError_t launch_dense_fw_batch_lookahead(u32* A, int64_t ld, int tile, int nt, int batch,
                                            int64_t gstride, hipStream_t s, hipStream_t side,
-                                           hipEvent_t* sync, hipEvent_t* ev, int kc, int pivot);
+                                           hipEvent_t* sync, hipEvent_t* ev, int kc, int pivot,
+                                           u32* flags = nullptr);
 // rounds of a single-matrix closure (pivot blocks)
 int fw_rounds_count(int nt, int tile, int pivot);
 // relaxations executed per matrix by launch_dense_fw and its batches (diagonal, panel and upper-triangle
