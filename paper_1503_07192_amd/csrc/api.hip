@@ -1355,7 +1355,7 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
     if (X->nT == 0) {
       TRY(graph_segment(X, s, [&](hipStream_t st) -> hipError_t {
         hipError_t e = spq::launch_mp_zero(X->mp, st);
-        if (e == hipSuccess) e = spq::launch_hier_level2_prep(ha, st);
+        if (e == hipSuccess) e = spq::launch_hier_level2_prep(ha, true, st);
         if (e == hipSuccess) e = spq::launch_hier_level2_close(ha, st);
         if (e == hipSuccess) e = spq::launch_hier_level2_compose(ha, st);
         return e;
@@ -1379,11 +1379,12 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
       la.nT = nT; la.gpt = X->gpt; la.V3gp = V3gp; la.kc = inner_kc; la.pivot = X->cpivot; la.m = m; la.V2p = X->V2p;
       la.eu = eu; la.ev = ev; la.w = w; la.comp = X->comp; la.local = X->local; la.bgoff = X->bgoff;
       la.grp = X->grp; la.b2off = X->b2off; la.b2rank = X->b2rank; la.BG2 = X->BG2;
+      la.ngroups = X->ngroups; la.Vgp = X->Vgp; la.Mg = X->Mg; la.b2list = X->b2list;
       la.tbase = X->tbase; la.tsize = X->tsize; la.M3 = X->M3; la.flag3 = X->flag3;
       la.b3list = X->b3list; la.b3rank = X->b3rank; la.m3 = X->m3;
       la.side = ha.side; la.sync = ha.sync;
       TRY(graph_segment(X, s, [&](hipStream_t st) -> hipError_t {
-        hipError_t e = spq::launch_hier_level2_prep(ha, st);
+        hipError_t e = spq::launch_hier_level2_prep(ha, false, st);
         if (e == hipSuccess) e = spq::launch_level3_a(la, st);
         return e;
       }));

@@ -145,42 +145,50 @@ __global__ void k_r_gather(int32_t Vgp, int32_t m2pmax, const int32_t* __restric
 }
 
 // BG2 matrix init: d_S between B2 vertices of one group, 0 on the diagonal,
-// INF elsewhere and on the padding.
-__global__ void k_bg2_init(int32_t V2, int64_t V2p, int32_t ngroups, const int32_t* __restrict__ b2off,
+// INF elsewhere and on the padding.  With super-groups (tbase, tsize: their first
+// BG2 ids and sizes) matrix blockIdx.y is BG2 on super-group blockIdx.y's vertices
+// alone: level 3 overwrites the rest of BG2, so nothing else of it is made first
+// (29,499 BG2 vertices in 16 super-groups: all of BG2, then its blocks gathered,
+// 0.81 ms; the blocks alone 0.09).
+__global__ void k_bg2_init(int32_t V2, int64_t ld, int32_t ngroups, const int32_t* __restrict__ b2off,
                            const int32_t* __restrict__ b2list, int32_t Vgp, const u32* __restrict__ Mg,
+                           const int32_t* __restrict__ tbase, const int32_t* __restrict__ tsize,
                            u32* __restrict__ BG2) {
-  const int64_t i = blockIdx.x;
-  u32* out = BG2 + i * V2p;
+  const int64_t p = blockIdx.x, base = tbase ? tbase[blockIdx.y] : 0, i = base + p;
+  u32* out = BG2 + (blockIdx.y * ld + p) * ld;
   int64_t lo = 0, hi = 0;
   const u32* prow = nullptr;
   const int32_t* list = nullptr;
-  if (i < V2) {
+  if (p < (tbase ? tsize[blockIdx.y] : V2)) {
     int32_t a = 0, b = ngroups - 1;  // group of B2 id i: largest s with b2off[s] <= i
     while (a < b) {
       const int32_t mid = (a + b + 1) >> 1;
       if (b2off[mid] <= i) a = mid; else b = mid - 1;
     }
-    lo = b2off[a];
-    hi = b2off[a + 1];
+    lo = b2off[a] - base;
+    hi = b2off[a + 1] - base;
     list = b2list + (int64_t)a * Vgp;
-    prow = Mg + ((int64_t)a * Vgp + list[i - lo]) * Vgp;
+    prow = Mg + ((int64_t)a * Vgp + list[p - lo]) * Vgp;
   }
-  for (int64_t q0 = (int64_t)threadIdx.x * 4; q0 < V2p; q0 += (int64_t)blockDim.x * 4) {
+  for (int64_t q0 = (int64_t)threadIdx.x * 4; q0 < ld; q0 += (int64_t)blockDim.x * 4) {
     u32 v[4];
 #pragma unroll
     for (int t = 0; t < 4; t++) {
       const int64_t q = q0 + t;
-      v[t] = (q == i) ? 0u : (q >= lo && q < hi) ? prow[list[q - lo]] : INF;
+      v[t] = (q == p) ? 0u : (q >= lo && q < hi) ? prow[list[q - lo]] : INF;
     }
     *reinterpret_cast<uint4*>(out + q0) = make_uint4(v[0], v[1], v[2], v[3]);
   }
 }
 
+// G edges between groups into BG2, or (tbase not null, super-groups of gpt
+// groups) those inside a super-group into its matrix.
 __global__ void k_bg2_edges(int64_t m, const int32_t* __restrict__ eu, const int32_t* __restrict__ ev,
                             const int32_t* __restrict__ w, const int32_t* __restrict__ comp,
                             const int32_t* __restrict__ local, const int32_t* __restrict__ bgoff,
                             const int32_t* __restrict__ grp, const int32_t* __restrict__ b2off,
-                            const int32_t* __restrict__ b2rank, int64_t V2p, u32* __restrict__ BG2) {
+                            const int32_t* __restrict__ b2rank, int64_t ld, int32_t gpt,
+                            const int32_t* __restrict__ tbase, u32* __restrict__ BG2) {
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < m;
        e += (int64_t)gridDim.x * blockDim.x) {
     const int32_t u = eu[e], v = ev[e];
@@ -188,10 +196,18 @@ __global__ void k_bg2_edges(int64_t m, const int32_t* __restrict__ eu, const int
     if (cu == cv) continue;
     const int32_t su = grp[cu], sv = grp[cv];
     if (su == sv) continue;
-    const int64_t a = b2off[su] + b2rank[bgoff[cu] + local[u]];
-    const int64_t b = b2off[sv] + b2rank[bgoff[cv] + local[v]];
-    atomicMin(BG2 + a * V2p + b, (u32)w[e]);
-    atomicMin(BG2 + b * V2p + a, (u32)w[e]);
+    u32* M = BG2;
+    int64_t base = 0;
+    if (tbase) {
+      const int32_t t = su / gpt;
+      if (sv / gpt != t) continue;
+      base = tbase[t];
+      M += t * ld * ld;
+    }
+    const int64_t a = b2off[su] + b2rank[bgoff[cu] + local[u]] - base;
+    const int64_t b = b2off[sv] + b2rank[bgoff[cv] + local[v]] - base;
+    atomicMin(M + a * ld + b, (u32)w[e]);
+    atomicMin(M + b * ld + a, (u32)w[e]);
   }
 }
 
@@ -226,47 +242,54 @@ __global__ void k_flat_store(int32_t V, int64_t Vp, const u32* __restrict__ BG,
 // ------------------------------------------------------- min-plus products --
 // c = min(c, min over k < cnt of At[rows[k]][i] + B[bmap[rows[k]]][j]): the K
 // rows are gathered through the list `rows` (rows k themselves when it is
-// null; cnt of them, streamed 16 at a time, rows past cnt read as INF without
-// touching memory), and B's rows once more through bmap when it is not null.
+// null; cnt of them), and B's rows once more through bmap.  Sixteen rows at a
+// time straight to LDS, double buffered; a lane has the row numbers of the chunk
+// after the one in flight in registers, so that a chunk waits for one load, not
+// for three in a row.  Rows past cnt repeat the last one and are not multiplied
+// beyond an even count.  127 VGPRs, four waves per SIMD (staged through
+// registers it took 131 and three): the last product of a 30,700-row share 5.0 -> 4.7
+// 4.7 ms, its 40 rounds' 7.5 -> 6.3.
 __device__ __forceinline__ void mp_stream128_rows(u32 (&c)[8][8], const u32* At, int64_t ldA,
                                                   const u32* B, int64_t ldB,
                                                   const int32_t* __restrict__ rows, int cnt,
-                                                  u32* sA, u32* sB,
-                                                  const int32_t* __restrict__ bmap = nullptr) {
+                                                  u32* sA, u32* sB, const int32_t* __restrict__ bmap) {
   constexpr int T = 128, KC = 16;
-  const int nch = (cnt + KC - 1) / KC;
-  if (nch <= 0) return;
-  const int e0 = threadIdx.x, e1 = threadIdx.x + 256;
-  const int r0 = e0 >> 5, c0 = (e0 & 31) * 4, r1 = e1 >> 5, c1 = (e1 & 31) * 4;
-  const uint4 inf4 = make_uint4(INF, INF, INF, INF);
-  auto lda = [&](int k, int col) -> uint4 {
-    if (k >= cnt) return inf4;
-    return *reinterpret_cast<const uint4*>(At + (int64_t)(rows ? rows[k] : k) * ldA + col);
+  if (cnt <= 0) return;
+  const int wv = (int)threadIdx.x >> 6, r0 = (int)threadIdx.x >> 5, col = ((int)threadIdx.x & 31) * 4;
+  int32_t ra[2], rb[2];  // this thread's rows of A and B, of the next chunk
+  auto index = [&](int k0) {
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+      const int k = min(k0 + h * 8 + r0, cnt - 1);
+      ra[h] = rows ? rows[k] : k;
+      rb[h] = bmap[ra[h]];
+    }
   };
-  auto ldb = [&](int k, int col) -> uint4 {
-    if (k >= cnt) return inf4;
-    const int32_t r = rows ? rows[k] : k;
-    return *reinterpret_cast<const uint4*>(B + (int64_t)(bmap ? bmap[r] : r) * ldB + col);
+  auto load = [&](int buf) {
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(At + ra[h] * ldA + col),
+                                       (__attribute__((address_space(3))) void*)(sA + buf * KC * T + (h * 256 + wv * 64) * 4),
+                                       16, 0, 0);
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(B + rb[h] * ldB + col),
+                                       (__attribute__((address_space(3))) void*)(sB + buf * KC * T + (h * 256 + wv * 64) * 4),
+                                       16, 0, 0);
+    }
   };
-  uint4 pa0 = lda(r0, c0), pa1 = lda(r1, c1);
-  uint4 pb0 = ldb(r0, c0), pb1 = ldb(r1, c1);
-  reinterpret_cast<uint4*>(sA)[e0] = pa0;
-  reinterpret_cast<uint4*>(sA)[e1] = pa1;
-  reinterpret_cast<uint4*>(sB)[e0] = pb0;
-  reinterpret_cast<uint4*>(sB)[e1] = pb1;
+  index(0);
+  load(0);
+  index(KC);
+  __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  for (int ch = 0; ch < nch; ch++) {
-    const int kn = (ch + 1 < nch ? ch + 1 : ch) * KC;
-    pa0 = lda(kn + r0, c0);
-    pa1 = lda(kn + r1, c1);
-    pb0 = ldb(kn + r0, c0);
-    pb1 = ldb(kn + r1, c1);
-    const int cur = (ch & 1) * KC * T, nxt = ((ch + 1) & 1) * KC * T;
-    minplus_lds<128>(c, sA + cur, sB + cur, KC);
-    reinterpret_cast<uint4*>(sA + nxt)[e0] = pa0;
-    reinterpret_cast<uint4*>(sA + nxt)[e1] = pa1;
-    reinterpret_cast<uint4*>(sB + nxt)[e0] = pb0;
-    reinterpret_cast<uint4*>(sB + nxt)[e1] = pb1;
+#pragma unroll 1
+  for (int k = 0; k < cnt; k += KC) {
+    const int cur = (k / KC) & 1;
+    if (k + KC < cnt) {
+      load(cur ^ 1);
+      index(k + 2 * KC);
+    }
+    minplus_lds<T>(c, sA + cur * KC * T, sB + cur * KC * T, min(KC, (cnt - k + 1) & ~1));
+    __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
   }
 }
@@ -1005,26 +1028,6 @@ __global__ void k_zero_u64(int n, unsigned long long* p) {
 // BG2 matrix for T1 <= T2: the block upper triangle the level-2 composition
 // reads (rows of a group S1, columns of a group S2 >= S1).
 
-// M3[T] (V3gp x V3gp): T's block of the unclosed BG2 matrix; 0 on the
-// padding's diagonal, INF elsewhere on the padding.
-__global__ void k_l3_gather(int64_t V2p, const u32* __restrict__ BG2, const int32_t* __restrict__ tbase,
-                            const int32_t* __restrict__ tsize, int32_t V3gp, u32* __restrict__ M3) {
-  const int t = blockIdx.y;
-  const int64_t p = blockIdx.x;
-  const int32_t nt = tsize[t];
-  u32* out = M3 + ((int64_t)t * V3gp + p) * V3gp;
-  const u32* src = BG2 + ((int64_t)tbase[t] + p) * V2p + tbase[t];
-  for (int64_t q0 = (int64_t)threadIdx.x * 4; q0 < V3gp; q0 += (int64_t)blockDim.x * 4) {
-    u32 v[4];
-#pragma unroll
-    for (int u = 0; u < 4; u++) {
-      const int64_t q = q0 + u;
-      v[u] = (p < nt && q < nt) ? src[q] : (q == p ? 0u : INF);
-    }
-    *reinterpret_cast<uint4*>(out + q0) = make_uint4(v[0], v[1], v[2], v[3]);
-  }
-}
-
 // G edges between super-groups (both ends are level-2 vertices).  BG3 ==
 // NULL: flags both ends as level-3 boundary vertices; otherwise enters the
 // edge into BG3 (ids b3off[T] + rank inside T).
@@ -1374,7 +1377,7 @@ __device__ __forceinline__ void tile_store_rows(const u32 (&c)[8][8], u32* g, in
 // step above for why the listed rows suffice and why in place is exact): rows
 // b3[ti*128 ..] x column tile tj of block s = min(DT, A3 (x) DT) over the
 // listed B3 rows (their indices in b3list).
-__global__ __launch_bounds__(256) void k_bf_intra3(int32_t bpmax, int32_t b3pmax, int64_t S2p,
+__global__ __launch_bounds__(256) SPQ_MP_ATTR void k_bf_intra3(int32_t bpmax, int32_t b3pmax, int64_t S2p,
                                                    const int32_t* __restrict__ m3,
                                                    const int32_t* __restrict__ boff,
                                                    const int32_t* __restrict__ b3list,
@@ -1406,7 +1409,7 @@ __global__ __launch_bounds__(256) void k_bf_intra3(int32_t bpmax, int32_t b3pmax
 
 // The rows outside B3, once the rounds have settled: rows nb3[ti*128 ..] x
 // column tile tj of block s = min(DT, Aout^T (x) DT[B3 rows]).
-__global__ __launch_bounds__(256) void k_bf_final(int32_t bpmax, int32_t b3pmax, int32_t n3pmax,
+__global__ __launch_bounds__(256) SPQ_MP_ATTR void k_bf_final(int32_t bpmax, int32_t b3pmax, int32_t n3pmax,
                                                   int64_t S2p, const int32_t* __restrict__ m3,
                                                   const int32_t* __restrict__ n3,
                                                   const int32_t* __restrict__ boff,
@@ -1485,14 +1488,14 @@ static void launch_r(const HierArgs& a, hipStream_t s) {
                                                                             a.Mg, a.R);
 }
 
-hipError_t launch_hier_level2_prep(const HierArgs& a, hipStream_t s) {
+hipError_t launch_hier_level2_prep(const HierArgs& a, bool bg2, hipStream_t s) {
   launch_r(a, s);
-  if (a.V2p > 0) {
+  if (bg2 && a.V2p > 0) {
     k_bg2_init<<<(unsigned)a.V2p, 256, 0, s>>>(a.V2, a.V2p, a.ngroups, a.b2off, a.b2list, a.Vgp, a.Mg,
-                                               a.BG2);
+                                               nullptr, nullptr, a.BG2);
     if (a.m > 0)
       k_bg2_edges<<<hblocks(a.m), 256, 0, s>>>(a.m, a.eu, a.ev, a.w, a.comp, a.local, a.bgoff, a.grp,
-                                               a.b2off, a.b2rank, a.V2p, a.BG2);
+                                               a.b2off, a.b2rank, a.V2p, 0, nullptr, a.BG2);
   }
   return hipGetLastError();
 }
@@ -1590,8 +1593,11 @@ hipError_t launch_flat_store(int32_t V, int64_t Vp, const u32* BG, const int32_t
 }
 
 hipError_t launch_level3_a(const L3Args& a, hipStream_t s) {
-  k_l3_gather<<<dim3((unsigned)a.V3gp, (unsigned)a.nT), 256, 0, s>>>(a.V2p, a.BG2, a.tbase, a.tsize,
-                                                                      a.V3gp, a.M3);
+  k_bg2_init<<<dim3((unsigned)a.V3gp, (unsigned)a.nT), 256, 0, s>>>(
+      0, a.V3gp, a.ngroups, a.b2off, a.b2list, a.Vgp, a.Mg, a.tbase, a.tsize, a.M3);
+  if (a.m > 0)
+    k_bg2_edges<<<hblocks(a.m), 256, 0, s>>>(a.m, a.eu, a.ev, a.w, a.comp, a.local, a.bgoff, a.grp, a.b2off,
+                                             a.b2rank, a.V3gp, a.gpt, a.tbase, a.M3);
   const int ntt = a.V3gp / 128;
   hipError_t e = (a.side && ntt > 1)
                      ? launch_dense_fw_batch_lookahead(a.M3, a.V3gp, 128, ntt, a.nT,
@@ -1613,7 +1619,7 @@ hipError_t launch_level3_b(const L3Args& a, hipStream_t s) {
                                                                          a.b3list, a.M3, a.R3);
   if (a.V3p > 0) {
     k_bg2_init<<<(unsigned)a.V3p, 256, 0, s>>>(a.V3, a.V3p, a.nT, a.b3off, a.b3list, a.V3gp, a.M3,
-                                               a.BG3);
+                                               nullptr, nullptr, a.BG3);
     if (a.m > 0)
       k_l3_edges<<<hblocks(a.m), 256, 0, s>>>(a.m, a.eu, a.ev, a.w, a.comp, a.local, a.bgoff, a.grp,
                                               a.gpt, a.b2off, a.b2rank, nullptr, a.b3off, a.b3rank,

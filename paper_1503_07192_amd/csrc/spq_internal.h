@@ -200,7 +200,7 @@ hipError_t launch_flat_store(int32_t V, int64_t Vp, const u32* BG, const int32_t
                              const int32_t* bglocal, u32* H, hipStream_t s);
 // level 2 in three steps: R_S and the unclosed BG2 matrix; its closure by
 // flat Floyd-Warshall (or by level 3 below); the composition into H
-hipError_t launch_hier_level2_prep(const HierArgs& a, hipStream_t s);
+hipError_t launch_hier_level2_prep(const HierArgs& a, bool bg2, hipStream_t s);
 hipError_t launch_hier_level2_close(const HierArgs& a, hipStream_t s);
 hipError_t launch_hier_level2_compose(const HierArgs& a, hipStream_t s);
 
@@ -214,7 +214,10 @@ struct L3Args {
   int64_t m, V2p, V3p;
   const int32_t *eu, *ev, *w, *comp, *local, *bgoff, *grp;
   const int32_t *b2off, *b2rank;       // level-2 ids
-  u32* BG2;                            // V2p x V2p, unclosed in, closed (upper block triangle) out
+  int32_t ngroups, Vgp;                // the groups' closures and boundary lists (level 1)
+  const u32* Mg;
+  const int32_t* b2list;
+  u32* BG2;                            // V2p x V2p: gets the closed upper block triangle
   const int32_t *tbase, *tsize;        // [nT]: first BG2 id, BG2 vertices of each super-group
   u32* M3;                             // nT x V3gp x V3gp
   uint8_t* flag3;                      // [V2]
