@@ -377,6 +377,13 @@ static double pair_relax(const spq_index* X, int32_t a1, int32_t a2) {
          mp_tiles(X->h_gV[a1]) * mp_tiles(X->h_gV[a2]) * (double)X->h_m2[a2];
 }
 
+// Executed relaxations of a batch of closures in P padded rows.
+static double batch_relax(int64_t P, int pivot, const std::vector<int32_t>& sizes) {
+  double r = 0;
+  for (int32_t v : sizes) r += spq::dense_fw_exec_relax(P / 128, 128, pivot, nullptr, (int)sizes.size(), v);
+  return r;
+}
+
 // Scratch of the composition for `chunk` pairs per launch.
 static hipError_t mp_work_alloc(spq_index* X, spq::MpWork* w, int32_t Kp, int32_t Vp, int32_t chunk) {
   hipError_t e = dalloc(&w->stats, chunk * spq::mp_stats_words(Kp, Vp));
@@ -456,7 +463,7 @@ static spq_status build_share(spq_index* X, spq::HierArgs& ha, int64_t m, bool p
   X->h_boff[NB] = X->V2;
   X->bpmax = (int32_t)std::max<int64_t>(128, round_up(bmax, 128));
   const int32_t BP = X->bpmax;
-  if (multi) X->relax_bg_exec += NB * spq::dense_fw_exec_relax(BP / 128, 128, X->cpivot, nullptr, NB);
+  if (multi) X->relax_bg_exec += batch_relax(BP, X->cpivot, X->h_bsize);
   HIP_TRY(hipMemcpyAsync(X->b2off, X->h_b2off.data(), sizeof(int32_t) * (G + 1), hipMemcpyHostToDevice, s));
   HIP_TRY(dalloc(&X->boff, NB + 1));
   HIP_TRY(dalloc(&X->bsize, NB));
@@ -1111,7 +1118,7 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
     if (X->Vgp > 32768)
       return guard(fail(SPQ_EINVAL, "a group holds more than 32,768 BG vertices: lower "
                                     "group_comps or group_bg"));
-    X->relax_bg_exec = X->ngroups * spq::dense_fw_exec_relax(X->Vgp / 128, 128, X->cpivot, nullptr, X->ngroups);
+    X->relax_bg_exec = batch_relax(X->Vgp, X->cpivot, X->h_gV);
   }
 
   // ---- index memory
@@ -1401,7 +1408,7 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
       X->V3p = round_up(X->V3, 128);
       X->m3pmax = (int32_t)std::max<int64_t>(128, round_up(m3max, 128));
       // executed relaxations of level 3's closures
-      X->relax_bg_exec += nT * spq::dense_fw_exec_relax(V3gp / 128, 128, X->cpivot, nullptr, nT);
+      X->relax_bg_exec += batch_relax(V3gp, X->cpivot, X->h_tsize);
       if (X->V3p > 0) X->relax_bg_exec += spq::dense_fw_exec_relax(X->V3p / 128, 128, X->cpivot);
       TRY(hipMemcpyAsync(X->b3off, X->h_b3off.data(), sizeof(int32_t) * (nT + 1),
                          hipMemcpyHostToDevice, s));

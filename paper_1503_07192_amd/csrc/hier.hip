@@ -246,8 +246,8 @@ __global__ void k_flat_store(int32_t V, int64_t Vp, const u32* __restrict__ BG,
 // time straight to LDS, double buffered; a lane has the row numbers of the chunk
 // after the one in flight in registers, so that a chunk waits for one load, not
 // for three in a row.  Rows past cnt repeat the last one and are not multiplied
-// beyond an even count.  127 VGPRs, four waves per SIMD (staged through
-// registers it took 131 and three): the last product of a 30,700-row share 5.0 -> 4.7
+// beyond an even count.  118 VGPRs, four waves per SIMD (staged through
+// registers it took 131 and three): the last product of a 30,700-row share 5.0 ->
 // 4.7 ms, its 40 rounds' 7.5 -> 6.3.
 __device__ __forceinline__ void mp_stream128_rows(u32 (&c)[8][8], const u32* At, int64_t ldA,
                                                   const u32* B, int64_t ldB,
@@ -1474,9 +1474,9 @@ hipError_t launch_hier_level1(const HierArgs& a, hipStream_t s) {
   hipError_t e = (a.side && ntg > 1)
                      ? launch_dense_fw_batch_lookahead(a.Mg, a.Vgp, 128, ntg, a.ngroups,
                                                        (int64_t)a.Vgp * a.Vgp, s, a.side, a.sync,
-                                                       nullptr, a.kc, a.pivot, a.fw_flags)
+                                                       nullptr, a.kc, a.pivot, a.fw_flags, a.gV)
                      : launch_dense_fw_batch(a.Mg, a.Vgp, 128, ntg, a.ngroups, (int64_t)a.Vgp * a.Vgp,
-                                             s, nullptr, a.kc, a.pivot, a.fw_flags);
+                                             s, nullptr, a.kc, a.pivot, a.fw_flags, a.gV);
   if (e != hipSuccess) return e;
   k_b2_scan<<<(unsigned)a.ngroups, 256, 0, s>>>(a.gbg0, a.gV, a.flag2, a.Vgp, a.b2list, a.b2rank, a.m2);
   return hipGetLastError();
@@ -1602,9 +1602,9 @@ hipError_t launch_level3_a(const L3Args& a, hipStream_t s) {
   hipError_t e = (a.side && ntt > 1)
                      ? launch_dense_fw_batch_lookahead(a.M3, a.V3gp, 128, ntt, a.nT,
                                                        (int64_t)a.V3gp * a.V3gp, s, a.side, a.sync,
-                                                       nullptr, a.kc, a.pivot, a.fw_flags)
+                                                       nullptr, a.kc, a.pivot, a.fw_flags, a.tsize)
                      : launch_dense_fw_batch(a.M3, a.V3gp, 128, ntt, a.nT, (int64_t)a.V3gp * a.V3gp,
-                                             s, nullptr, a.kc, a.pivot, a.fw_flags);
+                                             s, nullptr, a.kc, a.pivot, a.fw_flags, a.tsize);
   if (e != hipSuccess) return e;
   if (a.m > 0)
     k_l3_edges<<<hblocks(a.m), 256, 0, s>>>(a.m, a.eu, a.ev, a.w, a.comp, a.local, a.bgoff, a.grp,
@@ -1676,7 +1676,7 @@ hipError_t launch_share_prepare(const HierArgs& a, const ShareBlocks& b, hipStre
                                                b.gblk, b.bfirst, a.b2off, a.b2rank, b.bpmax, b.A);
     hipError_t e = launch_dense_fw_batch(b.A, b.bpmax, 128, b.bpmax / 128, b.nblk,
                                          (int64_t)b.bpmax * b.bpmax, s, nullptr, a.kc, a.pivot,
-                                         a.fw_flags);
+                                         a.fw_flags, b.bsize);
     if (e != hipSuccess) return e;
   }
   k_dt_init<<<(unsigned)a.V2p, 256, 0, s>>>(a.V2, a.S2, a.S2p, b.nblk, b.boff, b.bpmax, b.A, a.DT);

@@ -286,10 +286,11 @@ hipError_t launch_bg_assembly(const BgArgs& a, hipStream_t s);
 constexpr int FW_FLAGS = 16;
 hipError_t launch_dense_fw(u32* A, int64_t ld, int tile, int nt, hipStream_t s, hipEvent_t* ev,
                            int kc = 0, int pivot = 0, u32* flags = nullptr);
-// `batch` matrices of the same shape, gstride elements apart
+// `batch` matrices of the same shape, gstride elements apart; sizes: NULL, or [batch]
+// vertices of each, the rest being padding (0 on the diagonal, INF elsewhere)
 hipError_t launch_dense_fw_batch(u32* A, int64_t ld, int tile, int nt, int batch, int64_t gstride,
                                  hipStream_t s, hipEvent_t* ev, int kc = 0, int pivot = 0,
-                                 u32* flags = nullptr);
+                                 u32* flags = nullptr, const int32_t* sizes = nullptr);
 // `batch` matrices of the same shape at A + moff[order[i]] (device arrays)
 hipError_t launch_dense_fw_list(u32* A, int64_t ld, int tile, int nt, int batch, const int32_t* order,
                                 const int64_t* moff, hipStream_t s, int kc = 0, int pivot = 0,
@@ -304,12 +305,14 @@ hipError_t launch_dense_fw_lookahead(u32* A, int64_t ld, int tile, int nt, hipSt
 hipError_t launch_dense_fw_batch_lookahead(u32* A, int64_t ld, int tile, int nt, int batch,
                                            int64_t gstride, hipStream_t s, hipStream_t side,
                                            hipEvent_t* sync, hipEvent_t* ev, int kc, int pivot,
-                                           u32* flags = nullptr);
+                                           u32* flags = nullptr, const int32_t* sizes = nullptr);
 // rounds of a single-matrix closure (pivot blocks)
 int fw_rounds_count(int nt, int tile, int pivot);
-// relaxations executed per matrix by launch_dense_fw and its batches (diagonal, panel and upper-triangle
-// interior tiles of every round); *inner (optional) = the interior part
-double dense_fw_exec_relax(int64_t nt, int tile, int pivot = 0, double* inner = nullptr, int batch = 1);
+// relaxations executed by launch_dense_fw and its batches on one matrix of `batch`
+// (diagonal, panel and upper-triangle interior tiles of every round), of whose rows
+// only the first `size` are vertices (< 0: all); *inner (optional) = the interior part
+double dense_fw_exec_relax(int64_t nt, int tile, int pivot = 0, double* inner = nullptr, int batch = 1,
+                           int64_t size = -1);
 hipError_t launch_query(const QueryArgs& a, hipStream_t s);
 // VALU rate probes (probe.hip): kind 0 v_add_u32, 1 v_min3_u32, 2 the
 // relaxation loop on LDS operands; out: blocks * 256 words
