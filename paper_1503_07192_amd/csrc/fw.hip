@@ -159,11 +159,6 @@ __device__ __forceinline__ void tri_index(int b, int m, int& bi, int& bj) {
 // PT * T rows of the pivot block) is streamed through LDS in chunks of KC rows
 // of the two operand tiles (double buffered, next chunk prefetched into
 // registers while the current one is consumed).
-#ifdef SPQ_INNER_WPE
-#define SPQ_INNER_ATTR __attribute__((amdgpu_waves_per_eu(SPQ_INNER_WPE, SPQ_INNER_WPE)))
-#else
-#define SPQ_INNER_ATTR
-#endif
 //
 // The pivot block is tiles [c0, c0 + PT); nn = tiles of the next block
 // (parts 1 and 2).  part selects the tiles of the launch:
@@ -203,7 +198,7 @@ __device__ __forceinline__ void inner_tile(int part, int b, int c0, int nt, int 
 }
 
 template <int T, int KC, int PT>
-__global__ __launch_bounds__(256) SPQ_INNER_ATTR void k_fw_inner(u32* __restrict__ A, int64_t ld, int c0, int nt,
+__global__ __launch_bounds__(256, 4) void k_fw_inner(u32* __restrict__ A, int64_t ld, int c0, int nt,
                                                                 FwAt at, int part, int nn) {
   constexpr int Q = KC * T / 4 / 256;  // uint4 per thread per operand chunk
   static_assert(Q >= 1 && KC * T / 4 % 256 == 0, "chunk must split evenly");
@@ -231,16 +226,12 @@ __global__ __launch_bounds__(256) SPQ_INNER_ATTR void k_fw_inner(u32* __restrict
       const int e = threadIdx.x + s * 256;
       const int row = e / (T / 4), c4 = e % (T / 4);
       const int64_t off = (int64_t)(kc + row) * ld + c4 * 4;
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(Ar + off),
-                                       (__attribute__((address_space(3))) void*)(&sA[buf][(s * 256 + wv * 64) * 4]),
-                                       16, 0, 0);
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(Br + off),
-                                       (__attribute__((address_space(3))) void*)(&sB[buf][(s * 256 + wv * 64) * 4]),
-                                       16, 0, 0);
+      lds_load16(Ar + off, &sA[buf][(s * 256 + wv * 64) * 4]);
+      lds_load16(Br + off, &sB[buf][(s * 256 + wv * 64) * 4]);
     }
   };
   load_chunk(0, 0);
-  __builtin_amdgcn_s_waitcnt(0);
+  wait_loads();
   __syncthreads();
   // The chunk loop stays rolled (unrolled, the staged version needed 136
   // VGPRs and three waves per SIMD).
@@ -249,7 +240,7 @@ __global__ __launch_bounds__(256) SPQ_INNER_ATTR void k_fw_inner(u32* __restrict
   for (int ch = 0; ch < NCH; ch++) {
     if (ch + 1 < NCH) load_chunk((ch + 1) * KC, (ch + 1) & 1);
     minplus_lds<T>(t, sA[ch & 1], sB[ch & 1], KC);
-    __builtin_amdgcn_s_waitcnt(0);
+    wait_loads();
     __syncthreads();
   }
   tile_store<T>(t, Cij, ld);
@@ -301,10 +292,8 @@ __global__ __launch_bounds__(256) void k_fw_square(u32* A, int64_t ld, int nb, F
   auto load = [&](int k, int buf) {
 #pragma unroll
     for (int i = 0; i < KC / 8; i++) {
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(Ar + (int64_t)(k + i * 8) * ld),
-                                       (__attribute__((address_space(3))) void*)(&sm[w][buf][0][i * 256]), 16, 0, 0);
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(Br + (int64_t)(k + i * 8) * ld),
-                                       (__attribute__((address_space(3))) void*)(&sm[w][buf][1][i * 256]), 16, 0, 0);
+      lds_load16(Ar + (int64_t)(k + i * 8) * ld, &sm[w][buf][0][i * 256]);
+      lds_load16(Br + (int64_t)(k + i * 8) * ld, &sm[w][buf][1][i * 256]);
     }
   };
   // thread t keeps four entries of the tile for the end

@@ -268,18 +268,14 @@ __device__ __forceinline__ void mp_stream128_rows(u32 (&c)[8][8], const u32* At,
   auto load = [&](int buf) {
 #pragma unroll
     for (int h = 0; h < 2; h++) {
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(At + ra[h] * ldA + col),
-                                       (__attribute__((address_space(3))) void*)(sA + buf * KC * T + (h * 256 + wv * 64) * 4),
-                                       16, 0, 0);
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(B + rb[h] * ldB + col),
-                                       (__attribute__((address_space(3))) void*)(sB + buf * KC * T + (h * 256 + wv * 64) * 4),
-                                       16, 0, 0);
+      lds_load16(At + ra[h] * ldA + col, sA + buf * KC * T + (h * 256 + wv * 64) * 4);
+      lds_load16(B + rb[h] * ldB + col, sB + buf * KC * T + (h * 256 + wv * 64) * 4);
     }
   };
   index(0);
   load(0);
   index(KC);
-  __builtin_amdgcn_s_waitcnt(0);
+  wait_loads();
   __syncthreads();
 #pragma unroll 1
   for (int k = 0; k < cnt; k += KC) {
@@ -289,7 +285,7 @@ __device__ __forceinline__ void mp_stream128_rows(u32 (&c)[8][8], const u32* At,
       index(k + 2 * KC);
     }
     minplus_lds<T>(c, sA + cur * KC * T, sB + cur * KC * T, min(KC, (cnt - k + 1) & ~1));
-    __builtin_amdgcn_s_waitcnt(0);
+    wait_loads();
     __syncthreads();
   }
 }
@@ -306,14 +302,16 @@ __device__ __forceinline__ void fill_inf(u32 (&c)[8][8]) {
 }
 
 // The certificate's per-wave reduction: largest finite value, and whether
-// an INF joins two vertices connected in G.
-__device__ __forceinline__ void cert_reduce(u32 best, u32 wrong, u32* cert_bad, u32* cert_mbg) {
+// an INF joins two vertices connected in G.  seen: *cert_mbg as read before; a
+// wave that does not raise it leaves the word alone (one atomic per wave on it, 14 ns
+// each, was what bound the products of a 400,000-vertex graph: 23.7 -> 19.0 ms).
+__device__ __forceinline__ void cert_reduce(u32 best, u32 wrong, u32 seen, u32* cert_bad, u32* cert_mbg) {
   for (int o = 32; o > 0; o >>= 1) {
     best = max(best, (u32)__shfl_xor((int)best, o));
     wrong |= (u32)__shfl_xor((int)wrong, o);
   }
   if ((threadIdx.x & 63) == 0) {
-    if (best) atomicMax(cert_mbg, best);
+    if (best > seen) atomicMax(cert_mbg, best);
     if (wrong) atomicOr(cert_bad, 1u);
   }
 }
@@ -737,38 +735,46 @@ struct MpTerms {
   u32 uo, un, ul;  // row (block's x): rowoff, |B|, local index
 };
 
+// (Eight rows are read from LDS before the first is stored: one at a time each store
+// waited for its read: a 30,700-row share's build 53.0 -> 52.5 ms.)
 // Stores the staged half: staged row q (of n) is the block's row u0 + q, the
 // lane's column its column l (-1: none), so the 64 stores are consecutive inside
 // a component's run.  Query layout: element (x, y) at rowoff(x) |Y| + nb(x)
 // rowoff(y) + loc(x) nb(y) + loc(y) (bytes below 2^32): the rows of one
 // component follow each other nb(y) apart.  h: which half, row q's terms in
 // lane h*32 + q.  Mg (not null: S1 = S2): the group's closure is folded in.
-// CERT: best and worst get the largest finite value plus one and the largest.
+// CERT: worst gets the largest value.
 template <bool CERT>
 __device__ __forceinline__ void mp_store_half(const u32* s, const MpTerms& t, u32* base, int h, int32_t n,
-                                              int32_t l, u32 nY, const u32* Mg, int32_t Vp, u32& best,
-                                              u32& worst) {
+                                              int32_t l, u32 nY, const u32* Mg, int32_t Vp, u32& worst) {
   const int lane = threadIdx.x;
   if (l < 0) return;
-  const u32* sp = s + lane;
-  for (int q = 0; q < n;) {
-    const int r = h * 32 + q;
-    const u32 uo = (u32)__builtin_amdgcn_readlane((int)t.uo, r), un = (u32)__builtin_amdgcn_readlane((int)t.un, r),
-              ul = (u32)__builtin_amdgcn_readlane((int)t.ul, r);
-    char* row = reinterpret_cast<char*>(base) + (uint64_t)uo * nY * 4;
-    u32 off = __umul24(un, t.lo) + (__umul24(ul, t.ln) + t.ll);
-    const int e = min(n, q + (int)(un - ul));  // the component's rows end there
-#pragma unroll 4
-    for (; q < e; q++) {
-      u32 v = *sp;
-      sp += MP_ST;
-      if (Mg) v = min(v, Mg[(int64_t)q * Vp + l]);
-      *reinterpret_cast<u32*>(row + off) = v;
-      off += t.ln;
-      if (CERT) {
-        best = max(best, (v + 1) & INF);
-        worst = max(worst, v);
+  char* row = nullptr;
+  u32 off = 0;
+  int e = 0;  // where the component's rows end
+  for (int q0 = 0; q0 < n; q0 += 8) {
+    u32 v[8];
+#pragma unroll
+    for (int i = 0; i < 8; i++) v[i] = s[(q0 + i) * MP_ST + lane];
+    if (Mg) {
+#pragma unroll
+      for (int i = 0; i < 8; i++) v[i] = min(v[i], Mg[(int64_t)min(q0 + i, n - 1) * Vp + l]);
+    }
+#pragma unroll
+    for (int i = 0; i < 8; i++) {
+      const int q = q0 + i;
+      if (q >= n) break;
+      if (q == e) {
+        const int r = h * 32 + q;
+        const u32 uo = (u32)__builtin_amdgcn_readlane((int)t.uo, r), un = (u32)__builtin_amdgcn_readlane((int)t.un, r),
+                  ul = (u32)__builtin_amdgcn_readlane((int)t.ul, r);
+        row = reinterpret_cast<char*>(base) + (uint64_t)uo * nY * 4;
+        off = __umul24(un, t.lo) + (__umul24(ul, t.ln) + t.ll);
+        e = q + (int)(un - ul);
       }
+      *reinterpret_cast<u32*>(row + off) = v[i];
+      off += t.ln;
+      if (CERT) worst = max(worst, v[i]);
     }
   }
 }
@@ -777,13 +783,18 @@ __device__ __forceinline__ void mp_store_half(const u32* s, const MpTerms& t, u3
 __device__ __forceinline__ void mp_store_half_dense(const u32* s, u32* out, int64_t ldo, int32_t n,
                                                     int32_t l, const u32* Mg, int32_t Vp) {
   const int lane = threadIdx.x;
-#pragma unroll 4
-  for (int q = 0; q < n; q++) {
-    u32 v = s[q * MP_ST + lane];
-    if (l >= 0) {
-      if (Mg) v = min(v, Mg[(int64_t)q * Vp + l]);
-      out[q * ldo + l] = v;
+  if (l < 0) return;
+  for (int q0 = 0; q0 < n; q0 += 8) {
+    u32 v[8];
+#pragma unroll
+    for (int i = 0; i < 8; i++) v[i] = s[(q0 + i) * MP_ST + lane];
+    if (Mg) {
+#pragma unroll
+      for (int i = 0; i < 8; i++) v[i] = min(v[i], Mg[(int64_t)min(q0 + i, n - 1) * Vp + l]);
     }
+#pragma unroll
+    for (int i = 0; i < 8; i++)
+      if (q0 + i < n) out[(q0 + i) * ldo + l] = v[i];
   }
 }
 
@@ -870,18 +881,15 @@ __global__ __launch_bounds__(64) SPQ_MP_ATTR void k_mp_prod(MpArgs a) {
       u32* d = s + (st % MP_RING) * MP_KC * 2 * MP_T;
       const u32 k = (u32)kw + kl[st * MP_KC + (lane >> 4)];
       const u32* bp = B + (uint64_t)k * (u32)a.Vp + (lane & 15) * 4;
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)bp,
-                                       (__attribute__((address_space(3))) void*)(d + MP_KC * MP_T), 16, 0, 0);
+      lds_load16(bp, d + MP_KC * MP_T);
       if (SIDE) {
         const u32* ap = A + (uint64_t)k * (u32)a.Vp + (lane & 15) * 4;
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)ap,
-                                         (__attribute__((address_space(3))) void*)d, 16, 0, 0);
+        lds_load16(ap, d);
       } else {
 #pragma unroll
         for (int i = 0; i < MP_KC; i++) {
           const int32_t ki = __builtin_amdgcn_readlane((int)k, i * 16);
-          __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(A + (int64_t)ki * m.lda + acol),
-                                           (__attribute__((address_space(3))) void*)(d + i * MP_T), 4, 0, 0);
+          lds_load4(A + (int64_t)ki * m.lda + acol, d + i * MP_T);
         }
       }
     };
@@ -926,6 +934,7 @@ __global__ __launch_bounds__(64) SPQ_MP_ATTR void k_mp_prod(MpArgs a) {
             }
           }
         }
+        wait_loads();  // else the compiler waits for them in every step of the loop below
       }
     }
     for (int32_t w0 = 0;;) {
@@ -961,22 +970,23 @@ __global__ __launch_bounds__(64) SPQ_MP_ATTR void k_mp_prod(MpArgs a) {
   }
   __builtin_amdgcn_wave_barrier();
   if (SIDE == 0) {
-    // XT rows b: 64 consecutive x per store (those past the group are unused)
+    // XT rows b: 64 consecutive x per store (those past the group, and rows past
+    // its boundary, are unused)
     u32* xt = a.XT + ((int64_t)slot * a.Kp + x0) * a.Vp + p0;
 #pragma unroll
     for (int h = 0; h < 2; h++) {
       mp_stage<true>(c, s, h, ly, lx);
       __builtin_amdgcn_wave_barrier();
-      const int32_t n = min(m.rows - x0 - h * 32, 32);
-#pragma unroll 4
-      for (int q = 0; q < n; q++) xt[(int64_t)(h * 32 + q) * a.Vp + lane] = s[q * MP_ST + lane];
+#pragma unroll 8
+      for (int q = 0; q < 32; q++) xt[(int64_t)(h * 32 + q) * a.Vp + lane] = s[q * MP_ST + lane];
       __builtin_amdgcn_wave_barrier();
     }
     return;
   }
   const u32* Mg = s1 == s2 ? cs.Mg + ((int64_t)s1 * a.Vp + u0) * a.Vp : nullptr;
   const int32_t l = l0 + lane < llim ? l0 + lane : -1;
-  u32 best = 0, worst = 0;
+  u32 worst = 0, seen = 0;
+  if (CERT) seen = __hip_atomic_load(cs.cert_mbg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
   for (int h = 0; h < 2; h++) {
     const int32_t n = min(ulim - u0 - h * 32, 32);
@@ -990,24 +1000,28 @@ __global__ __launch_bounds__(64) SPQ_MP_ATTR void k_mp_prod(MpArgs a) {
     if (cs.dense)
       mp_store_half_dense(s, cs.dense + (int64_t)(gu + u0 + h * 32) * cs.ldo + gl, cs.ldo, n, l, Mh, a.Vp);
     else
-      mp_store_half<CERT>(s, t, base, h, n, l, (u32)llim, Mh, a.Vp, best, worst);
+      mp_store_half<CERT>(s, t, base, h, n, l, (u32)llim, Mh, a.Vp, worst);
     __builtin_amdgcn_wave_barrier();
   }
   if (CERT) {
-    // an INF somewhere: does it join vertices connected in G?  The stored
-    // entries again (this lane wrote them)
-    u32 wrong = 0;
+    // an INF somewhere (rare): the largest finite value, and whether an INF joins
+    // vertices connected in G, from the stored entries (this lane wrote them)
+    u32 wrong = 0, best = worst;
     if (worst >= INF) {
+      best = 0;
       const int32_t lab = cs.bglabel[gl + l];
       for (int32_t x = u0; x < min(ulim, u0 + MP_T); x++) {
         const int4 um = cs.meta[gu + x];
         const u32 off = __umul24((u32)um.y, t.lo) + (__umul24((u32)um.z, t.ln) + t.ll);
         const u32 v = *reinterpret_cast<const u32*>(reinterpret_cast<const char*>(base) +
                                                     (uint64_t)(u32)um.x * (u32)llim * 4 + off);
-        wrong |= (u32)(v >= INF && cs.bglabel[gu + x] == lab);
+        if (v < INF)
+          best = max(best, v);
+        else
+          wrong |= (u32)(cs.bglabel[gu + x] == lab);
       }
     }
-    cert_reduce(best ? best - 1 : 0, wrong, cs.cert_bad, cs.cert_mbg);
+    cert_reduce(best, wrong, seen, cs.cert_bad, cs.cert_mbg);
   }
 }
 
