@@ -377,6 +377,8 @@ template <int SIDE>
 constexpr int MP_SR = SIDE ? 128 : 64;
 template <int SIDE>
 constexpr int MP_RG = SIDE ? 8 : 4;
+template <int SIDE>
+constexpr int MP_KU = 32 / MP_RG<SIDE>;  // k per step of k_mp_keep
 constexpr int MP_T = 64;           // rows and columns of a product tile (one wave)
 constexpr int MP_KC = 4;           // k per LDS step of a product
 constexpr int MP_RING = 4;         // steps in LDS
@@ -443,9 +445,10 @@ __device__ __forceinline__ MpSide mp_side(int side, const MpArgs& a, int32_t slo
   return m;
 }
 
-// mn, mx of every k for the row tile of blockIdx.x (pair blockIdx.y), as
-// stats[((slot * Kp + k) * 2) * NT + tile] and NT further on.  r(x) = the minimum over up to 16
-// of the K rows, spread evenly.  Sixteen-byte loads, MP_SR / 4 lanes per k:
+// mn, mx of every k for the row tile of blockIdx.x (pair blockIdx.y), laid out as
+// k_mp_keep reads them (one wave's MP_RG row tiles and MP_KU k in a row; k from K on
+// to a whole MP_KU bound nothing).  r(x) = the minimum over up to 16 of the K rows,
+// spread evenly.  Sixteen-byte loads, MP_SR / 4 lanes per k:
 // bound by reading A once (plus the sampled rows).  Rows that are INF for every
 // k (unreachable) are left out; a tile without any other row keeps each
 // column's arg only.  Where a row is INF in the sample only, the tile's
@@ -458,11 +461,14 @@ __global__ __launch_bounds__(256) void k_mp_stats(MpArgs a) {
   __shared__ int odd, live;
   const int32_t slot = blockIdx.y, tile = blockIdx.x;
   const MpSide m = mp_side(SIDE, a, slot);
-  int32_t* out = a.stats + (int64_t)slot * a.Kp * 2 * a.NT + tile;
+  constexpr int RG = MP_RG<SIDE>, KU = MP_KU<SIDE>;
+  int32_t* out = a.stats + ((int64_t)slot * a.NT + tile / RG * RG) * 2 * a.Kp + tile % RG;
   auto put = [&](int32_t k, int32_t mn, int32_t mx) {
-    out[(int64_t)k * 2 * a.NT] = mn;
-    out[(int64_t)(k * 2 + 1) * a.NT] = mx;
+    out[(int64_t)k * RG] = mn;
+    out[((int64_t)a.Kp + k) * RG] = mx;
   };
+  const int32_t Kr = (m.K + KU - 1) / KU * KU;
+  if ((int32_t)threadIdx.x < Kr - m.K) put(m.K + threadIdx.x, MP_BIG, MP_BIG);
   const int32_t x0 = tile * SR, nx = min(m.rows - x0, SR);
   if (nx <= 0) {  // k_mp_keep reads whole groups of row tiles
     for (int32_t k = threadIdx.x; k < m.K; k += 256) put(k, MP_BIG, 0);
@@ -567,7 +573,6 @@ __global__ __launch_bounds__(256) void k_mp_keep(MpArgs a) {
   if (p >= m.W || t0 * SR >= m.rows) return;  // (no barrier below: waves are on their own)
   const u32* B = a.R + (int64_t)m.g * a.Kp * a.Vp + min(p + lane, m.W - 1);
   const int64_t ldb = a.Vp;
-  const cptr32 st = (cptr32)(a.stats + (int64_t)slot * a.Kp * 2 * a.NT + t0);
   const int32_t K = m.K;
   int32_t U[RG], arg[RG];
 #pragma unroll
@@ -576,22 +581,44 @@ __global__ __launch_bounds__(256) void k_mp_keep(MpArgs a) {
     arg[r] = -1;
   }
   u32 bmin = INF;
-  constexpr int KU = 32 / RG;  // k per step (a step past K repeats the last k)
-  for (int32_t k0 = 0; k0 < K; k0 += KU) {
+  constexpr int KU = MP_KU<SIDE>;
+  const int32_t Kr = (K + KU - 1) / KU * KU;
+  // a step's B entries (rows past K are there: Kp is a multiple of 128) and statistics
+  // (side: 0 the lower, 1 the upper ones); the next step's are on their way while one
+  // is worked on
+  struct Step {
     u32 b[KU];
+    int32_t m[KU * RG];
+  };
+  const int32_t* stats = a.stats + ((int64_t)slot * a.NT + t0) * 2 * a.Kp;
+  auto fetch = [&](Step& t, int32_t k0, int side) {
+    k0 = max(min(k0, Kr - KU), 0);
+    const u32* bp = B + (int64_t)k0 * ldb;
+    const cptr32 m = (cptr32)(stats + ((int64_t)side * a.Kp + k0) * RG);
 #pragma unroll
-    for (int q = 0; q < KU; q++) b[q] = B[(int64_t)min(k0 + q, K - 1) * ldb];
+    for (int q = 0; q < KU; q++, bp += ldb) t.b[q] = *bp;
+#pragma unroll
+    for (int i = 0; i < KU * RG; i++) t.m[i] = m[i];
+  };
+  Step cur, nxt;
+  fetch(nxt, 0, 1);
+#pragma unroll 1
+  for (int32_t k0 = 0; k0 < K; k0 += KU) {
+    cur = nxt;
+    fetch(nxt, k0 + KU, 1);
 #pragma unroll
     for (int q = 0; q < KU; q++) {
-      const int32_t k = min(k0 + q, K - 1);
-      const cptr32 mx = st + (int64_t)(k * 2 + 1) * a.NT;
-      bmin = min(bmin, b[q]);
-      const int32_t bu = (int32_t)min(b[q], (u32)MP_BIG);
+      bmin = min(bmin, cur.b[q]);
+      const int32_t bu = (int32_t)min(cur.b[q], (u32)MP_BIG);
 #pragma unroll
       for (int r = 0; r < RG; r++) {
-        const int32_t v = mx[r] + bu;
-        arg[r] = v < U[r] ? k : arg[r];
-        U[r] = min(U[r], v);
+        // v = mx + b;  if (v < U) arg = k;  U = min(U, v)
+        int32_t v;
+        asm("v_add_u32 %2, %3, %4\n\tv_cmp_lt_i32 vcc, %2, %0\n\tv_cndmask_b32 %1, %1, %5, vcc\n\t"
+            "v_min_i32 %0, %0, %2"
+            : "+v"(U[r]), "+v"(arg[r]), "=&v"(v)
+            : "s"(cur.m[q * RG + r]), "v"(bu), "v"(k0 + q)
+            : "vcc");
       }
     }
   }
@@ -615,6 +642,7 @@ __global__ __launch_bounds__(256) void k_mp_keep(MpArgs a) {
   u32 kept[RG];
 #pragma unroll
   for (int r = 0; r < RG; r++) kept[r] = 0;
+  fetch(nxt, 0, 0);
   for (int32_t s0 = 0; s0 < K; s0 += MP_SEG * 64) {
     const int32_t s1 = min(K, s0 + MP_SEG * 64);
     for (int32_t k0 = s0; k0 < s1; k0 += 32) {
@@ -625,16 +653,17 @@ __global__ __launch_bounds__(256) void k_mp_keep(MpArgs a) {
       for (int r = 0; r < RG; r++) word[r] = 0;
 #pragma unroll 1
       for (int q0 = 0; q0 < 32; q0 += KU) {
-        int32_t b[KU];
-#pragma unroll
-        for (int q = 0; q < KU; q++)
-          b[q] = (int32_t)min(B[(int64_t)min(k0 + q0 + q, K - 1) * ldb], (u32)MP_BIG);
+        cur = nxt;
+        fetch(nxt, k0 + q0 + KU, 0);
 #pragma unroll
         for (int q = 0; q < KU; q++) {
-          const cptr32 mn = st + (int64_t)min(k0 + q0 + q, K - 1) * 2 * a.NT;
+          const int32_t b = (int32_t)min(cur.b[q], (u32)MP_BIG);
+          int32_t t;
 #pragma unroll
           for (int r = 0; r < RG; r++)
-            word[r] = __builtin_amdgcn_alignbit(word[r], (u32)(mn[r] + b[q] + nU[r]), 31);
+            asm("v_add3_u32 %1, %2, %3, %4\n\tv_alignbit_b32 %0, %0, %1, 31"
+                : "+v"(word[r]), "=&v"(t)
+                : "s"(cur.m[q * RG + r]), "v"(b), "v"(nU[r]));
         }
       }
       const u32 valid = K - k0 >= 32 ? 0xffffffffu : (1u << (K - k0)) - 1;
