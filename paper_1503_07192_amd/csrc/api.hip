@@ -359,9 +359,16 @@ static hipError_t make_pairs(int32_t rows, int32_t G, bool upper, int64_t slot_e
     for (int32_t a2 = upper ? a1 : 0; a2 < G; a2++)
       h.push_back(swap && (*swap)[h.size()] ? make_int2(a2, a1 | spq::PAIR_SWAP) : make_int2(a1, a2));
   *npairs = (int32_t)h.size();
-  // pairs per launch: XT slots within 4 GiB, and the grid's y dimension
-  const int64_t budget = std::min<int64_t>((int64_t)1 << 30,
-                                           std::max<int64_t>((int64_t)1 << 26, out_elems / 32));
+  // pairs per launch: XT slots within 4 GiB, and the grid's y dimension.  Six kernels
+  // per launch, each with its own last wave: 2 GiB where that and the output fit in a
+  // third of what is free, else 1/32 of the output (400,000 vertices in 128 groups:
+  // launches of 0.25, 0.5, 0.9, 1, 2 and 4 GiB build in 70.6, 63.8, 62.0, 60.2, 59.5
+  // and 59.0 ms; 8,256 pairs of a 256 x 256 grid, 0.25 to 2: 11.3, 10.9, 10.6, 10.5).
+  int64_t budget = std::min<int64_t>((int64_t)1 << 30, std::max<int64_t>((int64_t)1 << 26, out_elems / 32));
+  size_t avail = 0, total = 0;
+  if (hipMemGetInfo(&avail, &total) == hipSuccess &&
+      (int64_t)(avail / sizeof(u32)) / 3 > out_elems + ((int64_t)1 << 29))
+    budget = std::max<int64_t>(budget, (int64_t)1 << 29);
   const int64_t fit = budget / std::max<int64_t>(slot_elems, 1);
   *chunk = (int32_t)std::max<int64_t>(1, std::min<int64_t>({(int64_t)*npairs, fit, 65528}));
   hipError_t e = dalloc(dev, std::max<int64_t>(*npairs, 1));
