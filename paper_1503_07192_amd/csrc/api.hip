@@ -205,6 +205,12 @@ struct spq_index {
   u32* flag = nullptr;
   u32 h_marks[32] = {};  // boundary vertices by mark (k_edges_scan)
   unsigned long long *sumc = nullptr, *total = nullptr;
+  // one block each: err, total, the marks' counts, sumc, cnt, nb (cleared and read back
+  // in one piece); gT, moff, off, bgoff, P, order, grp, gbg0, gV, fill (uploaded in one)
+  unsigned long long* counts = nullptr;
+  int32_t* plan = nullptr;
+  std::vector<int32_t> h_plan;
+  std::vector<unsigned long long> h_counts;
   u32 *err = nullptr, *members = nullptr, *M = nullptr, *BG = nullptr;
   u32* vrec = nullptr;
   int64_t* gT = nullptr;           // [groups] first element of each group's band in H
@@ -301,15 +307,12 @@ struct spq_index {
     for (auto x : execs) (void)hipGraphExecDestroy(x);
     for (auto g : graphs) (void)hipGraphDestroy(g);
     stream_give(device, cap);
-    void* ptrs[] = {comp, local, nb,   off,  bgoff, P,     order, bgcomp,  bglocal,
-                    cnt,  fill,  moff, flag, sumc,  total, err,   members, M,      BG,
-                    vrec, gT,    grp,   gbg0, gV,   bgrow, bgnb,  bggrp, b2list,  b2rank, m2,
-                    b2off, flag2, Mg,  R,    XT,    BG2,   H,     pairbase,
-                    bgvert, label, bglabel, cert, A,    DT,    bfflag,  bfstamp, bfcnt, bflist,
-                    sb_flag, sb_flagn, sb_list, sb_nlist, sb_rank, sb_nrank, sb_m, sb_n, sb_A3, sb_Aout,
-                    xe, xcount, boff, bsize, bfirst, gblk,
-                    eu_own, ev_own, w_own, tbase, tsize, b3list, b3rank, m3, b3off, flag3,
-                    M3, R3, XT3, BG3, plist, plist3, rowptr, adj, adeg, w_copy, meta,
+    void* ptrs[] = {comp, local, counts, plan, bgcomp, bglocal, flag, members, M, BG, vrec, bgrow,
+                    bgnb, bggrp, b2list, b2rank, m2, b2off, flag2, Mg, R, XT, BG2, H, pairbase, bgvert,
+                    label, bglabel, cert, A, DT, bfflag, bfstamp, bfcnt, bflist, sb_flag, sb_flagn,
+                    sb_list, sb_nlist, sb_rank, sb_nrank, sb_m, sb_n, sb_A3, sb_Aout, xe, xcount, boff,
+                    bsize, bfirst, gblk, eu_own, ev_own, w_own, tbase, tsize, b3list, b3rank, m3,
+                    b3off, flag3, M3, R3, XT3, BG3, plist, plist3, rowptr, adj, adeg, w_copy, meta,
                     mp.stats, mp.mask, mp3.stats, mp3.mask, mp_exec, fw_flags};
     for (void* p : ptrs) pool_release(p);
   }
@@ -953,19 +956,17 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
   TRY(hipEventRecord(X->ev[0], s));
 
   // ---- boundary detection and sizes (device), then the plan (host)
-  TRY(dalloc(&X->cnt, k));
-  TRY(dalloc(&X->nb, k));
+  constexpr int64_t SUMS = 18;  // words before sumc
+  TRY(dalloc(&X->counts, SUMS + 2 * (int64_t)k));
+  X->err = reinterpret_cast<u32*>(X->counts);
+  X->total = X->counts + 1;
+  X->sumc = X->counts + SUMS;
+  X->cnt = reinterpret_cast<int32_t*>(X->sumc + k);
+  X->nb = X->cnt + k;
   TRY(dalloc(&X->flag, n));
-  TRY(dalloc(&X->sumc, k));
-  TRY(dalloc(&X->total, 1 + 16));  // the total weight, then the marks' counts
-  TRY(dalloc(&X->err, 1));
   TRY(dalloc(&X->fw_flags, spq::FW_FLAGS));
-  TRY(hipMemsetAsync(X->cnt, 0, sizeof(int32_t) * k, s));
-  TRY(hipMemsetAsync(X->nb, 0, sizeof(int32_t) * k, s));
+  TRY(hipMemsetAsync(X->counts, 0, sizeof(unsigned long long) * (SUMS + 2 * (size_t)k), s));
   TRY(hipMemsetAsync(X->flag, 0, sizeof(u32) * (size_t)n, s));
-  TRY(hipMemsetAsync(X->sumc, 0, sizeof(unsigned long long) * k, s));
-  TRY(hipMemsetAsync(X->total, 0, 17 * sizeof(unsigned long long), s));
-  TRY(hipMemsetAsync(X->err, 0, sizeof(u32), s));
   spq::PartArgs pa{};
   pa.n = n; pa.k = k; pa.m = m;
   pa.eu = eu; pa.ev = ev; pa.w = w; pa.part = part;
@@ -973,20 +974,17 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
   pa.total = X->total; pa.err = X->err;
   pa.marks = reinterpret_cast<u32*>(X->total + 1);
   TRY(spq::launch_partition_scan(pa, s));
-  u32 herr = 0;
-  unsigned long long htotals[17] = {};
-  X->h_cnt.resize(k);
-  X->h_nb.resize(k);
-  X->h_sumc.resize(k);
-  TRY(hipMemcpyAsync(&herr, X->err, sizeof(u32), hipMemcpyDeviceToHost, s));
-  TRY(hipMemcpyAsync(htotals, X->total, sizeof(htotals), hipMemcpyDeviceToHost, s));
-  TRY(hipMemcpyAsync(X->h_cnt.data(), X->cnt, sizeof(int32_t) * k, hipMemcpyDeviceToHost, s));
-  TRY(hipMemcpyAsync(X->h_nb.data(), X->nb, sizeof(int32_t) * k, hipMemcpyDeviceToHost, s));
-  TRY(hipMemcpyAsync(X->h_sumc.data(), X->sumc, sizeof(unsigned long long) * k,
-                     hipMemcpyDeviceToHost, s));
+  std::vector<unsigned long long>& hc = X->h_counts;
+  hc.resize(SUMS + 2 * (size_t)k);
+  TRY(hipMemcpyAsync(hc.data(), X->counts, sizeof(unsigned long long) * hc.size(), hipMemcpyDeviceToHost, s));
   TRY(hipStreamSynchronize(s));
-  const unsigned long long htotal = htotals[0];
-  std::memcpy(X->h_marks, htotals + 1, sizeof(X->h_marks));
+  const u32 herr = (u32)hc[0];
+  const unsigned long long htotal = hc[1];
+  std::memcpy(X->h_marks, &hc[2], sizeof(X->h_marks));
+  X->h_sumc.assign(hc.begin() + SUMS, hc.begin() + SUMS + k);
+  const int32_t* hn = reinterpret_cast<const int32_t*>(&hc[SUMS + k]);
+  X->h_cnt.assign(hn, hn + k);
+  X->h_nb.assign(hn + k, hn + 2 * (int64_t)k);
   if (herr & spq::ERR_PART) return guard(fail(SPQ_EINVAL, "part[v] outside [0, k)"));
   if (herr & spq::ERR_VERTEX) return guard(fail(SPQ_EINVAL, "edge endpoint outside [0, n)"));
   if (herr & spq::ERR_WEIGHT) return guard(fail(SPQ_EINVAL, "edge weight outside [0, SPQ_INF)"));
@@ -1131,25 +1129,13 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
   // ---- index memory
   TRY(dalloc(&X->comp, n));
   TRY(dalloc(&X->local, n));
-  TRY(dalloc(&X->off, k + 1));
-  TRY(dalloc(&X->bgoff, k + 1));
-  TRY(dalloc(&X->P, k));
-  TRY(dalloc(&X->order, k));
-  TRY(dalloc(&X->moff, k));
   TRY(dalloc(&X->bgcomp, X->V));
   TRY(dalloc(&X->bglocal, X->V));
   TRY(dalloc(&X->bgvert, X->V));
-  TRY(dalloc(&X->fill, k));
   TRY(dalloc(&X->members, n));
   TRY(dalloc(&X->vrec, spq::VREC_WORDS * (int64_t)n));
   TRY(dalloc(&X->M, X->comp_elems));
   if (X->method == 1 && X->Vp > 0) TRY(dalloc(&X->BG, (int64_t)X->Vp * X->Vp));
-  TRY(dalloc(&X->grp, k));
-  TRY(dalloc(&X->gbg0, X->ngroups));
-  TRY(dalloc(&X->gV, X->ngroups));
-  TRY(hipMemcpyAsync(X->grp, X->h_grp.data(), sizeof(int32_t) * k, hipMemcpyHostToDevice, s));
-  TRY(hipMemcpyAsync(X->gbg0, X->h_gbg0.data(), sizeof(int32_t) * X->ngroups, hipMemcpyHostToDevice, s));
-  TRY(hipMemcpyAsync(X->gV, X->h_gV.data(), sizeof(int32_t) * X->ngroups, hipMemcpyHostToDevice, s));
   // band of each group in the blocked store: the full store keeps group pairs
   // S1 <= S2 (rows of S1 against S1 .. last), a share keeps share groups
   // against all groups, the flat method one group
@@ -1162,14 +1148,28 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
       t += (int64_t)X->h_gV[g] * (share_comps > 0 ? X->V : X->V - X->h_gbg0[g]);
     }
   }
-  TRY(dalloc(&X->gT, X->ngroups));
-  TRY(hipMemcpyAsync(X->gT, X->h_gT.data(), sizeof(int64_t) * X->ngroups, hipMemcpyHostToDevice, s));
-  TRY(hipMemcpyAsync(X->off, X->h_off.data(), sizeof(int32_t) * (k + 1), hipMemcpyHostToDevice, s));
-  TRY(hipMemcpyAsync(X->bgoff, X->h_bgoff.data(), sizeof(int32_t) * (k + 1), hipMemcpyHostToDevice, s));
-  TRY(hipMemcpyAsync(X->P, X->h_P.data(), sizeof(int32_t) * k, hipMemcpyHostToDevice, s));
-  TRY(hipMemcpyAsync(X->order, X->h_order.data(), sizeof(int32_t) * k, hipMemcpyHostToDevice, s));
-  TRY(hipMemcpyAsync(X->moff, X->h_moff.data(), sizeof(int64_t) * k, hipMemcpyHostToDevice, s));
-  TRY(hipMemsetAsync(X->fill, 0, sizeof(int32_t) * k, s));
+  {
+    const size_t G = X->ngroups, K = k;
+    X->h_plan.resize(4 * G + 8 * K + 2);
+    TRY(dalloc(&X->plan, (int64_t)X->h_plan.size()));
+    size_t at = 0;
+    auto put = [&](auto** dev, const auto& host) {
+      *dev = reinterpret_cast<std::remove_reference_t<decltype(*dev)>>(X->plan + at);
+      std::memcpy(&X->h_plan[at], host.data(), host.size() * sizeof(host[0]));
+      at += host.size() * sizeof(host[0]) / sizeof(int32_t);
+    };
+    put(&X->gT, X->h_gT);  // 8-byte elements first
+    put(&X->moff, X->h_moff);
+    put(&X->off, X->h_off);
+    put(&X->bgoff, X->h_bgoff);
+    put(&X->P, X->h_P);
+    put(&X->order, X->h_order);
+    put(&X->grp, X->h_grp);
+    put(&X->gbg0, X->h_gbg0);
+    put(&X->gV, X->h_gV);
+    put(&X->fill, std::vector<int32_t>(K, 0));
+    TRY(hipMemcpyAsync(X->plan, X->h_plan.data(), sizeof(int32_t) * at, hipMemcpyHostToDevice, s));
+  }
   if (X->graph) {
     // the captured kernels read the index's own copies of the edges
     TRY(dalloc(&X->eu_own, m));
@@ -1502,20 +1502,18 @@ spq_status spq_reweight_index(spq_index* X, const int32_t* w, void* stream) {
   HIP_TRY(hipStreamWaitEvent(s, X->ev[4], 0));
   HIP_TRY(hipEventRecord(X->ev[0], s));
   // validate the new weights and sum them, per component and in total
-  HIP_TRY(hipMemsetAsync(X->sumc, 0, sizeof(unsigned long long) * k, s));
-  HIP_TRY(hipMemsetAsync(X->total, 0, sizeof(unsigned long long), s));
-  HIP_TRY(hipMemsetAsync(X->err, 0, sizeof(u32), s));
+  const size_t sums = sizeof(unsigned long long) * (size_t)(X->sumc + k - X->counts);  // all before cnt
+  std::vector<unsigned long long>& hc = X->h_counts;
+  HIP_TRY(hipMemsetAsync(X->counts, 0, sums, s));
   spq::PartArgs pa{};
   pa.n = X->n; pa.k = k; pa.m = X->m; pa.eu = X->eu_own; pa.ev = X->ev_own; pa.w = w;
   pa.part = X->comp; pa.flag = X->flag; pa.sumc = X->sumc; pa.total = X->total; pa.err = X->err;
   HIP_TRY(spq::launch_edges_scan(pa, s));
-  u32 herr = 0;
-  unsigned long long htotal = 0;
-  HIP_TRY(hipMemcpyAsync(&herr, X->err, sizeof(u32), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipMemcpyAsync(&htotal, X->total, sizeof(htotal), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipMemcpyAsync(X->h_sumc.data(), X->sumc, sizeof(unsigned long long) * k,
-                         hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipMemcpyAsync(hc.data(), X->counts, sums, hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
+  const u32 herr = (u32)hc[0];
+  const unsigned long long htotal = hc[1];
+  std::memcpy(X->h_sumc.data(), &hc[X->sumc - X->counts], sizeof(unsigned long long) * k);
   if (herr & spq::ERR_WEIGHT) return fail(SPQ_EINVAL, "edge weight outside [0, SPQ_INF)");
   if (herr) return fail(SPQ_EDEVICE, "edge scan reported an inconsistent index");
   const bool cert = htotal >= (unsigned long long)SPQ_INF;
