@@ -634,9 +634,14 @@ static spq_status build_share(spq_index* X, spq::HierArgs& ha, int64_t m, bool p
     count(fl, cn);  // the next round's work
   }
   X->bf_rounds = (int32_t)consumed;
-  // the rows outside B3 from the settled B3 rows
-  HIP_TRY(spq::launch_share_final(ha, blk, b3, s));
-  for (int32_t t = 0; t < NB; t++)
+  // the rows outside B3 from the settled B3 rows; the composition's operand panels
+  // and the store, not written yet, are its scratch
+  int64_t rows3 = 0;
+  const bool pruned = spq::share_final_words(blk, b3, X->S2p, &rows3) <= X->h_elems &&
+                      rows3 <= (int64_t)G * X->S2p * X->m2pmax && NB <= 65528;
+  HIP_TRY(spq::launch_mp_zero(X->mp, s));
+  HIP_TRY(spq::launch_share_final(ha, blk, b3, pruned ? X->BG2 : nullptr, X->H, s));
+  for (int32_t t = 0; t < NB && !pruned; t++)
     if (X->h_sbm[t] > 0)
       X->relax_bg_exec += (double)((X->h_sbn[t] + 127) / 128) * ntc * 128.0 * 128.0 *
                           (double)round_up(X->h_sbm[t], 16);
@@ -646,7 +651,6 @@ static spq_status build_share(spq_index* X, spq::HierArgs& ha, int64_t m, bool p
     for (auto& e : X->prof) HIP_TRY(hipEventCreate(&e));
     ha.evt = X->prof.data();
   }
-  HIP_TRY(spq::launch_mp_zero(X->mp, s));
   HIP_TRY(spq::launch_share_compose(ha, X->DT, s));
   return SPQ_OK;
 }

@@ -408,10 +408,16 @@ struct MpArgs {
   unsigned long long* mask;
   unsigned long long* exec;  // 16 counters
   CompStore cs;
+  // side 2, the last product of a share's Bellman-Ford: rows (share sources), the blocks'
+  // first level-2 ids, their rows outside B3 (nstride apart) and the table they lie in
+  int32_t rows, nstride;
+  const int32_t *boff, *nlist;
+  u32* DT;
 };
 
 // One side of the composition for the pair of a slot: 0 the first product,
-// 1 the second.
+// 1 the second; 2: block `slot` of the Bellman-Ford's last product, K its B3 rows (of
+// DT, gathered into XT; leading dimension ldd), columns its other rows.
 struct MpSide {
   int32_t g;      // the group whose boundary vertices are the K and whose closure rows are B
   int32_t K;      // its boundary vertices
@@ -422,10 +428,19 @@ struct MpSide {
 };
 
 __device__ __forceinline__ MpSide mp_side(int side, const MpArgs& a, int32_t slot) {
+  MpSide m;
+  if (side == 2) {
+    m.g = slot;
+    m.K = a.m2[slot];
+    m.W = a.gV[slot];
+    m.rows = a.rows;
+    m.A = a.XT + (int64_t)slot * a.Kp * a.ldd;
+    m.lda = a.ldd;
+    return m;
+  }
   const int2 pr = a.plist[a.pbase + slot];
   const bool sw = (pr.y & PAIR_SWAP) != 0;
   const int32_t s1 = pr.x, s2 = pr.y & ~PAIR_SWAP;
-  MpSide m;
   m.g = side ? s2 : s1;
   m.K = a.m2[m.g];
   m.W = a.gV[m.g];
@@ -853,6 +868,7 @@ __device__ __forceinline__ void mp_place(const MpArgs& a, int32_t& slot, int32_t
 // SIDE 0, the first product: rows b in B2(S2), columns x of S1, stored as XT.
 // SIDE 1: rows x of S1, columns y of S2, stored as the block D(S1, S2) (D(S2,
 // S1) for a swapped pair).  CERT: with the certificate.
+// SIDE 2: rows: share sources, columns: rows of DT, lowered in place.
 template <int SIDE, bool CERT>
 __global__ __launch_bounds__(64) SPQ_MP_ATTR void k_mp_prod(MpArgs a) {
   __shared__ __attribute__((aligned(16))) u32 s[32 * MP_ST];
@@ -868,13 +884,13 @@ __global__ __launch_bounds__(64) SPQ_MP_ATTR void k_mp_prod(MpArgs a) {
   if (x0 >= m.rows || p0 >= m.W) return;
   const CompStore& cs = a.cs;
   const int lane = threadIdx.x, ly = lane >> 3, lx = lane & 7;
-  const int2 pr = a.plist[a.pbase + slot];
+  const int2 pr = SIDE == 2 ? make_int2(slot, slot) : a.plist[a.pbase + slot];
   const bool sw = (pr.y & PAIR_SWAP) != 0;
   const int32_t s1 = pr.x, s2 = pr.y & ~PAIR_SWAP;
   // the block's rows (of a swapped pair the tile's columns) and columns
   const int32_t u0 = sw ? p0 : x0, ulim = sw ? m.W : m.rows;
   const int32_t l0 = sw ? x0 : p0, llim = sw ? m.rows : m.W;
-  const int32_t gu = SIDE ? cs.g0[sw ? s2 : s1] : 0, gl = SIDE ? cs.g0[sw ? s1 : s2] : 0;
+  const int32_t gu = SIDE == 1 ? cs.g0[sw ? s2 : s1] : 0, gl = SIDE == 1 ? cs.g0[sw ? s1 : s2] : 0;
   u32* base = nullptr;
   MpTerms t{};
   u32 c[8][8];
@@ -912,7 +928,7 @@ __global__ __launch_bounds__(64) SPQ_MP_ATTR void k_mp_prod(MpArgs a) {
       const u32* bp = B + (uint64_t)k * (u32)a.Vp + (lane & 15) * 4;
       lds_load16(bp, d + MP_KC * MP_T);
       if (SIDE) {
-        const u32* ap = A + (uint64_t)k * (u32)a.Vp + (lane & 15) * 4;
+        const u32* ap = A + (uint64_t)k * (u32)m.lda + (lane & 15) * 4;
         lds_load16(ap, d);
       } else {
 #pragma unroll
@@ -927,7 +943,7 @@ __global__ __launch_bounds__(64) SPQ_MP_ATTR void k_mp_prod(MpArgs a) {
 #pragma unroll
     for (int i = 0; i < MP_RING; i++)
       if (i * MP_KC < n) load_step(0, i);
-    if (SIDE && !cs.dense) {  // the store's terms, before they are needed
+    if (SIDE == 1 && !cs.dense) {  // the store's terms, before they are needed
       base = cs.H + (sw ? cs.pairbase[(int64_t)s2 * cs.ngroups + s1]
                         : cs.pairbase[(int64_t)s1 * cs.ngroups + s2]);
       const int32_t ug = gu + min(u0 + lane, ulim - 1), lg = gl + min(l0 + lane, llim - 1);
@@ -1008,6 +1024,33 @@ __global__ __launch_bounds__(64) SPQ_MP_ATTR void k_mp_prod(MpArgs a) {
       __builtin_amdgcn_wave_barrier();
 #pragma unroll 8
       for (int q = 0; q < 32; q++) xt[(int64_t)(h * 32 + q) * a.Vp + lane] = s[q * MP_ST + lane];
+      __builtin_amdgcn_wave_barrier();
+    }
+    return;
+  }
+  if (SIDE == 2) {
+    // DT's rows of the tile's columns, 64 consecutive sources per store
+    const int32_t* nl = a.nlist + (int64_t)slot * a.nstride + p0;
+    u32* D = a.DT + (int64_t)a.boff[slot] * a.ldd + x0 + lane;
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+      mp_stage<false>(c, s, h, ly, lx);
+      __builtin_amdgcn_wave_barrier();
+      const int32_t n = min(m.W - p0 - h * 32, 32);
+      for (int q0 = 0; q0 < n; q0 += 8) {
+        u32 v[8], old[8];
+        int32_t row[8];
+#pragma unroll
+        for (int i = 0; i < 8; i++) row[i] = nl[h * 32 + min(q0 + i, n - 1)];
+#pragma unroll
+        for (int i = 0; i < 8; i++) {
+          v[i] = s[(q0 + i) * MP_ST + lane];
+          old[i] = D[row[i] * a.ldd];
+        }
+#pragma unroll
+        for (int i = 0; i < 8; i++)
+          if (q0 + i < n) D[row[i] * a.ldd] = min(v[i], old[i]);
+      }
       __builtin_amdgcn_wave_barrier();
     }
     return;
@@ -1373,6 +1416,18 @@ __global__ void k_aout_gather(int32_t bpmax, int32_t b3pmax, int32_t n3pmax,
   for (int32_t i = threadIdx.x; i < n3pmax; i += blockDim.x) out[i] = (arow && i < nt) ? arow[nl[i]] : INF;
 }
 
+// The B3 rows of DT, block by block: row k of block t at rows3[(t * b3pmax + k) * S2p].
+__global__ void k_b3_rows(int32_t bpmax, int64_t S2p, const int32_t* __restrict__ m3,
+                          const int32_t* __restrict__ b3list, const int32_t* __restrict__ boff,
+                          const u32* __restrict__ DT, u32* __restrict__ rows3) {
+  const int t = blockIdx.y;
+  const int32_t k = blockIdx.x;
+  if (k >= m3[t]) return;
+  const uint4* src = reinterpret_cast<const uint4*>(DT + ((int64_t)boff[t] + b3list[(int64_t)t * bpmax + k]) * S2p);
+  uint4* dst = reinterpret_cast<uint4*>(rows3 + ((int64_t)t * gridDim.x + k) * S2p);
+  for (int64_t i = threadIdx.x; i < S2p / 4; i += blockDim.x) dst[i] = src[i];
+}
+
 // The 128 x 128 tile whose row r is g + rows[r] * ld, in the register layout
 // of tile_load; rows r >= nvalid read as INF and are not stored.
 __device__ __forceinline__ void tile_load_rows(u32 (&c)[8][8], const u32* g, int64_t ld,
@@ -1568,15 +1623,15 @@ int64_t mp_mask_words(int32_t Kp, int32_t Vp) {
 
 template <int SIDE>
 static void mp_product(MpArgs a, bool cert, const MpWork& w, hipEvent_t* evt, hipStream_t s) {
-  const int32_t rows = SIDE ? a.Vp : a.Kp;
+  const int32_t rows = SIDE == 2 ? (int32_t)a.ldd : SIDE ? a.Vp : a.Kp;
   a.NT = mp_row_tiles<SIDE>(rows);
-  a.exec = w.exec + (SIDE && !a.cs.dense ? 16 : 0);
+  a.exec = w.exec + (SIDE == 1 && !a.cs.dense ? 16 : 0);
   const unsigned np = (unsigned)a.np;
   k_mp_stats<SIDE><<<dim3((unsigned)a.NT, np), 256, 0, s>>>(a);
   k_mp_keep<SIDE><<<dim3((unsigned)((a.NC + 3) / 4 * (a.NT / MP_RG<SIDE>)), np), 256, 0, s>>>(a);
   if (evt) (void)hipEventRecord(evt[0], s);
   const dim3 g((unsigned)(rows / MP_T * a.NC), (np + 7) / 8 * 8);
-  if (SIDE && cert)
+  if (SIDE == 1 && cert)
     k_mp_prod<SIDE, SIDE == 1><<<g, 64, 0, s>>>(a);
   else
     k_mp_prod<SIDE, false><<<g, 64, 0, s>>>(a);
@@ -1763,11 +1818,41 @@ hipError_t launch_share_round(const HierArgs& a, const ShareBlocks& b, const Sha
   return hipGetLastError();
 }
 
-hipError_t launch_share_final(const HierArgs& a, const ShareBlocks& b, const ShareB3& c,
-                              hipStream_t s) {
-  const int ntm = c.n3pmax / 128, ntc = (int)(a.S2p / 128);
-  k_bf_final<<<dim3((unsigned)(ntm * ntc), (unsigned)b.nblk), 256, 0, s>>>(
-      b.bpmax, c.b3pmax, c.n3pmax, a.S2p, c.m3, c.n3, b.boff, c.b3list, c.nb3list, c.Aout, a.DT);
+// The rows outside B3 from the settled B3 rows, pruned like the composition's products
+// (the B3 rows of DT are distances from far away, Aout is part of a closed matrix): the
+// B3 rows are gathered into rows3, then the same three kernels, masks and statistics in
+// `scratch`.  By one product of every B3 row (k_bf_final, where the scratch is too
+// small) a 30,700-row share took 4.6 ms, so 1.8 (build 49.3 -> 46.7).
+int64_t share_final_words(const ShareBlocks& b, const ShareB3& c, int64_t S2p, int64_t* rows3) {
+  *rows3 = (int64_t)b.nblk * c.b3pmax * S2p;
+  const int64_t nt = mp_row_tiles<2>((int32_t)S2p);
+  return (int64_t)b.nblk * (nt * (c.n3pmax / MP_T) * (c.b3pmax / 64) * 2 + nt * 2 * c.b3pmax);
+}
+
+hipError_t launch_share_final(const HierArgs& a, const ShareBlocks& b, const ShareB3& c, u32* rows3,
+                              u32* scratch, hipStream_t s) {
+  if (!rows3) {
+    const int ntm = c.n3pmax / 128, ntc = (int)(a.S2p / 128);
+    k_bf_final<<<dim3((unsigned)(ntm * ntc), (unsigned)b.nblk), 256, 0, s>>>(
+        b.bpmax, c.b3pmax, c.n3pmax, a.S2p, c.m3, c.n3, b.boff, c.b3list, c.nb3list, c.Aout, a.DT);
+    return hipGetLastError();
+  }
+  k_b3_rows<<<dim3((unsigned)c.b3pmax, (unsigned)b.nblk), 256, 0, s>>>(b.bpmax, a.S2p, c.m3, c.b3list,
+                                                                       b.boff, a.DT, rows3);
+  MpArgs m{};
+  m.np = b.nblk;
+  m.Vp = c.n3pmax;
+  m.Kp = c.b3pmax;
+  m.NC = m.Vp / MP_T;
+  m.NW = m.Kp / 64;
+  m.m2 = c.m3; m.gV = c.n3;
+  m.ldd = a.S2p;
+  m.R = c.Aout; m.XT = rows3;
+  m.rows = a.S2; m.nstride = b.bpmax; m.boff = b.boff; m.nlist = c.nb3list; m.DT = a.DT;
+  const int64_t nt = mp_row_tiles<2>((int32_t)a.S2p);
+  m.mask = reinterpret_cast<unsigned long long*>(scratch);
+  m.stats = reinterpret_cast<int32_t*>(scratch + (int64_t)b.nblk * nt * m.NC * m.NW * 2);
+  mp_product<2>(m, false, a.work, nullptr, s);
   return hipGetLastError();
 }
 

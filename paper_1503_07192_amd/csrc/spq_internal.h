@@ -169,8 +169,10 @@ hipError_t launch_share_b3_lists(const HierArgs& a, const ShareBlocks& b, uint8_
 hipError_t launch_share_b3_gather(const ShareBlocks& b, const ShareB3& c, hipStream_t s);
 // After the rounds: rows outside B3 from the settled B3 rows,
 //   DT[v] = min(DT[v], min over b in B3(T) of A_T[v][b] + DT[b])
-hipError_t launch_share_final(const HierArgs& a, const ShareBlocks& b, const ShareB3& c,
-                              hipStream_t s);
+hipError_t launch_share_final(const HierArgs& a, const ShareBlocks& b, const ShareB3& c, u32* rows3,
+                              u32* scratch, hipStream_t s);
+// words of its scratch (returned) and of rows3; rows3 null: the product of every B3 row
+int64_t share_final_words(const ShareBlocks& b, const ShareB3& c, int64_t S2p, int64_t* rows3);
 // One Bellman-Ford round of the share, on the B3 rows of every block.  dirty
 // flags: per block, ntc = S2p / 128 column tiles then one "any" word; cnt /
 // list: per (block, tile) the number of B3 rows lowered since the last intra
