@@ -357,10 +357,10 @@ struct CompStore {
 // product starts from it.
 //
 // Measured (MI355X): 400,000 Delaunay vertices in 128 groups, both levels'
-// products 79 -> 52 ms with all tests, the second one executing 0.48e12
-// relaxations instead of 1.45e12; build 117 -> 87 ms.  A 30,700-row share of a
-// 1024 x 1024 grid: 45 -> 22 ms, 0.13e12 of 0.93e12 relaxations; build 79.5 ->
-// 56.5 ms.  The test stays exact and costs little on operands it cannot prune.
+// products 79 -> 40 ms with all tests, the second one executing 0.48e12
+// relaxations instead of 1.45e12; build 117 -> 58.5 ms.  A 30,700-row share of a
+// 1024 x 1024 grid: 45 -> 19 ms, 0.13e12 of 0.93e12 relaxations; build 79.5 ->
+// 46.7 ms.  The test stays exact and costs little on operands it cannot prune.
 //
 // Three kernels per product and chunk of pairs: k_mp_stats (mn, mx per row
 // tile and k), k_mp_keep (per row tile and 64 columns a bit mask of the k to
@@ -372,7 +372,7 @@ struct CompStore {
 // group's.  There 128 rows per tile test half as often as 64 and keep 10 - 17%
 // more: second product and test 21.6 + 5.4 ms against 20.6 + 8.2 on 400,000
 // Delaunay vertices in 128 groups, 12.4 + 3.5 against 11.8 + 6.6 ms on a share
-// of 32 of a 1024 x 1024 grid's 256 groups
+// of 32 of a 1024 x 1024 grid's 256 groups (now, at 128: 18.9 + 4.8 and 10.5 + 2.4)
 template <int SIDE>
 constexpr int MP_SR = SIDE ? 128 : 64;
 template <int SIDE>
