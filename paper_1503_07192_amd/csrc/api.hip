@@ -728,8 +728,11 @@ static void plan_components(spq_index* X, bool plain) {
 // are the same.  Measured beside them: flat closures of 860 / 1,596 / 3,740 /
 // 6,780 / 15,548 / 27,900 vertices 0.5 / 0.9 / 2.7 / 8.3 / 60 / 324 ms, two-tile
 // closures of 1,792 / 5,512 / 7,680 vertices 0.9 / 5.8 / 10 ms, batches of 16 of 1,792
-// and 8 of 3,712 vertices 2.8 and 10 ms, compositions of 7.0e9 entries through
-// 230 vertices 42 ms and of 3.9e8 through 480 5 ms.
+// and 8 of 3,712 vertices 2.8 and 10 ms.  A composition's products are pruned, so that
+// the vertices it goes through count for little between many groups and for more
+// between few super-groups: 7.0e9 entries through 157 / 230 / 298 / 426 vertices of 256 /
+// 128 / 64 / 32 groups 27 / 28 / 30 / 37 ms, 8.1e8 and 4.4e8 through 518 of 16
+// super-groups 9.7 and 5.2.
 static double flat_seconds(double v) {
   if (v <= 512) return 7e-5;
   return std::ceil(v / 512) * 2.4e-4 + v * v * v / 2 / 33e12 + v * v * 8 / 2.5e12;
@@ -738,8 +741,8 @@ static double closure_seconds(double v, double batch) {
   if (v <= 512 && batch <= 13) return v <= 32 ? 2e-5 : 1e-4;
   return std::ceil(v / 256) * (batch > 1 ? 1.5e-4 : 1.1e-4) + batch * v * v * v / 2 / 28e12;
 }
-static double compose_seconds(double entries, double through) {
-  return 2.5e-4 + entries * through / 38e12 + entries * 4 / 2.5e12;
+static double compose_seconds(double entries, double through, bool level3) {
+  return 2.5e-4 + entries * through / (level3 ? 60e12 : 230e12) + entries * 3.2e-12;
 }
 
 // Boundary vertices of the partition into runs of `comps` components, counted
@@ -769,7 +772,7 @@ static Bg2Plan bg2_plan(const spq_index* X, int32_t G, double comps, double v2, 
     if (size * size * nT > v2 * v2) continue;  // (more memory than BG2 itself)
     const double v3 = std::min(v2, cut_vertices(X, comps * gpt));
     const double t = 3e-4 + closure_seconds(size, nT) + closure_seconds(v3, 1) +
-                     compose_seconds(v2 * v2 / 2, v3 / nT);
+                     compose_seconds(v2 * v2 / 2, v3 / nT, true);
     if (t < best.seconds) best = Bg2Plan{gpt, t};
   }
   return best;
@@ -778,8 +781,8 @@ static Bg2Plan bg2_plan(const spq_index* X, int32_t G, double comps, double v2, 
 // The fastest two-level plan over powers of two of components per group (cpg =
 // 0: none), with groups of at most 4,096 BG vertices.  Measured builds, planned
 // against the flat closure or groups of about 4,096: 1,596 BG vertices 0.75 - 0.90
-// against 1.28 ms, 6,780 2.0 - 2.6 against 8.7, 27,900 5.8 - 14 against 327, 38,426
-// 10.7 against 27; partitions that cut everywhere (shuffled) stay flat.  Above
+// against 1.28 ms, 6,780 2.0 - 2.6 against 8.7, 27,900 9.9 against 325, 118,395 59 (the
+// best of all groupings 57); partitions that cut everywhere (shuffled) stay flat.  Above
 // PLAN_MAX BG vertices the groups stay at about 4,096.
 constexpr int32_t PLAN_MAX = 131072;
 struct TwoLevelPlan {
@@ -796,7 +799,7 @@ static TwoLevelPlan plan_two_level(const spq_index* X) {
     if (G <= 1024 && (double)G * widest * widest <= V * V) {
       const double v2 = cut_vertices(X, (double)cpg);
       const double t = 3e-4 + closure_seconds(widest, G) + bg2_plan(X, G, (double)cpg, v2, nullptr).seconds +
-                       compose_seconds(V * V / 2, v2 / G);
+                       compose_seconds(V * V / 2, v2 / G, false);
       if (t < best.seconds) best = TwoLevelPlan{(int32_t)cpg, t};
     }
     for (size_t i = 0; 2 * i < size.size(); i++)
