@@ -578,6 +578,7 @@ __device__ __forceinline__ u32 wave_or(u32 v) {
 template <int SIDE>
 __global__ __launch_bounds__(256) void k_mp_keep(MpArgs a) {
   constexpr int SR = MP_SR<SIDE>, RG = MP_RG<SIDE>;
+  static_assert(RG % 2 == 0, "the bounds are raised two row tiles at a time");
   __shared__ u32 seg[4][RG][MP_SEG * 2];
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
   const int32_t slot = blockIdx.y;
@@ -626,13 +627,18 @@ __global__ __launch_bounds__(256) void k_mp_keep(MpArgs a) {
       bmin = min(bmin, cur.b[q]);
       const int32_t bu = (int32_t)min(cur.b[q], (u32)MP_BIG);
 #pragma unroll
-      for (int r = 0; r < RG; r++) {
-        // v = mx + b;  if (v < U) arg = k;  U = min(U, v)
-        int32_t v;
-        asm("v_add_u32 %2, %3, %4\n\tv_cmp_lt_i32 vcc, %2, %0\n\tv_cndmask_b32 %1, %1, %5, vcc\n\t"
-            "v_min_i32 %0, %0, %2"
-            : "+v"(U[r]), "+v"(arg[r]), "=&v"(v)
-            : "s"(cur.m[q * RG + r]), "v"(bu), "v"(k0 + q)
+      for (int r = 0; r < RG; r += 2) {
+        // v = mx + b;  if (v < U) arg = k;  U = min(U, v).  Two row tiles at a time, with a
+        // mask each: v_cndmask may read a mask two wait states after the v_cmp that
+        // wrote it, which the other tile's instructions fill.
+        int32_t v0, v1;
+        unsigned long long below;
+        asm("v_add_u32 %4, %7, %9\n\tv_add_u32 %5, %8, %9\n\t"
+            "v_cmp_lt_i32 vcc, %4, %0\n\tv_cmp_lt_i32_e64 %6, %5, %2\n\t"
+            "v_min_i32 %0, %0, %4\n\tv_cndmask_b32 %1, %1, %10, vcc\n\t"
+            "v_min_i32 %2, %2, %5\n\tv_cndmask_b32_e64 %3, %3, %10, %6"
+            : "+&v"(U[r]), "+&v"(arg[r]), "+&v"(U[r + 1]), "+v"(arg[r + 1]), "=&v"(v0), "=&v"(v1), "=&s"(below)
+            : "s"(cur.m[q * RG + r]), "s"(cur.m[q * RG + r + 1]), "v"(bu), "v"(k0 + q)
             : "vcc");
       }
     }
