@@ -60,14 +60,17 @@ __device__ __forceinline__ void relax2(u32& c, u32 a0, u32 b0, u32 a1, u32 b1) {
 // ahead then waits for the loads it has just begun (first products of a 400,000-vertex
 // graph 7.9 -> 7.4 ms, 256-pivot interiors 14.3 -> 13.6, a share's second products 10.9 ->
 // 10.5).  No output register is written; loads the compiler does not count only make
-// its own waits longer.
+// its own waits longer.  m0 is written and not declared: it is a reserved register,
+// which a clobber list cannot name, and no instruction of the compiler's own in these
+// kernels uses it (LDS needs it no more, they index no registers; a test reads the
+// compiled listing for it).
 __device__ __forceinline__ void lds_load16(const u32* g, u32* lds) {
   const u32 m0 = __builtin_amdgcn_readfirstlane((u32)(uintptr_t)(__attribute__((address_space(3))) u32*)lds);
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(m0), "v"(g) : "memory", "m0");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(m0), "v"(g) : "memory");
 }
 __device__ __forceinline__ void lds_load4(const u32* g, u32* lds) {
   const u32 m0 = __builtin_amdgcn_readfirstlane((u32)(uintptr_t)(__attribute__((address_space(3))) u32*)lds);
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(m0), "v"(g) : "memory", "m0");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(m0), "v"(g) : "memory");
 }
 // (the builtin: the compiler then knows its own loads to be complete too)
 __device__ __forceinline__ void wait_loads() {

@@ -80,3 +80,16 @@ def test_scalar_results_of_vector_instructions_are_waited_for(listings):
                 seen += inside
     assert seen > 1000  # the statements were found
     assert not bad, bad[:4]
+
+
+def test_m0_belongs_to_the_asm_statements(listings):
+    """The statements that load to LDS write m0, a reserved register that no
+    clobber list may name: no instruction of the compiler's may rely on it, and
+    the compiler has nothing to say about them."""
+    for src in SOURCES:
+        code, said = listings[src]
+        assert "inline-asm" not in said, said.split("\n")[0]
+        for kernel, ins in code.items():
+            used = [(name, ops) for name, ops, inside in ins if "m0" in ops and not inside]
+            loads = [name for name, _, inside in ins if inside and name.startswith("global_load_lds")]
+            assert not (loads and used), (kernel, used[:3])
