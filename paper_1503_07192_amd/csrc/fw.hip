@@ -197,8 +197,9 @@ __device__ __forceinline__ void inner_tile(int part, int b, int c0, int nt, int 
   }
 }
 
+// Four workgroups per CU while their chunks take 32 KB of LDS each, two at 64 KB.
 template <int T, int KC, int PT>
-__global__ __launch_bounds__(256, 4) void k_fw_inner(u32* __restrict__ A, int64_t ld, int c0, int nt,
+__global__ __launch_bounds__(256, KC * T <= 2048 ? 4 : 2) void k_fw_inner(u32* __restrict__ A, int64_t ld, int c0, int nt,
                                                                 FwAt at, int part, int nn) {
   constexpr int Q = KC * T / 4 / 256;  // uint4 per thread per operand chunk
   static_assert(Q >= 1 && KC * T / 4 % 256 == 0, "chunk must split evenly");

@@ -93,3 +93,8 @@ def test_m0_belongs_to_the_asm_statements(listings):
             used = [(name, ops) for name, ops, inside in ins if "m0" in ops and not inside]
             loads = [name for name, _, inside in ins if inside and name.startswith("global_load_lds")]
             assert not (loads and used), (kernel, used[:3])
+
+
+def test_occupancy_targets_are_met(listings):
+    for src in SOURCES:
+        assert "occupancy" not in listings[src][1], listings[src][1]
