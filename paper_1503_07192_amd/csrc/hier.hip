@@ -284,7 +284,7 @@ __device__ __forceinline__ void mp_stream128_rows(u32 (&c)[8][8], const u32* At,
       load(cur ^ 1);
       index(k + 2 * KC);
     }
-    minplus_lds<T>(c, sA + cur * KC * T, sB + cur * KC * T, min(KC, (cnt - k + 1) & ~1));
+    minplus_lds<T, 1>(c, sA + cur * KC * T, sB + cur * KC * T, min(KC, (cnt - k + 1) & ~1));
     wait_loads();
     __syncthreads();
   }

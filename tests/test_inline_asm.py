@@ -98,3 +98,8 @@ def test_m0_belongs_to_the_asm_statements(listings):
 def test_occupancy_targets_are_met(listings):
     for src in SOURCES:
         assert "occupancy" not in listings[src][1], listings[src][1]
+
+
+def test_loops_unroll_as_asked(listings):
+    for src in SOURCES:
+        assert "not unrolled" not in listings[src][1], listings[src][1]
