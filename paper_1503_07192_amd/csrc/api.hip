@@ -1328,7 +1328,11 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
     // level 3 (super-groups of gpt groups): as asked, or where it is estimated
     // to close BG2 faster than one flat closure
     if (X->V2 > 0 && level3_opt >= 0) {
-      const int32_t gpt = level3_opt > 0 ? std::min(level3_opt, G) : bg2_plan(X, G, (double)k / G, X->V2, X->h_b2off.data()).gpt;
+      // (k / G would count a partial last group as a whole one, and the cut of
+      // super-groups half as wide as they are)
+      const double comps = X->group_bg ? (double)k / G : X->cpg;
+      const int32_t gpt = level3_opt > 0 ? std::min(level3_opt, G)
+                                         : bg2_plan(X, G, comps, X->V2, X->h_b2off.data()).gpt;
       if (gpt > 0) {
         X->gpt = gpt;
         X->nT = (G + gpt - 1) / gpt;
