@@ -37,3 +37,12 @@ def test_partial_last_group(side, groups, groups3):
     and 4 were taken for 8 and 2)."""
     st = build_and_check(side)
     assert (st["ngroups"], st["groups3"]) == (groups, groups3)
+
+
+@pytest.mark.parametrize("side,groups3", [(130, 0), (200, 5)])
+def test_level3_is_taken_where_it_pays(side, groups3):
+    """2,175 BG2 vertices: one flat closure is estimated at 1.2 ms, any
+    super-groups at 1.6 or more.  7,643 of 20 groups: 11 ms flat, 3.1 by
+    super-groups of 4."""
+    st = build_and_check(side)
+    assert st["groups3"] == groups3 and (st["v_bg3"] > 0) == (groups3 > 0)
