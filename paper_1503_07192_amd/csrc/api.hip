@@ -757,22 +757,28 @@ static double cut_vertices(const spq_index* X, double comps) {
 
 // How to close BG2 (v2 vertices of G groups of `comps` components; b2off: the
 // groups' first BG2 ids, NULL while only their number is known): gpt = 0 by one
-// flat closure, else by level 3 on super-groups of gpt groups (a power of two).
+// flat closure, else by level 3 on super-groups of gpt groups.  opt: the caller's
+// level3_groups: -1 no level 3, 0 whichever is estimated faster (gpt a power of
+// two), else super-groups of so many groups.
 struct Bg2Plan {
   int32_t gpt;
   double seconds;
 };
-static Bg2Plan bg2_plan(const spq_index* X, int32_t G, double comps, double v2, const int32_t* b2off) {
-  Bg2Plan best{0, closure_seconds(v2, 1)};
-  for (int32_t gpt = 2; gpt < G; gpt *= 2) {
+static Bg2Plan bg2_plan(const spq_index* X, int32_t G, double comps, double v2, const int32_t* b2off,
+                        int32_t opt) {
+  auto super = [&](int32_t gpt) {
     const double nT = std::ceil((double)G / gpt);
     double size = v2 / G * gpt;  // of the widest super-group: all are padded to it
     if (b2off)
       for (int32_t g = 0; g < G; g += gpt) size = std::max(size, (double)(b2off[std::min(g + gpt, G)] - b2off[g]));
-    if (size * size * nT > v2 * v2) continue;  // (more memory than BG2 itself)
+    if (opt == 0 && size * size * nT > v2 * v2) return 1e30;  // (more memory than BG2 itself)
     const double v3 = std::min(v2, cut_vertices(X, comps * gpt));
-    const double t = 3e-4 + closure_seconds(size, nT) + closure_seconds(v3, 1) +
-                     compose_seconds(v2 * v2 / 2, v3 / nT, true);
+    return 3e-4 + closure_seconds(size, nT) + closure_seconds(v3, 1) + compose_seconds(v2 * v2 / 2, v3 / nT, true);
+  };
+  if (opt > 0) return Bg2Plan{std::min(opt, G), super(std::min(opt, G))};
+  Bg2Plan best{0, closure_seconds(v2, 1)};
+  for (int32_t gpt = 2; opt == 0 && gpt < G; gpt *= 2) {
+    const double t = super(gpt);
     if (t < best.seconds) best = Bg2Plan{gpt, t};
   }
   return best;
@@ -783,13 +789,16 @@ static Bg2Plan bg2_plan(const spq_index* X, int32_t G, double comps, double v2, 
 // against the flat closure or groups of about 4,096: 1,596 BG vertices 0.75 - 0.90
 // against 1.28 ms, 6,780 2.0 - 2.6 against 8.7, 27,900 9.9 against 325, 118,395 59 (the
 // best of all groupings 57); partitions that cut everywhere (shuffled) stay flat.  Above
-// PLAN_MAX BG vertices the groups stay at about 4,096.
+// PLAN_MAX BG vertices the groups stay at about 4,096.  level3: the caller's
+// level3_groups; without level 3 BG2 is closed flat, which few wide groups keep
+// small (118,395 BG vertices: 128 groups leave 29,500 of BG2, 0.47 s, 32 groups
+// 13,600, 0.05).
 constexpr int32_t PLAN_MAX = 131072;
 struct TwoLevelPlan {
   int32_t cpg;
   double seconds;
 };
-static TwoLevelPlan plan_two_level(const spq_index* X) {
+static TwoLevelPlan plan_two_level(const spq_index* X, int32_t level3) {
   TwoLevelPlan best{0, 1e30};
   const double V = X->V;
   std::vector<int32_t> size(X->h_nb);  // BG vertices of every run of cpg components
@@ -798,7 +807,7 @@ static TwoLevelPlan plan_two_level(const spq_index* X) {
     if (widest > 4096) break;
     if (G <= 1024 && (double)G * widest * widest <= V * V) {
       const double v2 = cut_vertices(X, (double)cpg);
-      const double t = 3e-4 + closure_seconds(widest, G) + bg2_plan(X, G, (double)cpg, v2, nullptr).seconds +
+      const double t = 3e-4 + closure_seconds(widest, G) + bg2_plan(X, G, (double)cpg, v2, nullptr, level3).seconds +
                        compose_seconds(V * V / 2, v2 / G, false);
       if (t < best.seconds) best = TwoLevelPlan{(int32_t)cpg, t};
     }
@@ -1034,7 +1043,7 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
       (X->method == 2 || (method_opt == 0 && plain_flat))) {
     // the estimated fastest grouping, and (up to 32,768 BG vertices) that or the
     // flat closure, which keeps a fifth's doubt
-    const TwoLevelPlan p = plan_two_level(X);
+    const TwoLevelPlan p = plan_two_level(X, level3_opt);
     if (p.cpg > 0 && (X->method == 2 || p.seconds < 0.8 * flat_seconds(X->V))) {
       X->method = 2;
       group_comps = p.cpg;
@@ -1331,8 +1340,7 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
       // (k / G would count a partial last group as a whole one, and the cut of
       // super-groups half as wide as they are)
       const double comps = X->group_bg ? (double)k / G : X->cpg;
-      const int32_t gpt = level3_opt > 0 ? std::min(level3_opt, G)
-                                         : bg2_plan(X, G, comps, X->V2, X->h_b2off.data()).gpt;
+      const int32_t gpt = bg2_plan(X, G, comps, X->V2, X->h_b2off.data(), level3_opt).gpt;
       if (gpt > 0) {
         X->gpt = gpt;
         X->nT = (G + gpt - 1) / gpt;

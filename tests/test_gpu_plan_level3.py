@@ -46,3 +46,12 @@ def test_level3_is_taken_where_it_pays(side, groups3):
     super-groups of 4."""
     st = build_and_check(side)
     assert st["groups3"] == groups3 and (st["v_bg3"] > 0) == (groups3 > 0)
+
+
+@pytest.mark.parametrize("level3,groups,groups3", [(-1, 10, 0), (16, 79, 5), (0, 20, 5)])
+def test_grouping_follows_the_callers_level3(level3, groups, groups3):
+    """Groups are chosen for the closure of BG2 that the caller asks for: without
+    level 3, half as many wider ones (3,600 BG2 vertices instead of 7,600), for
+    super-groups of 16 four times as many."""
+    st = build_and_check(200, level3_groups=level3)
+    assert (st["ngroups"], st["groups3"]) == (groups, groups3)
