@@ -39,10 +39,17 @@ spq_status fail(spq_status s, const std::string& msg) {
 // hipMalloc of memory freed a moment earlier costs about a second per 100 GB
 // on this device, so a freed index hands its blocks back to this cache and
 // the next build reuses them.  spq_release_cached_memory() returns them.
+// A build's scratch goes back when the build has queued its work: its blocks stay
+// live until the event behind that work has passed.
 struct Pool {
   std::mutex mu;
   std::unordered_map<void*, std::pair<int, size_t>> live;  // ptr -> (device, bytes)
   std::multimap<std::pair<int, size_t>, void*> idle;       // (device, bytes) -> ptr
+  struct Queued {
+    hipEvent_t done;
+    std::vector<void*> blocks;
+  };
+  std::vector<Queued> queued;
 };
 
 Pool& pool() {
@@ -55,8 +62,31 @@ size_t pool_round(size_t b) {
   return b < big ? (b + 255) & ~size_t(255) : (b + big - 1) & ~(big - 1);
 }
 
+// Blocks whose work is over become idle (wait: also those whose work is not, once it
+// is).  Caller holds the lock.
+void pool_collect(bool wait) {
+  Pool& P = pool();
+  for (size_t i = 0; i < P.queued.size();) {
+    Pool::Queued& q = P.queued[i];
+    if ((wait ? hipEventSynchronize(q.done) : hipEventQuery(q.done)) != hipSuccess) {
+      (void)hipGetLastError();
+      i++;
+      continue;
+    }
+    (void)hipEventDestroy(q.done);
+    for (void* p : q.blocks) {
+      auto it = P.live.find(p);
+      P.idle.insert({it->second, p});
+      P.live.erase(it);
+    }
+    std::swap(q, P.queued.back());
+    P.queued.pop_back();
+  }
+}
+
 void pool_drop_idle(int dev) {  // caller holds the lock
   Pool& P = pool();
+  pool_collect(true);
   for (auto it = P.idle.begin(); it != P.idle.end();) {
     if (dev < 0 || it->first.first == dev) {
       (void)hipFree(it->second);
@@ -74,6 +104,7 @@ hipError_t pool_alloc(void** out, size_t bytes) {
   bytes = pool_round(bytes);
   Pool& P = pool();
   std::lock_guard<std::mutex> lock(P.mu);
+  pool_collect(false);
   auto it = P.idle.lower_bound({dev, bytes});
   if (it != P.idle.end() && it->first.first == dev && it->first.second <= bytes + bytes / 4) {
     *out = it->second;
@@ -102,6 +133,26 @@ void pool_release(void* p) {
   }
   P.idle.insert({it->second, p});
   P.live.erase(it);
+}
+
+// Releases blocks that work queued on s may still use.  Without an event they are
+// waited for here.
+void pool_release_after(hipStream_t s, std::vector<void*> blocks) {
+  blocks.erase(std::remove(blocks.begin(), blocks.end(), nullptr), blocks.end());
+  if (blocks.empty()) return;
+  hipEvent_t done = nullptr;
+  hipError_t e = hipEventCreateWithFlags(&done, hipEventDisableTiming);
+  if (e == hipSuccess) e = hipEventRecord(done, s);
+  if (e == hipSuccess) {
+    Pool& P = pool();
+    std::lock_guard<std::mutex> lock(P.mu);
+    P.queued.push_back({done, std::move(blocks)});
+    return;
+  }
+  (void)hipGetLastError();
+  if (done) (void)hipEventDestroy(done);
+  (void)hipStreamSynchronize(s);
+  for (void* p : blocks) pool_release(p);
 }
 
 // Streams for the lookahead's side work, graph capture and host-array
@@ -346,11 +397,17 @@ static hipError_t graph_segment(spq_index* X, hipStream_t s, F&& body) {
 
 // Pair list of a composition (rows groups [0, rows) against groups [first,
 // G), first = the row group itself when `upper`), uploaded to *dev, and the
-// pairs per launch: the XT buffer holds one slot of slot_elems words per
-// pair of a launch, within 1/32 of the composition's output clamped to
-// [256 MiB, 4 GiB], at least one slot.
+// pairs per launch: each has a slot of slot_elems words of scratch (XT, statistics and
+// masks), all of a launch within a budget, at least one slot.  The budget is 1/32 of
+// the composition's output clamped to [256 MiB, 4 GiB], and where 2 GiB and the output
+// fit in a third of what is free, 2 GiB at least: six kernels per launch, each with its
+// own last wave (400,000 vertices in 128 groups with launches of 0.25, 0.5, 0.9, 1, 2
+// and 4 GiB build in 70.6, 63.8, 62.0, 60.2, 59.5 and 59.0 ms; 8,256 pairs of a 256 x 256
+// grid, 0.25 to 2: 11.3, 10.9, 10.6, 10.5).  Scratch that stays with the index for its
+// replays (`resident`) takes half of the output instead of the 2 GiB (a replay of 136
+// pairs, store 1.4 GiB, scratch 0.25 and 0.6 GiB: 9.42 and 9.21 ms).
 static hipError_t make_pairs(int32_t rows, int32_t G, bool upper, int64_t slot_elems,
-                             int64_t out_elems, int2** dev, int32_t* npairs, int32_t* chunk,
+                             int64_t out_elems, bool resident, int2** dev, int32_t* npairs, int32_t* chunk,
                              hipStream_t s, const std::vector<uint8_t>* swap = nullptr) {
   const int64_t count = upper ? (int64_t)rows * (2 * (int64_t)G - rows + 1) / 2 : (int64_t)rows * G;
   if (count > 0x7fffffff) return hipErrorOutOfMemory;  // pair list beyond int32 indexing
@@ -362,16 +419,11 @@ static hipError_t make_pairs(int32_t rows, int32_t G, bool upper, int64_t slot_e
     for (int32_t a2 = upper ? a1 : 0; a2 < G; a2++)
       h.push_back(swap && (*swap)[h.size()] ? make_int2(a2, a1 | spq::PAIR_SWAP) : make_int2(a1, a2));
   *npairs = (int32_t)h.size();
-  // pairs per launch: XT slots within 4 GiB, and the grid's y dimension.  Six kernels
-  // per launch, each with its own last wave: 2 GiB where that and the output fit in a
-  // third of what is free, else 1/32 of the output (400,000 vertices in 128 groups:
-  // launches of 0.25, 0.5, 0.9, 1, 2 and 4 GiB build in 70.6, 63.8, 62.0, 60.2, 59.5
-  // and 59.0 ms; 8,256 pairs of a 256 x 256 grid, 0.25 to 2: 11.3, 10.9, 10.6, 10.5).
   int64_t budget = std::min<int64_t>((int64_t)1 << 30, std::max<int64_t>((int64_t)1 << 26, out_elems / 32));
   size_t avail = 0, total = 0;
   if (hipMemGetInfo(&avail, &total) == hipSuccess &&
       (int64_t)(avail / sizeof(u32)) / 3 > out_elems + ((int64_t)1 << 29))
-    budget = std::max<int64_t>(budget, (int64_t)1 << 29);
+    budget = std::max(budget, std::min<int64_t>((int64_t)1 << 29, resident ? out_elems / 2 : INT64_MAX));
   const int64_t fit = budget / std::max<int64_t>(slot_elems, 1);
   *chunk = (int32_t)std::max<int64_t>(1, std::min<int64_t>({(int64_t)*npairs, fit, 65528}));
   hipError_t e = dalloc(dev, std::max<int64_t>(*npairs, 1));
@@ -392,6 +444,15 @@ static double batch_relax(int64_t P, int pivot, const std::vector<int32_t>& size
   double r = 0;
   for (int32_t v : sizes) r += spq::dense_fw_exec_relax(P / 128, 128, pivot, nullptr, (int)sizes.size(), v);
   return r;
+}
+
+// The composition's scratch, given back once the work queued on s is over (a captured
+// index keeps it for its replays; the counters stay).
+static void mp_release(spq_index* X, hipStream_t s) {
+  if (X->graph) return;
+  pool_release_after(s, {X->XT, X->mp.stats, X->mp.mask, X->XT3, X->mp3.stats, X->mp3.mask});
+  X->XT = X->XT3 = nullptr;
+  X->mp = X->mp3 = spq::MpWork{};
 }
 
 // Scratch of the composition for `chunk` pairs per launch.
@@ -493,7 +554,7 @@ static spq_status build_share(spq_index* X, spq::HierArgs& ha, int64_t m, bool p
   for (int32_t a1 = 0; a1 < X->share_groups; a1++)
     for (int32_t a2 = 0; a2 < G; a2++)
       swap[(size_t)a1 * G + a2] = a1 != a2 && cost(a2, a1) < cost(a1, a2);
-  HIP_TRY(make_pairs(X->share_groups, G, false, mp_slot_words(X->m2pmax, Vgp), X->h_elems, &X->plist,
+  HIP_TRY(make_pairs(X->share_groups, G, false, mp_slot_words(X->m2pmax, Vgp), X->h_elems, false, &X->plist,
                      &X->npairs, &X->chunk, s, &swap));
   HIP_TRY(dalloc(&X->XT, (int64_t)X->chunk * X->m2pmax * Vgp));
   HIP_TRY(mp_work_alloc(X, &X->mp, X->m2pmax, Vgp, X->chunk));
@@ -1324,6 +1385,7 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
       spq_status ss = build_share(X, ha, m, profile, level3_opt, s);
       if (ss != SPQ_OK) return guard(ss);
       TRY(hipEventRecord(X->ev[4], s));
+      mp_release(X, s);
       *out = X;
       return SPQ_OK;
     }
@@ -1358,8 +1420,8 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
     // executed relaxations of level 2 (its BG2 closure is counted with level 3)
     if (X->V2p > 0 && X->nT == 0)
       X->relax_bg_exec += spq::dense_fw_exec_relax(X->V2p / 128, 128, X->cpivot);
-    TRY(make_pairs(G, G, true, mp_slot_words(X->m2pmax, Vgp), X->h_elems, &X->plist, &X->npairs,
-                   &X->chunk, s));
+    TRY(make_pairs(G, G, true, mp_slot_words(X->m2pmax, Vgp), X->h_elems, X->graph, &X->plist,
+                   &X->npairs, &X->chunk, s));
     X->inner_launches = (X->npairs + X->chunk - 1) / X->chunk;
     if (profile) {
       X->prof.resize(2 * X->inner_launches);
@@ -1440,7 +1502,7 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
                          hipMemcpyHostToDevice, s));
       TRY(dalloc(&X->R3, (int64_t)nT * X->m3pmax * V3gp));
       int32_t np3 = 0, ch3 = 0;
-      TRY(make_pairs(nT, nT, true, mp_slot_words(X->m3pmax, V3gp), X->V2p * X->V2p / 2, &X->plist3,
+      TRY(make_pairs(nT, nT, true, mp_slot_words(X->m3pmax, V3gp), X->V2p * X->V2p / 2, X->graph, &X->plist3,
                      &np3, &ch3, s));
       TRY(dalloc(&X->XT3, (int64_t)ch3 * X->m3pmax * V3gp));
       TRY(mp_work_alloc(X, &X->mp3, X->m3pmax, V3gp, ch3));
@@ -1457,6 +1519,7 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
       }));
     }
     TRY(hipEventRecord(X->ev[4], s));
+    mp_release(X, s);
     spq_status cs = certify(X, s);
     if (cs != SPQ_OK) return guard(cs);
     *out = X;
