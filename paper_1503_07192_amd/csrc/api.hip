@@ -197,6 +197,46 @@ void stream_give(int dev, hipStream_t s) {
   P.idle.insert({dev, s});
 }
 
+// Pinned words where a build or replay leaves what it counted, so that
+// spq_index_stats reads it without a copy: 64-byte slots cut from 4-KiB blocks, handed
+// back by freed indexes; the blocks go when no slot is taken
+// (spq_release_cached_memory).
+struct PinnedPool {
+  std::mutex mu;
+  std::vector<unsigned long long*> idle, blocks;
+};
+constexpr size_t PIN_WORDS = 8, PIN_SLOTS = 64;
+
+PinnedPool& pinned_pool() {
+  static PinnedPool* p = new PinnedPool();  // lives until the process ends
+  return *p;
+}
+
+hipError_t pinned_take(unsigned long long** out) {
+  PinnedPool& P = pinned_pool();
+  std::lock_guard<std::mutex> lock(P.mu);
+  if (P.idle.empty()) {
+    void* b = nullptr;
+    hipError_t e = hipHostMalloc(&b, sizeof(unsigned long long) * PIN_WORDS * PIN_SLOTS,
+                                 hipHostMallocMapped | hipHostMallocPortable);
+    if (e != hipSuccess) return e;
+    P.blocks.push_back(static_cast<unsigned long long*>(b));
+    for (size_t i = 0; i < PIN_SLOTS; i++) P.idle.push_back(P.blocks.back() + i * PIN_WORDS);
+  }
+  *out = P.idle.back();
+  P.idle.pop_back();
+  std::fill(*out, *out + PIN_WORDS, 0ull);
+  return hipSuccess;
+}
+
+// nothing queued may still write to it
+void pinned_give(unsigned long long* p) {
+  if (!p) return;
+  PinnedPool& P = pinned_pool();
+  std::lock_guard<std::mutex> lock(P.mu);
+  P.idle.push_back(p);
+}
+
 template <typename T>
 hipError_t dalloc(T** p, int64_t count) {
   *p = nullptr;
@@ -290,7 +330,8 @@ struct spq_index {
   u32 *M3 = nullptr, *R3 = nullptr, *XT3 = nullptr, *BG3 = nullptr;
   spq::MpWork mp, mp3;                  // composition scratch, level 2 and 3
   u32* fw_flags = nullptr;  // the dense closures' scratch flags
-  unsigned long long* mp_exec = nullptr;  // executed relaxations of the products
+  unsigned long long* mp_exec = nullptr;  // executed relaxations of the products: counters,
+  unsigned long long* counted = nullptr;  //   and (pinned) what the last build or replay counted
   // share mode
   int32_t share_comps = 0, share_groups = 0, S2 = 0, bf_rounds = 0;
   int64_t S2p = 0;
@@ -366,6 +407,7 @@ struct spq_index {
                     b3off, flag3, M3, R3, XT3, BG3, plist, plist3, rowptr, adj, adeg, w_copy, meta,
                     mp.stats, mp.mask, mp3.stats, mp3.mask, mp_exec, fw_flags};
     for (void* p : ptrs) pool_release(p);
+    pinned_give(counted);
   }
 };
 
@@ -456,10 +498,15 @@ static void mp_release(spq_index* X, hipStream_t s) {
 }
 
 // Scratch of the composition for `chunk` pairs per launch.
-static hipError_t mp_work_alloc(spq_index* X, spq::MpWork* w, int32_t Kp, int32_t Vp, int32_t chunk) {
+static hipError_t mp_work_alloc(spq_index* X, spq::MpWork* w, int32_t Kp, int32_t Vp, int32_t chunk,
+                                hipStream_t s) {
   hipError_t e = dalloc(&w->stats, chunk * spq::mp_stats_words(Kp, Vp));
   if (e == hipSuccess) e = dalloc(&w->mask, chunk * spq::mp_mask_words(Kp, Vp));
-  if (e == hipSuccess && !X->mp_exec) e = dalloc(&X->mp_exec, spq::MP_EXEC);
+  if (e == hipSuccess && !X->mp_exec) {  // (cleared here once, then by every launch_mp_counts)
+    e = pinned_take(&X->counted);
+    if (e == hipSuccess) e = dalloc(&X->mp_exec, spq::MP_EXEC);
+    if (e == hipSuccess) e = hipMemsetAsync(X->mp_exec, 0, sizeof(*X->mp_exec) * spq::MP_EXEC, s);
+  }
   w->exec = X->mp_exec;
   return e;
 }
@@ -557,7 +604,7 @@ static spq_status build_share(spq_index* X, spq::HierArgs& ha, int64_t m, bool p
   HIP_TRY(make_pairs(X->share_groups, G, false, mp_slot_words(X->m2pmax, Vgp), X->h_elems, false, &X->plist,
                      &X->npairs, &X->chunk, s, &swap));
   HIP_TRY(dalloc(&X->XT, (int64_t)X->chunk * X->m2pmax * Vgp));
-  HIP_TRY(mp_work_alloc(X, &X->mp, X->m2pmax, Vgp, X->chunk));
+  HIP_TRY(mp_work_alloc(X, &X->mp, X->m2pmax, Vgp, X->chunk, s));
   HIP_TRY(dalloc(&X->A, (int64_t)NB * BP * BP));
   // the Bellman-Ford matrix carries 128 spare rows: a row tile may start at
   // the last block's last level-2 id
@@ -700,7 +747,6 @@ static spq_status build_share(spq_index* X, spq::HierArgs& ha, int64_t m, bool p
   int64_t rows3 = 0;
   const bool pruned = spq::share_final_words(blk, b3, X->S2p, &rows3) <= X->h_elems &&
                       rows3 <= (int64_t)G * X->S2p * X->m2pmax && NB <= 65528;
-  HIP_TRY(spq::launch_mp_zero(X->mp, s));
   HIP_TRY(spq::launch_share_final(ha, blk, b3, pruned ? X->BG2 : nullptr, X->H, s));
   for (int32_t t = 0; t < NB && !pruned; t++)
     if (X->h_sbm[t] > 0)
@@ -713,6 +759,7 @@ static spq_status build_share(spq_index* X, spq::HierArgs& ha, int64_t m, bool p
     ha.evt = X->prof.data();
   }
   HIP_TRY(spq::launch_share_compose(ha, X->DT, s));
+  HIP_TRY(spq::launch_mp_counts(X->mp, X->counted, s));
   return SPQ_OK;
 }
 
@@ -1431,7 +1478,7 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
     TRY(hipMemcpyAsync(X->b2off, X->h_b2off.data(), sizeof(int32_t) * (G + 1), hipMemcpyHostToDevice, s));
     TRY(dalloc(&X->R, (int64_t)G * X->m2pmax * Vgp));
     TRY(dalloc(&X->XT, (int64_t)X->chunk * X->m2pmax * Vgp));
-    TRY(mp_work_alloc(X, &X->mp, X->m2pmax, Vgp, X->chunk));
+    TRY(mp_work_alloc(X, &X->mp, X->m2pmax, Vgp, X->chunk, s));
     ha.work = X->mp;
     if (X->V2p > 0) TRY(dalloc(&X->BG2, X->V2p * X->V2p));
     TRY(dalloc(&X->H, X->h_elems));
@@ -1449,10 +1496,10 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
     }
     if (X->nT == 0) {
       TRY(graph_segment(X, s, [&](hipStream_t st) -> hipError_t {
-        hipError_t e = spq::launch_mp_zero(X->mp, st);
-        if (e == hipSuccess) e = spq::launch_hier_level2_prep(ha, true, st);
+        hipError_t e = spq::launch_hier_level2_prep(ha, true, st);
         if (e == hipSuccess) e = spq::launch_hier_level2_close(ha, st);
         if (e == hipSuccess) e = spq::launch_hier_level2_compose(ha, st);
+        if (e == hipSuccess) e = spq::launch_mp_counts(X->mp, X->counted, st);
         return e;
       }));
     } else {
@@ -1505,16 +1552,16 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
       TRY(make_pairs(nT, nT, true, mp_slot_words(X->m3pmax, V3gp), X->V2p * X->V2p / 2, X->graph, &X->plist3,
                      &np3, &ch3, s));
       TRY(dalloc(&X->XT3, (int64_t)ch3 * X->m3pmax * V3gp));
-      TRY(mp_work_alloc(X, &X->mp3, X->m3pmax, V3gp, ch3));
+      TRY(mp_work_alloc(X, &X->mp3, X->m3pmax, V3gp, ch3, s));
       la.work = X->mp3;
       la.plist = X->plist3; la.npairs = np3; la.chunk = ch3;
       if (X->V3p > 0) TRY(dalloc(&X->BG3, X->V3p * X->V3p));
       la.V3 = X->V3; la.V3p = X->V3p; la.m3pmax = X->m3pmax; la.b3off = X->b3off; la.R3 = X->R3;
       la.XT3 = X->XT3; la.BG3 = X->BG3; la.side = ha.side; la.sync = ha.sync;
       TRY(graph_segment(X, s, [&](hipStream_t st) -> hipError_t {
-        hipError_t e = spq::launch_mp_zero(X->mp, st);
-        if (e == hipSuccess) e = spq::launch_level3_b(la, st);
+        hipError_t e = spq::launch_level3_b(la, st);
         if (e == hipSuccess) e = spq::launch_hier_level2_compose(ha, st);
+        if (e == hipSuccess) e = spq::launch_mp_counts(X->mp, X->counted, st);
         return e;
       }));
     }
@@ -1817,13 +1864,9 @@ spq_status spq_index_stats(const spq_index* X, spq_stats* st) {
   st->v_bg3 = X->V3;
   if (X->method == 2) st->v_bg_padded = X->Vgp;
   HIP_TRY(hipEventSynchronize(X->ev[4]));
-  if (X->mp_exec) {  // the products' relaxations, counted on the device
-    unsigned long long h[spq::MP_EXEC];
-    HIP_TRY(hipMemcpy(h, X->mp_exec, sizeof(h), hipMemcpyDeviceToHost));
-    for (int i = 0; i < spq::MP_EXEC; i++) {
-      st->relax_bg_exec += (double)h[i];
-      if (i >= spq::MP_EXEC / 2) st->relax_dominant += (double)h[i];
-    }
+  if (X->counted) {  // the products' relaxations, counted on the device
+    st->relax_bg_exec += (double)X->counted[0];
+    st->relax_dominant += (double)X->counted[1];
   }
   for (size_t i = 0; i + 1 < X->prof.size(); i += 2) {
     float ms = 0;
@@ -1893,6 +1936,15 @@ void spq_release_cached_memory(void) {
     Pool& P = pool();
     std::lock_guard<std::mutex> lock(P.mu);
     pool_drop_idle(-1);
+  }
+  {
+    PinnedPool& P = pinned_pool();
+    std::lock_guard<std::mutex> lock(P.mu);
+    if (P.idle.size() == P.blocks.size() * PIN_SLOTS) {
+      for (auto* b : P.blocks) (void)hipHostFree(b);
+      P.idle.clear();
+      P.blocks.clear();
+    }
   }
   StreamPool& S = stream_pool();
   std::lock_guard<std::mutex> lock(S.mu);

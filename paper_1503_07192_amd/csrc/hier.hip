@@ -1103,8 +1103,17 @@ __global__ __launch_bounds__(64) SPQ_MP_ATTR void k_mp_prod(MpArgs a) {
   }
 }
 
-__global__ void k_zero_u64(int n, unsigned long long* p) {
-  if ((int)threadIdx.x < n) p[threadIdx.x] = 0ull;
+// What the products counted: all of it and the level-2 second products' part into
+// `out` (pinned host memory), the counters cleared for the next replay.
+__global__ __launch_bounds__(64) void k_mp_counts(unsigned long long* exec, unsigned long long* out) {
+  unsigned long long n = (int)threadIdx.x < MP_EXEC ? exec[threadIdx.x] : 0ull;
+  if ((int)threadIdx.x < MP_EXEC) exec[threadIdx.x] = 0ull;
+  for (int o = 8; o > 0; o >>= 1) n += __shfl_xor(n, o);
+  const unsigned long long dominant = __shfl(n, MP_EXEC / 2);
+  if (threadIdx.x == 0) {
+    out[0] = n + dominant;
+    out[1] = dominant;
+  }
 }
 
 // ------------------------------------------------------------- level 3
@@ -1676,8 +1685,9 @@ static hipError_t compose_level2(const HierArgs& a, const int32_t* bglabel, u32*
   return hipGetLastError();
 }
 
-hipError_t launch_mp_zero(const MpWork& w, hipStream_t s) {
-  k_zero_u64<<<1, 64, 0, s>>>(MP_EXEC, w.exec);
+hipError_t launch_mp_counts(const MpWork& w, unsigned long long* out, hipStream_t s) {
+  static_assert(MP_EXEC == 32, "two times sixteen counters, summed by sixteen lanes");
+  k_mp_counts<<<1, 64, 0, s>>>(w.exec, out);
   return hipGetLastError();
 }
 

@@ -90,7 +90,9 @@ constexpr int MP_EXEC = 32;
 // Kp: rows per XT slot (a multiple of 128), Vp: their length (likewise)
 int64_t mp_stats_words(int32_t Kp, int32_t Vp);
 int64_t mp_mask_words(int32_t Kp, int32_t Vp);
-hipError_t launch_mp_zero(const MpWork& w, hipStream_t s);  // clears the counters
+// after the last product: out[0] all that was counted, out[1] the level-2 second
+// products' part; clears the counters
+hipError_t launch_mp_counts(const MpWork& w, unsigned long long* out, hipStream_t s);
 
 // Two-level BG (hier.hip).
 struct HierArgs {
