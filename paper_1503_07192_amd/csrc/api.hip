@@ -297,7 +297,7 @@ struct spq_index {
   u32 h_marks[32] = {};  // boundary vertices by mark (k_edges_scan)
   unsigned long long *sumc = nullptr, *total = nullptr;
   // one block each: err, total, the marks' counts, sumc, cnt, nb (cleared and read back
-  // in one piece); gT, moff, off, bgoff, P, order, grp, gbg0, gV, fill (uploaded in one)
+  // in one piece), exec, fw_flags (cleared with them); gT, moff, off, bgoff, P, order, grp, gbg0, gV, fill (uploaded in one)
   unsigned long long* counts = nullptr;
   int32_t* plan = nullptr;
   std::vector<int32_t> h_plan;
@@ -329,9 +329,11 @@ struct spq_index {
   int32_t npairs = 0, chunk = 0;
   u32 *M3 = nullptr, *R3 = nullptr, *XT3 = nullptr, *BG3 = nullptr;
   spq::MpWork mp, mp3;                  // composition scratch, level 2 and 3
-  u32* fw_flags = nullptr;  // the dense closures' scratch flags
-  unsigned long long* mp_exec = nullptr;  // executed relaxations of the products: counters,
-  unsigned long long* counted = nullptr;  //   and (pinned) what the last build or replay counted
+  u32* fw_flags = nullptr;  // the dense closures' scratch flags (in counts)
+  spq::FwWork fw_comp() const { return {fw_flags, exec + spq::MP_EXEC}; }
+  spq::FwWork fw_bg() const { return {fw_flags, exec + spq::MP_EXEC + 1}; }
+  unsigned long long* exec = nullptr;     // counters of executed relaxations (in counts), and
+  unsigned long long* counted = nullptr;  //   (pinned) what the last build or replay counted
   // share mode
   int32_t share_comps = 0, share_groups = 0, S2 = 0, bf_rounds = 0;
   int64_t S2p = 0;
@@ -405,7 +407,7 @@ struct spq_index {
                     sb_list, sb_nlist, sb_rank, sb_nrank, sb_m, sb_n, sb_A3, sb_Aout, xe, xcount, boff,
                     bsize, bfirst, gblk, eu_own, ev_own, w_own, tbase, tsize, b3list, b3rank, m3,
                     b3off, flag3, M3, R3, XT3, BG3, plist, plist3, rowptr, adj, adeg, w_copy, meta,
-                    mp.stats, mp.mask, mp3.stats, mp3.mask, mp_exec, fw_flags};
+                    mp.stats, mp.mask, mp3.stats, mp3.mask};
     for (void* p : ptrs) pool_release(p);
     pinned_give(counted);
   }
@@ -498,16 +500,10 @@ static void mp_release(spq_index* X, hipStream_t s) {
 }
 
 // Scratch of the composition for `chunk` pairs per launch.
-static hipError_t mp_work_alloc(spq_index* X, spq::MpWork* w, int32_t Kp, int32_t Vp, int32_t chunk,
-                                hipStream_t s) {
+static hipError_t mp_work_alloc(spq_index* X, spq::MpWork* w, int32_t Kp, int32_t Vp, int32_t chunk) {
   hipError_t e = dalloc(&w->stats, chunk * spq::mp_stats_words(Kp, Vp));
   if (e == hipSuccess) e = dalloc(&w->mask, chunk * spq::mp_mask_words(Kp, Vp));
-  if (e == hipSuccess && !X->mp_exec) {  // (cleared here once, then by every launch_mp_counts)
-    e = pinned_take(&X->counted);
-    if (e == hipSuccess) e = dalloc(&X->mp_exec, spq::MP_EXEC);
-    if (e == hipSuccess) e = hipMemsetAsync(X->mp_exec, 0, sizeof(*X->mp_exec) * spq::MP_EXEC, s);
-  }
-  w->exec = X->mp_exec;
+  w->exec = X->exec;
   return e;
 }
 
@@ -604,7 +600,7 @@ static spq_status build_share(spq_index* X, spq::HierArgs& ha, int64_t m, bool p
   HIP_TRY(make_pairs(X->share_groups, G, false, mp_slot_words(X->m2pmax, Vgp), X->h_elems, false, &X->plist,
                      &X->npairs, &X->chunk, s, &swap));
   HIP_TRY(dalloc(&X->XT, (int64_t)X->chunk * X->m2pmax * Vgp));
-  HIP_TRY(mp_work_alloc(X, &X->mp, X->m2pmax, Vgp, X->chunk, s));
+  HIP_TRY(mp_work_alloc(X, &X->mp, X->m2pmax, Vgp, X->chunk));
   HIP_TRY(dalloc(&X->A, (int64_t)NB * BP * BP));
   // the Bellman-Ford matrix carries 128 spare rows: a row tile may start at
   // the last block's last level-2 id
@@ -643,7 +639,8 @@ static spq_status build_share(spq_index* X, spq::HierArgs& ha, int64_t m, bool p
   ha.share_groups = X->share_groups; ha.S2 = X->S2; ha.S2p = X->S2p; ha.DT = X->DT;
   ha.D2t = X->DT; ha.d2tld = X->S2p;
   ha.xe = X->xe; ha.xcount = X->xcount;
-  const spq::ShareBlocks blk{NB, BP, multi, X->bfirst, X->gblk, X->boff, X->bsize, X->A};
+  const spq::ShareBlocks blk{NB, BP, multi, X->bfirst, X->gblk, X->boff, X->bsize,
+                             X->h_bsize.data(), X->A};
   HIP_TRY(spq::launch_share_prepare(ha, blk, s));
   HIP_TRY(spq::launch_share_b3_lists(ha, blk, X->sb_flag, X->sb_flagn, X->sb_list, X->sb_nlist,
                                      X->sb_rank, X->sb_nrank, X->sb_m, X->sb_n, s));
@@ -759,7 +756,7 @@ static spq_status build_share(spq_index* X, spq::HierArgs& ha, int64_t m, bool p
     ha.evt = X->prof.data();
   }
   HIP_TRY(spq::launch_share_compose(ha, X->DT, s));
-  HIP_TRY(spq::launch_mp_counts(X->mp, X->counted, s));
+  HIP_TRY(spq::launch_counts(X->exec, X->counted, s));
   return SPQ_OK;
 }
 
@@ -1081,15 +1078,18 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
 
   // ---- boundary detection and sizes (device), then the plan (host)
   constexpr int64_t SUMS = 18;  // words before sumc
-  TRY(dalloc(&X->counts, SUMS + 2 * (int64_t)k));
+  constexpr int64_t TAIL = spq::EXEC_WORDS + spq::FW_FLAGS / 2;  // words of exec and fw_flags
+  TRY(pinned_take(&X->counted));
+  TRY(dalloc(&X->counts, SUMS + 2 * (int64_t)k + TAIL));
   X->err = reinterpret_cast<u32*>(X->counts);
   X->total = X->counts + 1;
   X->sumc = X->counts + SUMS;
   X->cnt = reinterpret_cast<int32_t*>(X->sumc + k);
   X->nb = X->cnt + k;
+  X->exec = X->sumc + 2 * (int64_t)k;
+  X->fw_flags = reinterpret_cast<u32*>(X->exec + spq::EXEC_WORDS);
   TRY(dalloc(&X->flag, n));
-  TRY(dalloc(&X->fw_flags, spq::FW_FLAGS));
-  TRY(hipMemsetAsync(X->counts, 0, sizeof(unsigned long long) * (SUMS + 2 * (size_t)k), s));
+  TRY(hipMemsetAsync(X->counts, 0, sizeof(unsigned long long) * (SUMS + 2 * (size_t)k + TAIL), s));
   TRY(hipMemsetAsync(X->flag, 0, sizeof(u32) * (size_t)n, s));
   spq::PartArgs pa{};
   pa.n = n; pa.k = k; pa.m = m;
@@ -1351,13 +1351,13 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
       for (int32_t b = 0; b < X->nbig && e == hipSuccess; b++) {
         const int32_t c = X->h_order[b];
         e = spq::launch_dense_fw(X->M + X->h_moff[c], X->h_P[c], 128, X->h_P[c] / 128, st, nullptr,
-                                 inner_kc, X->cpivot, X->fw_flags);
+                                 inner_kc, X->cpivot, X->fw_comp());
       }
     } else {
       for (int32_t i = 0; i < X->nbig && e == hipSuccess;) {
         const int32_t i2 = big_run(X, i), P = X->h_P[X->h_order[i]];
         e = spq::launch_dense_fw_list(X->M, P, 128, P / 128, i2 - i, X->order + i, X->moff, st, inner_kc,
-                                      X->cpivot, X->fw_flags);
+                                      X->cpivot, X->fw_comp());
         i = i2;
       }
     }
@@ -1380,7 +1380,7 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
   // ---- Phase 3: BG and its all-pairs distances
   if (X->method == 2) {
     spq::HierArgs ha{};
-    ha.fw_flags = X->fw_flags;
+    ha.fw = X->fw_bg();
     const int32_t G = X->ngroups, V = X->V, Vgp = X->Vgp;
     TRY(dalloc(&X->Mg, (int64_t)G * Vgp * Vgp));
     TRY(dalloc(&X->flag2, V));
@@ -1398,7 +1398,7 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
     ha.V = V; ha.ngroups = G; ha.Vgp = Vgp; ha.m = m; ha.kc = inner_kc; ha.pivot = X->cpivot;
     ha.eu = eu; ha.ev = ev; ha.w = w; ha.comp = X->comp; ha.local = X->local; ha.bgoff = X->bgoff;
     ha.nb = X->nb; ha.bgcomp = X->bgcomp; ha.bglocal = X->bglocal; ha.P = X->P; ha.moff = X->moff;
-    ha.M = X->M; ha.grp = X->grp; ha.gbg0 = X->gbg0; ha.gV = X->gV; ha.bgrow = X->bgrow;
+    ha.M = X->M; ha.grp = X->grp; ha.gbg0 = X->gbg0; ha.gV = X->gV; ha.h_gV = X->h_gV.data(); ha.bgrow = X->bgrow;
     ha.bgnb = X->bgnb; ha.bggrp = X->bggrp; ha.Mg = X->Mg; ha.flag2 = X->flag2; ha.b2list = X->b2list;
     ha.b2rank = X->b2rank; ha.m2 = X->m2;
     // the closures of this path (the groups' and super-groups' batches, BG2
@@ -1478,7 +1478,7 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
     TRY(hipMemcpyAsync(X->b2off, X->h_b2off.data(), sizeof(int32_t) * (G + 1), hipMemcpyHostToDevice, s));
     TRY(dalloc(&X->R, (int64_t)G * X->m2pmax * Vgp));
     TRY(dalloc(&X->XT, (int64_t)X->chunk * X->m2pmax * Vgp));
-    TRY(mp_work_alloc(X, &X->mp, X->m2pmax, Vgp, X->chunk, s));
+    TRY(mp_work_alloc(X, &X->mp, X->m2pmax, Vgp, X->chunk));
     ha.work = X->mp;
     if (X->V2p > 0) TRY(dalloc(&X->BG2, X->V2p * X->V2p));
     TRY(dalloc(&X->H, X->h_elems));
@@ -1499,7 +1499,7 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
         hipError_t e = spq::launch_hier_level2_prep(ha, true, st);
         if (e == hipSuccess) e = spq::launch_hier_level2_close(ha, st);
         if (e == hipSuccess) e = spq::launch_hier_level2_compose(ha, st);
-        if (e == hipSuccess) e = spq::launch_mp_counts(X->mp, X->counted, st);
+        if (e == hipSuccess) e = spq::launch_counts(X->exec, X->counted, st);
         return e;
       }));
     } else {
@@ -1517,12 +1517,12 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
       // level-3 boundary flags depend on the edges only and are only ever set
       TRY(hipMemsetAsync(X->flag3, 0, X->V2, s));
       spq::L3Args la{};
-      la.fw_flags = X->fw_flags;
+      la.fw = X->fw_bg();
       la.nT = nT; la.gpt = X->gpt; la.V3gp = V3gp; la.kc = inner_kc; la.pivot = X->cpivot; la.m = m; la.V2p = X->V2p;
       la.eu = eu; la.ev = ev; la.w = w; la.comp = X->comp; la.local = X->local; la.bgoff = X->bgoff;
       la.grp = X->grp; la.b2off = X->b2off; la.b2rank = X->b2rank; la.BG2 = X->BG2;
       la.ngroups = X->ngroups; la.Vgp = X->Vgp; la.Mg = X->Mg; la.b2list = X->b2list;
-      la.tbase = X->tbase; la.tsize = X->tsize; la.M3 = X->M3; la.flag3 = X->flag3;
+      la.tbase = X->tbase; la.tsize = X->tsize; la.h_tsize = X->h_tsize.data(); la.M3 = X->M3; la.flag3 = X->flag3;
       la.b3list = X->b3list; la.b3rank = X->b3rank; la.m3 = X->m3;
       la.side = ha.side; la.sync = ha.sync;
       TRY(graph_segment(X, s, [&](hipStream_t st) -> hipError_t {
@@ -1552,7 +1552,7 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
       TRY(make_pairs(nT, nT, true, mp_slot_words(X->m3pmax, V3gp), X->V2p * X->V2p / 2, X->graph, &X->plist3,
                      &np3, &ch3, s));
       TRY(dalloc(&X->XT3, (int64_t)ch3 * X->m3pmax * V3gp));
-      TRY(mp_work_alloc(X, &X->mp3, X->m3pmax, V3gp, ch3, s));
+      TRY(mp_work_alloc(X, &X->mp3, X->m3pmax, V3gp, ch3));
       la.work = X->mp3;
       la.plist = X->plist3; la.npairs = np3; la.chunk = ch3;
       if (X->V3p > 0) TRY(dalloc(&X->BG3, X->V3p * X->V3p));
@@ -1561,7 +1561,7 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
       TRY(graph_segment(X, s, [&](hipStream_t st) -> hipError_t {
         hipError_t e = spq::launch_level3_b(la, st);
         if (e == hipSuccess) e = spq::launch_hier_level2_compose(ha, st);
-        if (e == hipSuccess) e = spq::launch_mp_counts(X->mp, X->counted, st);
+        if (e == hipSuccess) e = spq::launch_counts(X->exec, X->counted, st);
         return e;
       }));
     }
@@ -1604,12 +1604,12 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
     if (e != hipSuccess) return e;
     if (la)
       e = spq::launch_dense_fw_lookahead(X->BG, X->Vp, tile, X->Vp / tile, st, X->side, X->la_sync,
-                                         pev, inner_kc, X->pivot, X->part1, X->fw_flags);
+                                         pev, inner_kc, X->pivot, X->part1, X->fw_bg());
     else
-      e = spq::launch_dense_fw(X->BG, X->Vp, tile, X->Vp / tile, st, pev, inner_kc, X->pivot, X->fw_flags);
+      e = spq::launch_dense_fw(X->BG, X->Vp, tile, X->Vp / tile, st, pev, inner_kc, X->pivot, X->fw_bg());
     if (e != hipSuccess) return e;
     return spq::launch_flat_store(V, X->Vp, X->BG, X->bgcomp, X->bgoff, X->nb, X->grp, X->gbg0,
-                                  X->bgrow, X->bgnb, X->bggrp, X->bglocal, X->H, st);
+                                  X->bgrow, X->bgnb, X->bggrp, X->bglocal, X->H, X->exec, X->counted, st);
   }));
   TRY(hipEventRecord(X->ev[4], s));
 #undef TRY
@@ -1864,10 +1864,10 @@ spq_status spq_index_stats(const spq_index* X, spq_stats* st) {
   st->v_bg3 = X->V3;
   if (X->method == 2) st->v_bg_padded = X->Vgp;
   HIP_TRY(hipEventSynchronize(X->ev[4]));
-  if (X->counted) {  // the products' relaxations, counted on the device
-    st->relax_bg_exec += (double)X->counted[0];
-    st->relax_dominant += (double)X->counted[1];
-  }
+  // the products' and the squarings' relaxations, counted on the device
+  st->relax_bg_exec += (double)X->counted[0];
+  st->relax_dominant += (double)X->counted[1];
+  st->relax_comp_exec += (double)X->counted[2];
   for (size_t i = 0; i + 1 < X->prof.size(); i += 2) {
     float ms = 0;
     HIP_TRY(hipEventElapsedTime(&ms, X->prof[i], X->prof[i + 1]));

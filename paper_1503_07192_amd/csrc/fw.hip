@@ -35,7 +35,7 @@ struct FwAt {
   int64_t gstride;
   const int32_t* order;
   const int64_t* moff;
-  u32* flags;  // FW_FLAGS words (any content), or null: see k_fw_square
+  FwWork work;  // or none: see k_fw_square
   // null, or the vertices of each matrix, `first` of them before A's first row: the
   // tiles past them are padding, which no closure changes, and are left out.  Groups
   // differ in size (a 400,000-vertex graph: 128 of 930 vertices on average in 1,152
@@ -269,17 +269,22 @@ __global__ __launch_bounds__(256, KC * T <= 2048 ? 4 : 2) void k_fw_inner(u32* _
 // The next round's closure runs beside this round's interior and is the longer
 // of the two where matrices are small: its waves go first on a SIMD they share
 // (13 -> 9 us a launch).  Both: the closures of a 27,900-vertex BG in three levels
-// 1.5 of 14.0 ms less, a 400,000-vertex graph's 1.6 of 74.2.
-__global__ __launch_bounds__(256) void k_fw_square(u32* A, int64_t ld, int nb, FwAt at, int q, int nq) {
+// 1.5 of 14.0 ms less, a 400,000-vertex graph's 1.6 of 74.2.  relax: what this squaring
+// executes in the whole batch, counted if it runs.
+__global__ __launch_bounds__(256) void k_fw_square(u32* A, int64_t ld, int nb, FwAt at, int q, int nq,
+                                                   unsigned long long relax) {
   constexpr int KC = 16;
   __shared__ __attribute__((aligned(16))) u32 sm[4][2][2][KC * 32];
-  if (at.flags) {
-    if (blockIdx.x == 0 && blockIdx.y == 0) {
-      if (q == 0 && threadIdx.x >= 1 && (int)threadIdx.x < nq) at.flags[threadIdx.x] = 0;
-      if (q == 2 && threadIdx.x == 0) at.flags[0] = 0;
+  u32* flags = at.work.flags;
+  const bool first = blockIdx.x == 0 && blockIdx.y == 0;
+  if (flags) {
+    if (first) {
+      if (q == 0 && threadIdx.x >= 1 && (int)threadIdx.x < nq) flags[threadIdx.x] = 0;
+      if (q == 2 && threadIdx.x == 0) flags[0] = 0;
     }
-    if (q > 0 && at.flags[q - 1] == 0) return;
+    if (q > 0 && flags[q - 1] == 0) return;
   }
+  if (at.work.ran && first && threadIdx.x == 0) atomicAdd(at.work.ran, relax);
   __builtin_amdgcn_s_setprio(3);
   A = fw_at(A, at);
   int bi, bj;
@@ -343,7 +348,7 @@ __global__ __launch_bounds__(256) void k_fw_square(u32* A, int64_t ld, int nb, F
     v.z = min(v.z, x.z);
     v.w = min(v.w, x.w);
   }
-  if (at.flags && (v.x != old.x || v.y != old.y || v.z != old.z || v.w != old.w)) at.flags[q] = 1;
+  if (flags && (v.x != old.x || v.y != old.y || v.z != old.z || v.w != old.w)) flags[q] = 1;
   *reinterpret_cast<uint4*>(Cp) = v;
   if (bi == bj) return;
   u32* tr = red + 4096;  // [32][33]
@@ -416,6 +421,7 @@ static int64_t inner_count(int nt, FwBlock b, int part, int nn) {
 struct FwBatch {
   int batch;
   FwAt at;
+  const int32_t* hsizes;  // at.sizes on the host
 };
 
 template <int T, int KC>
@@ -439,11 +445,21 @@ static bool fw_by_squaring(int tile, int pt, int batch) {
   return pt > 1 && tri_count(pt * tile / 32) * batch <= SQUARE_WGS;
 }
 
+// Relaxations of one squaring of a block of n vertices, of which the first `size` (< 0:
+// all) are not padding.
+static double square_relax(int64_t n, int64_t size) {
+  const int64_t used = size < 0 ? n : std::max<int64_t>(0, std::min(n, size));
+  return (double)tri_count((used + 31) / 32) * 1024.0 * (double)n;
+}
+
 static void fw_square_all(u32* D, int64_t ld, int n, FwBatch bt, hipStream_t s) {
   const int nq = fw_squarings(n);
+  double relax = bt.hsizes ? 0 : bt.batch * square_relax(n, -1);
+  for (int i = 0; bt.hsizes && i < bt.batch; i++)
+    relax += square_relax(n, std::max(0, bt.hsizes[i] - bt.at.first));
   for (int q = 0; q < nq; q++)
     k_fw_square<<<dim3((unsigned)tri_count(n / 32), (unsigned)bt.batch), 256, 0, s>>>(D, ld, n / 32, bt.at,
-                                                                                     q, nq);
+                                                                                     q, nq, (unsigned long long)relax);
 }
 
 // A whole matrix of up to 512 vertices is one block.
@@ -603,8 +619,8 @@ int fw_rounds_count(int nt, int tile, int pivot) {
 }
 
 hipError_t launch_dense_fw(u32* A, int64_t ld, int tile, int nt, hipStream_t s, hipEvent_t* ev,
-                           int kc, int pivot, u32* flags) {
-  return launch_dense_fw_batch(A, ld, tile, nt, 1, 0, s, ev, kc, pivot, flags);
+                           int kc, int pivot, FwWork work) {
+  return launch_dense_fw_batch(A, ld, tile, nt, 1, 0, s, ev, kc, pivot, work);
 }
 
 static hipError_t dense_lookahead(u32* A, int64_t ld, int tile, int nt, FwBatch bt, hipStream_t s,
@@ -626,15 +642,15 @@ static hipError_t dense_lookahead(u32* A, int64_t ld, int tile, int nt, FwBatch 
 
 hipError_t launch_dense_fw_lookahead(u32* A, int64_t ld, int tile, int nt, hipStream_t s,
                                      hipStream_t side, hipEvent_t* sync, hipEvent_t* ev, int kc,
-                                     int pivot, hipStream_t p1, u32* flags) {
-  return dense_lookahead(A, ld, tile, nt, FwBatch{1, FwAt{0, nullptr, nullptr, flags, nullptr, 0}}, s, side, p1, sync, ev, kc, pivot);
+                                     int pivot, hipStream_t p1, FwWork work) {
+  return dense_lookahead(A, ld, tile, nt, FwBatch{1, FwAt{0, nullptr, nullptr, work, nullptr, 0}, nullptr}, s, side, p1, sync, ev, kc, pivot);
 }
 
 hipError_t launch_dense_fw_batch_lookahead(u32* A, int64_t ld, int tile, int nt, int batch,
                                            int64_t gstride, hipStream_t s, hipStream_t side,
-                                           hipEvent_t* sync, hipEvent_t* ev, int kc, int pivot, u32* flags,
-                                           const int32_t* sizes) {
-  return dense_lookahead(A, ld, tile, nt, FwBatch{batch, FwAt{gstride, nullptr, nullptr, flags, sizes, 0}}, s, side,
+                                           hipEvent_t* sync, hipEvent_t* ev, int kc, int pivot, FwWork work,
+                                           FwSizes sizes) {
+  return dense_lookahead(A, ld, tile, nt, FwBatch{batch, FwAt{gstride, nullptr, nullptr, work, sizes.dev, 0}, sizes.host}, s, side,
                          nullptr, sync, ev, kc, pivot);
 }
 #undef CHK
@@ -664,31 +680,26 @@ static hipError_t dense_rounds(u32* A, int64_t ld, int tile, int nt, FwBatch bt,
 }
 
 hipError_t launch_dense_fw_batch(u32* A, int64_t ld, int tile, int nt, int batch, int64_t gstride,
-                                 hipStream_t s, hipEvent_t* ev, int kc, int pivot, u32* flags, const int32_t* sizes) {
-  return dense_rounds(A, ld, tile, nt, FwBatch{batch, FwAt{gstride, nullptr, nullptr, flags, sizes, 0}}, s, ev, kc,
+                                 hipStream_t s, hipEvent_t* ev, int kc, int pivot, FwWork work, FwSizes sizes) {
+  return dense_rounds(A, ld, tile, nt, FwBatch{batch, FwAt{gstride, nullptr, nullptr, work, sizes.dev, 0}, sizes.host}, s, ev, kc,
                       pivot);
 }
 
 hipError_t launch_dense_fw_list(u32* A, int64_t ld, int tile, int nt, int batch, const int32_t* order,
-                                const int64_t* moff, hipStream_t s, int kc, int pivot, u32* flags) {
-  return dense_rounds(A, ld, tile, nt, FwBatch{batch, FwAt{0, order, moff, flags, nullptr, 0}}, s, nullptr, kc, pivot);
+                                const int64_t* moff, hipStream_t s, int kc, int pivot, FwWork work) {
+  return dense_rounds(A, ld, tile, nt, FwBatch{batch, FwAt{0, order, moff, work, nullptr, 0}, nullptr}, s, nullptr, kc, pivot);
 }
 
 // Executed relaxations of a matrix closed in a batch of `batch`: per round the
-// pivot block (one tile: T^3; more: squarings, or the rounds over half-size
-// blocks on it), the panel (each of its tiles K = block rows) and the
+// pivot block (one tile: T^3; more: squarings, which are counted as they run, or the
+// rounds over half-size blocks on it), the panel (each of its tiles K = block rows) and the
 // upper-triangle interior tiles; `inner` gets the interior part.
-static double square_relax(int64_t n, int64_t size) {
-  const int64_t used = size < 0 ? n : std::max<int64_t>(0, std::min(n, size));
-  return (double)fw_squarings((int)n) * (double)tri_count((used + 31) / 32) * 1024.0 * (double)n;
-}
-
 double dense_fw_exec_relax(int64_t nt, int tile, int pivot, double* inner, int batch, int64_t size) {
   const double t3 = (double)tile * tile * tile;
   const int ptiles = pivot_tiles_of(tile, pivot);
   const int64_t used = size < 0 ? nt : std::min(nt, (size + tile - 1) / tile);  // tiles not padding
   if (inner) *inner = 0;
-  if (fw_all_squaring(tile, (int)nt, ptiles, batch)) return square_relax(nt * tile, size);
+  if (fw_all_squaring(tile, (int)nt, ptiles, batch)) return 0;
   std::vector<FwBlock> blk(fw_blocks((int)nt, ptiles, nullptr));
   fw_blocks((int)nt, ptiles, blk.data());
   double all = 0, in = 0;
@@ -697,7 +708,7 @@ double dense_fw_exec_relax(int64_t nt, int tile, int pivot, double* inner, int b
     if (mine <= 0) break;
     const int64_t left = size < 0 ? -1 : size - (int64_t)b.c0 * tile;
     all += b.pt == 1                           ? t3
-           : fw_by_squaring(tile, b.pt, batch) ? square_relax(b.pt * tile, left)
+           : fw_by_squaring(tile, b.pt, batch) ? 0.0
                                                : dense_fw_exec_relax(b.pt, tile, b.pt / 2 * tile, nullptr, batch, left);
     if (nt <= b.pt) continue;
     all += (double)mine * (used - mine) * b.pt * t3;

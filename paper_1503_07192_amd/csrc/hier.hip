@@ -227,12 +227,35 @@ __global__ void k_hier_vmeta(int32_t V, const int32_t* __restrict__ bgcomp, cons
   if (meta) meta[x] = make_int4(bgoff[c] - gbg0[s], nb[c], bglocal[x], 0);
 }
 
+// The counters' sums into `out` (pinned host memory; see launch_counts), and the
+// counters cleared for the next replay.  By one wave.
+__device__ __forceinline__ void counts_out(unsigned long long* exec, unsigned long long* out) {
+  static_assert(MP_EXEC == 32, "two times sixteen counters, summed by sixteen lanes");
+  const int l = threadIdx.x;
+  unsigned long long n = l < EXEC_WORDS ? exec[l] : 0ull;
+  if (l < EXEC_WORDS) exec[l] = 0ull;
+  const unsigned long long comps = __shfl(n, MP_EXEC), bg = __shfl(n, MP_EXEC + 1);
+  for (int o = 8; o > 0; o >>= 1) n += __shfl_xor(n, o);
+  const unsigned long long second = __shfl(n, MP_EXEC / 2);
+  if (l == 0) {
+    out[0] = n + second + bg;
+    out[1] = second;
+    out[2] = comps;
+  }
+}
+
+__global__ __launch_bounds__(64) void k_counts(unsigned long long* exec, unsigned long long* out) {
+  counts_out(exec, out);
+}
+
 // Flat method: row x of the closed BG matrix into the blocked store of one
 // group (the layout above with S1 = S2 = the only group).
 __global__ void k_flat_store(int32_t V, int64_t Vp, const u32* __restrict__ BG,
                              const int32_t* __restrict__ bgrow, const int32_t* __restrict__ bgnb,
-                             const int32_t* __restrict__ bglocal, u32* __restrict__ H) {
+                             const int32_t* __restrict__ bglocal, u32* __restrict__ H,
+                             unsigned long long* exec, unsigned long long* counted) {
   const int64_t x = blockIdx.x;
+  if (x == 0 && threadIdx.x < 64) counts_out(exec, counted);
   const u32* row = BG + x * Vp;
   const int64_t rb = (int64_t)bgrow[x] * V, nbx = bgnb[x], locx = bglocal[x];
   for (int32_t y = threadIdx.x; y < V; y += blockDim.x)
@@ -1103,19 +1126,6 @@ __global__ __launch_bounds__(64) SPQ_MP_ATTR void k_mp_prod(MpArgs a) {
   }
 }
 
-// What the products counted: all of it and the level-2 second products' part into
-// `out` (pinned host memory), the counters cleared for the next replay.
-__global__ __launch_bounds__(64) void k_mp_counts(unsigned long long* exec, unsigned long long* out) {
-  unsigned long long n = (int)threadIdx.x < MP_EXEC ? exec[threadIdx.x] : 0ull;
-  if ((int)threadIdx.x < MP_EXEC) exec[threadIdx.x] = 0ull;
-  for (int o = 8; o > 0; o >>= 1) n += __shfl_xor(n, o);
-  const unsigned long long dominant = __shfl(n, MP_EXEC / 2);
-  if (threadIdx.x == 0) {
-    out[0] = n + dominant;
-    out[1] = dominant;
-  }
-}
-
 // ------------------------------------------------------------- level 3
 // The construction once more, on BG2, when BG2 itself is too large for one
 // flat Floyd-Warshall: super-groups T of consecutive groups; M3[T] = BG2
@@ -1587,9 +1597,9 @@ hipError_t launch_hier_level1(const HierArgs& a, hipStream_t s) {
   hipError_t e = (a.side && ntg > 1)
                      ? launch_dense_fw_batch_lookahead(a.Mg, a.Vgp, 128, ntg, a.ngroups,
                                                        (int64_t)a.Vgp * a.Vgp, s, a.side, a.sync,
-                                                       nullptr, a.kc, a.pivot, a.fw_flags, a.gV)
+                                                       nullptr, a.kc, a.pivot, a.fw, FwSizes{a.gV, a.h_gV})
                      : launch_dense_fw_batch(a.Mg, a.Vgp, 128, ntg, a.ngroups, (int64_t)a.Vgp * a.Vgp,
-                                             s, nullptr, a.kc, a.pivot, a.fw_flags, a.gV);
+                                             s, nullptr, a.kc, a.pivot, a.fw, FwSizes{a.gV, a.h_gV});
   if (e != hipSuccess) return e;
   k_b2_scan<<<(unsigned)a.ngroups, 256, 0, s>>>(a.gbg0, a.gV, a.flag2, a.Vgp, a.b2list, a.b2rank, a.m2);
   return hipGetLastError();
@@ -1618,8 +1628,8 @@ hipError_t launch_hier_level2_close(const HierArgs& a, hipStream_t s) {
   const int nt = (int)(a.V2p / 128);
   if (a.side && nt > 1)
     return launch_dense_fw_lookahead(a.BG2, a.V2p, 128, nt, s, a.side, a.sync, nullptr, a.kc, a.pivot,
-                                     nullptr, a.fw_flags);
-  return launch_dense_fw(a.BG2, a.V2p, 128, nt, s, nullptr, a.kc, a.pivot, a.fw_flags);
+                                     nullptr, a.fw);
+  return launch_dense_fw(a.BG2, a.V2p, 128, nt, s, nullptr, a.kc, a.pivot, a.fw);
 }
 
 // Buffers and launch shapes of the composition's kernels (Kp: rows per slot,
@@ -1685,9 +1695,8 @@ static hipError_t compose_level2(const HierArgs& a, const int32_t* bglabel, u32*
   return hipGetLastError();
 }
 
-hipError_t launch_mp_counts(const MpWork& w, unsigned long long* out, hipStream_t s) {
-  static_assert(MP_EXEC == 32, "two times sixteen counters, summed by sixteen lanes");
-  k_mp_counts<<<1, 64, 0, s>>>(w.exec, out);
+hipError_t launch_counts(unsigned long long* exec, unsigned long long* out, hipStream_t s) {
+  k_counts<<<1, 64, 0, s>>>(exec, out);
   return hipGetLastError();
 }
 
@@ -1698,11 +1707,12 @@ hipError_t launch_hier_level2_compose(const HierArgs& a, hipStream_t s) {
 hipError_t launch_flat_store(int32_t V, int64_t Vp, const u32* BG, const int32_t* bgcomp,
                              const int32_t* bgoff, const int32_t* nb, const int32_t* grp,
                              const int32_t* gbg0, int32_t* bgrow, int32_t* bgnb, int32_t* bggrp,
-                             const int32_t* bglocal, u32* H, hipStream_t s) {
-  if (V <= 0) return hipSuccess;
+                             const int32_t* bglocal, u32* H, unsigned long long* exec,
+                             unsigned long long* counted, hipStream_t s) {
+  if (V <= 0) return launch_counts(exec, counted, s);
   k_hier_vmeta<<<hblocks(V), 256, 0, s>>>(V, bgcomp, bgoff, nb, grp, gbg0, bglocal, bgrow, bgnb, bggrp,
                                           nullptr);
-  k_flat_store<<<(unsigned)V, 256, 0, s>>>(V, Vp, BG, bgrow, bgnb, bglocal, H);
+  k_flat_store<<<(unsigned)V, 256, 0, s>>>(V, Vp, BG, bgrow, bgnb, bglocal, H, exec, counted);
   return hipGetLastError();
 }
 
@@ -1716,9 +1726,9 @@ hipError_t launch_level3_a(const L3Args& a, hipStream_t s) {
   hipError_t e = (a.side && ntt > 1)
                      ? launch_dense_fw_batch_lookahead(a.M3, a.V3gp, 128, ntt, a.nT,
                                                        (int64_t)a.V3gp * a.V3gp, s, a.side, a.sync,
-                                                       nullptr, a.kc, a.pivot, a.fw_flags, a.tsize)
+                                                       nullptr, a.kc, a.pivot, a.fw, FwSizes{a.tsize, a.h_tsize})
                      : launch_dense_fw_batch(a.M3, a.V3gp, 128, ntt, a.nT, (int64_t)a.V3gp * a.V3gp,
-                                             s, nullptr, a.kc, a.pivot, a.fw_flags, a.tsize);
+                                             s, nullptr, a.kc, a.pivot, a.fw, FwSizes{a.tsize, a.h_tsize});
   if (e != hipSuccess) return e;
   if (a.m > 0)
     k_l3_edges<<<hblocks(a.m), 256, 0, s>>>(a.m, a.eu, a.ev, a.w, a.comp, a.local, a.bgoff, a.grp,
@@ -1741,8 +1751,8 @@ hipError_t launch_level3_b(const L3Args& a, hipStream_t s) {
     const int nt = (int)(a.V3p / 128);
     hipError_t e = (a.side && nt > 1)
                        ? launch_dense_fw_lookahead(a.BG3, a.V3p, 128, nt, s, a.side, a.sync, nullptr,
-                                                   a.kc, a.pivot, nullptr, a.fw_flags)
-                       : launch_dense_fw(a.BG3, a.V3p, 128, nt, s, nullptr, a.kc, a.pivot, a.fw_flags);
+                                                   a.kc, a.pivot, nullptr, a.fw)
+                       : launch_dense_fw(a.BG3, a.V3p, 128, nt, s, nullptr, a.kc, a.pivot, a.fw);
     if (e != hipSuccess) return e;
   }
   return launch_level3_compose(a, s);
@@ -1790,7 +1800,7 @@ hipError_t launch_share_prepare(const HierArgs& a, const ShareBlocks& b, hipStre
                                                b.gblk, b.bfirst, a.b2off, a.b2rank, b.bpmax, b.A);
     hipError_t e = launch_dense_fw_batch(b.A, b.bpmax, 128, b.bpmax / 128, b.nblk,
                                          (int64_t)b.bpmax * b.bpmax, s, nullptr, a.kc, a.pivot,
-                                         a.fw_flags, b.bsize);
+                                         a.fw, FwSizes{b.bsize, b.h_bsize});
     if (e != hipSuccess) return e;
   }
   k_dt_init<<<(unsigned)a.V2p, 256, 0, s>>>(a.V2, a.S2, a.S2p, b.nblk, b.boff, b.bpmax, b.A, a.DT);

@@ -90,9 +90,26 @@ constexpr int MP_EXEC = 32;
 // Kp: rows per XT slot (a multiple of 128), Vp: their length (likewise)
 int64_t mp_stats_words(int32_t Kp, int32_t Vp);
 int64_t mp_mask_words(int32_t Kp, int32_t Vp);
-// after the last product: out[0] all that was counted, out[1] the level-2 second
-// products' part; clears the counters
-hipError_t launch_mp_counts(const MpWork& w, unsigned long long* out, hipStream_t s);
+// The index's counters of executed relaxations: MP_EXEC of the products, then the
+// squarings of the components and those of BG.  At the end of a build or replay their
+// sums go to `out` and they are cleared: out[0] the products and BG's squarings, out[1]
+// the level-2 second products, out[2] the components' squarings.
+constexpr int EXEC_WORDS = MP_EXEC + 2;
+hipError_t launch_counts(unsigned long long* exec, unsigned long long* out, hipStream_t s);
+
+// Scratch of a dense closure (fw.hip), not shared with one that may run at the same
+// time: FW_FLAGS device words of any content, with which squarings past the last useful
+// one end at once, and a counter that the relaxations of the others are added to.
+constexpr int FW_FLAGS = 16;
+struct FwWork {
+  u32* flags = nullptr;
+  unsigned long long* ran = nullptr;
+};
+// Vertices of each matrix of a batch, on the device and on the host; the rest of a
+// matrix is padding (0 on the diagonal, INF elsewhere).
+struct FwSizes {
+  const int32_t *dev = nullptr, *host = nullptr;
+};
 
 // Two-level BG (hier.hip).
 struct HierArgs {
@@ -105,6 +122,7 @@ struct HierArgs {
   const int64_t* moff;
   const u32* M;
   const int32_t *grp, *gbg0, *gV;  // [k], [ngroups], [ngroups]
+  const int32_t* h_gV;             // gV on the host
   int32_t *bgrow, *bgnb, *bggrp;   // [V]
   u32* Mg;                         // ngroups x Vgp x Vgp
   uint8_t* flag2;                  // [V]
@@ -128,7 +146,7 @@ struct HierArgs {
   int64_t d2tld = 0;               //   its leading dimension
   int32_t npairs, chunk;           //   their count, pairs per launch (XT slots)
   MpWork work;
-  u32* fw_flags = nullptr;         // launch_dense_fw's flags
+  FwWork fw;                       // of the closures
   hipEvent_t* evt;                 // NULL, or 2 per composition launch (second product)
   // exactness certificate fused into the composition (NULL: off)
   const int32_t* bglabel;
@@ -148,6 +166,7 @@ struct ShareBlocks {
   int32_t nblk, bpmax;
   bool multi;
   const int32_t *bfirst, *gblk, *boff, *bsize;
+  const int32_t* h_bsize;  // bsize on the host
   u32* A;
 };
 hipError_t launch_share_prepare(const HierArgs& a, const ShareBlocks& b, hipStream_t s);
@@ -198,10 +217,12 @@ hipError_t launch_share_compose(const HierArgs& a, const u32* DT, hipStream_t s)
 hipError_t launch_hier_level1(const HierArgs& a, hipStream_t s);
 // Flat method: per-BG-vertex layout terms, then the closed BG matrix (Vp x Vp)
 // copied into the blocked store of a single group.
+// (exec, counted: as launch_counts, in the same launch)
 hipError_t launch_flat_store(int32_t V, int64_t Vp, const u32* BG, const int32_t* bgcomp,
                              const int32_t* bgoff, const int32_t* nb, const int32_t* grp,
                              const int32_t* gbg0, int32_t* bgrow, int32_t* bgnb, int32_t* bggrp,
-                             const int32_t* bglocal, u32* H, hipStream_t s);
+                             const int32_t* bglocal, u32* H, unsigned long long* exec,
+                             unsigned long long* counted, hipStream_t s);
 // level 2 in three steps: R_S and the unclosed BG2 matrix; its closure by
 // flat Floyd-Warshall (or by level 3 below); the composition into H
 hipError_t launch_hier_level2_prep(const HierArgs& a, bool bg2, hipStream_t s);
@@ -230,7 +251,8 @@ struct L3Args {
   u32 *R3, *BG3;                       // nT x m3pmax x V3gp, V3p x V3p
   u32* XT3;                            // chunk x m3pmax x V3gp
   MpWork work;
-  u32* fw_flags = nullptr;         // launch_dense_fw's flags
+  FwWork fw;                       // of the closures
+  const int32_t* h_tsize;              // tsize on the host
   const int2* plist;                   // super-group pairs T1 <= T2
   int32_t npairs, chunk;               //   their count, pairs per launch
 };
@@ -284,36 +306,34 @@ hipError_t launch_comp_fw(int32_t count, const int32_t* order, const int32_t* P,
 hipError_t launch_bg_assembly(const BgArgs& a, hipStream_t s);
 // ev: NULL, or two events per round recorded around its interior-tile
 // launch(es); kc: K chunk of the interior-tile kernel, 16 or 32 (0 = default);
-// pivot: rows per pivot block, the tile (or 0) or twice the tile (see fw.hip);
-// flags: FW_FLAGS device words of any content, not shared with a closure that may
-// run at the same time, with which squarings past the last useful one end at once
-constexpr int FW_FLAGS = 16;
+// pivot: rows per pivot block, the tile (or 0) or twice the tile (see fw.hip)
 hipError_t launch_dense_fw(u32* A, int64_t ld, int tile, int nt, hipStream_t s, hipEvent_t* ev,
-                           int kc = 0, int pivot = 0, u32* flags = nullptr);
-// `batch` matrices of the same shape, gstride elements apart; sizes: NULL, or [batch]
-// vertices of each, the rest being padding (0 on the diagonal, INF elsewhere)
+                           int kc = 0, int pivot = 0, FwWork work = {});
+// `batch` matrices of the same shape, gstride elements apart; sizes: none (all of each
+// matrix), or [batch]
 hipError_t launch_dense_fw_batch(u32* A, int64_t ld, int tile, int nt, int batch, int64_t gstride,
                                  hipStream_t s, hipEvent_t* ev, int kc = 0, int pivot = 0,
-                                 u32* flags = nullptr, const int32_t* sizes = nullptr);
+                                 FwWork work = {}, FwSizes sizes = {});
 // `batch` matrices of the same shape at A + moff[order[i]] (device arrays)
 hipError_t launch_dense_fw_list(u32* A, int64_t ld, int tile, int nt, int batch, const int32_t* order,
                                 const int64_t* moff, hipStream_t s, int kc = 0, int pivot = 0,
-                                u32* flags = nullptr);
+                                FwWork work = {});
 // Same closure with a lookahead over two streams (side: created by the caller,
 // default priority; sync: two events), or three with p1 (part 1 of every
 // round beside part 2; sync: three events).
 hipError_t launch_dense_fw_lookahead(u32* A, int64_t ld, int tile, int nt, hipStream_t s,
                                      hipStream_t side, hipEvent_t* sync, hipEvent_t* ev, int kc,
-                                     int pivot = 0, hipStream_t p1 = nullptr, u32* flags = nullptr);
+                                     int pivot = 0, hipStream_t p1 = nullptr, FwWork work = {});
 // the lookahead closure of `batch` matrices, gstride elements apart
 hipError_t launch_dense_fw_batch_lookahead(u32* A, int64_t ld, int tile, int nt, int batch,
                                            int64_t gstride, hipStream_t s, hipStream_t side,
                                            hipEvent_t* sync, hipEvent_t* ev, int kc, int pivot,
-                                           u32* flags = nullptr, const int32_t* sizes = nullptr);
+                                           FwWork work = {}, FwSizes sizes = {});
 // rounds of a single-matrix closure (pivot blocks)
 int fw_rounds_count(int nt, int tile, int pivot);
 // relaxations executed by launch_dense_fw and its batches on one matrix of `batch`
-// (diagonal, panel and upper-triangle interior tiles of every round), of whose rows
+// (diagonal, panel and upper-triangle interior tiles of every round; without the
+// squarings, which FwWork::ran counts as they run), of whose rows
 // only the first `size` are vertices (< 0: all); *inner (optional) = the interior part
 double dense_fw_exec_relax(int64_t nt, int tile, int pivot = 0, double* inner = nullptr, int batch = 1,
                            int64_t size = -1);
