@@ -517,7 +517,7 @@ __global__ __launch_bounds__(256) void k_mp_stats(MpArgs a) {
   const u32* A = m.A + x0;
   auto load = [&](int32_t k) -> uint4 {
     const u32* p = A + (int64_t)k * m.lda + x;
-    if (x + 3 < nx) return *reinterpret_cast<const uint4*>(p);
+    if (x + 3 < nx) return load_words4(p);  // (the first product's rows start anywhere)
     return make_uint4(x < nx ? p[0] : INF, x + 1 < nx ? p[1] : INF, x + 2 < nx ? p[2] : INF, INF);
   };
   {
@@ -996,7 +996,7 @@ __global__ __launch_bounds__(64) SPQ_MP_ATTR void k_mp_prod(MpArgs a) {
             const int32_t x = h * 32 + ly * 4, nx = m.rows - x0 - x;
             const u32* ap = A + (int64_t)r * m.lda + x;
             if (nx >= 4) {
-              const uint4 v = *reinterpret_cast<const uint4*>(ap);
+              const uint4 v = load_words4(ap);
               c[h * 4][j] = v.x;
               c[h * 4 + 1][j] = v.y;
               c[h * 4 + 2][j] = v.z;

@@ -376,7 +376,7 @@ __global__ void k_vrec(int32_t n, const int32_t* __restrict__ comp, const int32_
 #endif
 
 __device__ __forceinline__ uint4 load4_upto(const u32* p, int valid) {
-  if (valid >= 4) return *reinterpret_cast<const uint4*>(p);
+  if (valid >= 4) return load_words4(p);
   return make_uint4(valid > 0 ? p[0] : INF, valid > 1 ? p[1] : INF, valid > 2 ? p[2] : INF, INF);
 }
 

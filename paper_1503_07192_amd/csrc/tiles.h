@@ -79,6 +79,14 @@ __device__ __forceinline__ void wait_loads() {
   asm volatile("" ::: "memory");
 }
 
+// Four consecutive words that start at any word: one 16-byte load (global memory takes
+// those at 4-byte alignment), and the compiler is promised no more than that.
+__device__ __forceinline__ uint4 load_words4(const u32* p) {
+  typedef u32 words4 __attribute__((ext_vector_type(4), aligned(4)));
+  const words4 v = *reinterpret_cast<const words4*>(p);
+  return make_uint4(v.x, v.y, v.z, v.w);
+}
+
 template <int T>
 __device__ __forceinline__ void tile_load(u32 (&c)[T / 16][T / 16], const u32* __restrict__ g,
                                           int64_t ld) {
