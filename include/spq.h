@@ -63,8 +63,8 @@ typedef struct {
                           2 two-level */
   int32_t group_comps; /* two-level: consecutive components per group
                           (0 = auto: up to 131,072 BG vertices the power of
-                          two estimated fastest, above about 4,096 BG
-                          vertices per group).  A
+                          two estimated fastest with the level3_groups given,
+                          above about 4,096 BG vertices per group).  A
                           share build with 100 groups or more cuts a group
                           that is wider (in 128-tiles of BG vertices) than
                           the 99th percentile into halves of consecutive
@@ -137,8 +137,10 @@ typedef struct {
                               is kept beside it) */
   double relax_comp;       /* sum over C of |C|^3: Floyd-Warshall relaxations, Phase 2 */
   double relax_bg;         /* v_bg^3: Floyd-Warshall relaxations in BG, Phase 3 */
-  double relax_comp_exec;  /* relaxations the kernels execute for Phase 2 (padded
-                              tiles; symmetric tiles computed once) */
+  double relax_comp_exec;  /* relaxations the kernels executed for Phase 2 in the
+                              last build or replay (padded tiles; symmetric
+                              tiles computed once; squarings and pruned
+                              products as far as they ran) */
   double relax_bg_exec;    /* same for BG */
   double relax_dominant;   /* executed by the launches of the dominant BG kernel:
                               interior tiles (flat) or the composition product
@@ -181,8 +183,12 @@ typedef struct {
  *   out           receives the index; on error *out is NULL
  * The inputs are read during the call only and stay owned by the caller.
  * The call blocks until the partition sizes are known (one small device to
- * host copy), then queues the remaining work on `stream` and returns; the
- * index is usable by work queued later on the same stream.
+ * host copy; two-level also until the groups' boundary sizes are, with level 3
+ * the super-groups'), then queues the remaining work on `stream` and returns;
+ * the index is usable by work queued later on the same stream.  The two-level
+ * method's scratch (up to 2 GiB per level where memory allows) goes back to the
+ * library's cache behind that work; with SPQ_GRAPH the index keeps it for its
+ * replays, then at most half of its distance store or 256 MiB.
  * BG distances are closed either by Floyd-Warshall on the whole BG matrix
  * (flat) or by the two-level method: BG split into groups of consecutive
  * components, each group closed, the graph of the group boundaries closed,

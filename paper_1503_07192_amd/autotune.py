@@ -69,8 +69,8 @@ def candidates(v_bg: int, k: int, share_comps: int):
         for kc in (16, 32):
             out.append({"bg_method": 2, "group_comps": cpg, "inner_kc": kc})
         if v_bg > 65536 and cpg in (16, 32):
-            # BG2 closed by super-groups of fewer or more groups than the
-            # automatic choice (about 4,096 BG2 vertices each)
+            # BG2 closed by super-groups of so many groups (the automatic choice
+            # takes the power of two that it estimates fastest)
             for l3 in (8, 32):
                 out.append({"bg_method": 2, "group_comps": cpg, "inner_kc": 16,
                             "level3_groups": l3})

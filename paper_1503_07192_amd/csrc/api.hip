@@ -896,8 +896,8 @@ static Bg2Plan bg2_plan(const spq_index* X, int32_t G, double comps, double v2, 
 // best of all groupings 57); partitions that cut everywhere (shuffled) stay flat.  Above
 // PLAN_MAX BG vertices the groups stay at about 4,096.  level3: the caller's
 // level3_groups; without level 3 BG2 is closed flat, which few wide groups keep
-// small (118,395 BG vertices: 128 groups leave 29,500 of BG2, 0.47 s, 32 groups
-// 13,600, 0.05).
+// small (118,395 BG vertices: 128 groups leave 29,499 of BG2 and build in 441 ms, 32
+// groups 13,623 and 119).
 constexpr int32_t PLAN_MAX = 131072;
 struct TwoLevelPlan {
   int32_t cpg;
@@ -1055,8 +1055,11 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
   X->m = m;
   X->tile = tile;
   // default: four-tile blocks for the flat BG closure (measured 388 against
-  // 408 ms on a 27,904-wide matrix), two-tile blocks for the other closures
-  // (four measured 10 ms slower on the 256-group composition's closures)
+  // 408 ms on a 27,904-wide matrix), two-tile blocks for the other closures.
+  // Builds with one, two and four there (blocks closed by squarings): a 256 x 256
+  // grid in 16 groups, 4 super-groups 10.9, 9.7 and 10.4 ms; 400,000 Delaunay
+  // vertices in 128 groups 61.1, 58.3 and 58.6; the share of a 1024 x 1024 grid 45.7,
+  // 44.6 and 44.8
   X->pivot = pivot ? pivot : 4 * tile;
   X->cpivot = pivot ? pivot / tile * 128 : 256;
   X->graph = use_graph;
@@ -1487,7 +1490,7 @@ spq_status spq_build_index(int32_t n, int64_t m, const int32_t* eu, const int32_
                        hipMemcpyHostToDevice, s));
     ha.m2pmax = X->m2pmax; ha.V2 = X->V2; ha.V2p = X->V2p; ha.b2off = X->b2off; ha.R = X->R;
     ha.XT = X->XT; ha.BG2 = X->BG2; ha.H = X->H; ha.pairbase = X->pairbase;
-      ha.plist = X->plist; ha.npairs = X->npairs; ha.chunk = X->chunk;
+    ha.plist = X->plist; ha.npairs = X->npairs; ha.chunk = X->chunk;
     if (X->certify) {
       ha.bglabel = X->bglabel;
       ha.cert_bad = X->cert + 1;

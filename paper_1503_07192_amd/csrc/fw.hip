@@ -15,7 +15,7 @@ namespace spq {
 // Blocked Floyd-Warshall on one symmetric matrix of nt x nt tiles, in rounds
 // over pivot blocks of one, two or four tiles (the tiles left at the end form
 // smaller blocks):
-//   close    the pivot block: k_fw_diag for one tile; a larger block by
+//   close    the pivot block: k_fw_diag64 or k_fw_diag128 for one tile; a larger block by
 //            squarings (k_fw_square) or, in large batches, by the same rounds on
 //            the sub-matrix, over blocks of half its size
 //   panel    tile (a, j), a in the block, j outside it: tile (a, j) =

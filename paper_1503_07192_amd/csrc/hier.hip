@@ -371,7 +371,7 @@ struct CompStore {
 // k'.  So with U[y] = min over k' of mx[k'] + B[k'][y], reached first at
 // arg[y], the rows X x columns Y of the product need only the k that some y
 // of Y has as arg[y] or with mn[k] + B[k][y] < U[y]: exactly the same minima
-// from (measured) a quarter to a half of the K.  r is near a row's minimum,
+// from (measured) a seventh to a half of the K.  r is near a row's minimum,
 // so that mx - mn stays small.
 //
 // A column y that is itself one of the K (y in B2 of its group) takes part in
@@ -892,7 +892,7 @@ __device__ __forceinline__ void mp_place(const MpArgs& a, int32_t& slot, int32_t
 // One wave per 64 x 64 tile of a product, over the kept k.  The two 256-byte
 // operand rows of a kept k go straight to LDS, into a ring of MP_RING steps of
 // MP_KC k; waves share nothing, so no barrier holds one up.  8 x 8
-// entries per lane: 128 VGPRs, 8.5 KB of LDS, four waves per SIMD.
+// entries per lane: 128 VGPRs, 9.2 KB of LDS, four waves per SIMD.
 //
 // SIDE 0, the first product: rows b in B2(S2), columns x of S1, stored as XT.
 // SIDE 1: rows x of S1, columns y of S2, stored as the block D(S1, S2) (D(S2,
